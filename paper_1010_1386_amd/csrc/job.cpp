@@ -412,6 +412,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
   // wide CRT items, problem by problem
   for (int pass = 0; pass < 3; ++pass) J->wide_items[pass].clear();
   J->wide_mfma = false;
+  J->wdig_items.clear();
   for (int li = 0; li < nl; ++li) {
     const Plan& P = J->plans[J->live[li]];
     const DevProblem& d = J->dev[li];
@@ -665,14 +666,30 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     J->wide_off[pass] = o;
     o = align_up(o + sizeof(WorkItem) * J->wide_items[pass].size(), A);
   }
+  // CRT constants are laid out once per prime list (problems with the same
+  // canonical list share them); the wide path's digit planes are built on the
+  // device by the owning problem's items
+  {
+    std::map<const CrtConst*, int> crt_owner;
+    for (int li = 0; li < nl; ++li) {
+      const Plan& P = J->plans[J->live[li]];
+      const DevProblem& d = J->dev[li];
+      ProbLayout& L = J->lay[li];
+      const auto own = crt_owner.emplace(P.crt.get(), li);
+      L.crt_own = own.second;
+      L.crt_from = own.first->second;
+      if (L.crt_own && d.wide_mfma)
+        for (int b = 0; b < d.wnpad / kWideMfmaK; ++b)
+          for (int t = 0; t < blocks_of(d.wlpad, kWideDigitLimbs); ++t) J->wdig_items.push_back({li, -1, b, t});
+    }
+  }
+  J->wdig_off = o;
+  o = align_up(o + sizeof(WorkItem) * J->wdig_items.size(), A);
   J->nclr = 0;
   for (int li = 0; li < nl; ++li)
     J->nclr += (J->dev[li].wide ? 1 : 0) + (J->dev[li].evmf ? 1 : 0) + (J->skip_reduce[li] > 0 ? 1 : 0);
   J->clr_off = o;
   o = align_up(o + sizeof(ClearRange) * J->nclr, A);
-  // CRT constants are laid out once per prime list (problems with the same
-  // canonical list share them)
-  std::map<const CrtConst*, int> crt_owner;
   for (int li = 0; li < nl; ++li) {
     const Plan& P = J->plans[J->live[li]];
     const DevProblem& d = J->dev[li];
@@ -681,16 +698,12 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     L.coeff = o; o = align_up(o + static_cast<size_t>(d.ncoef) * d.L_in * 4, 16);
     L.gdeg = o;  o = align_up(o + static_cast<size_t>(d.myp + d.nyp) / kRowGroup * 4, 16);
     L.pidx = o;  o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
-    auto own = crt_owner.find(P.crt.get());
-    if (own != crt_owner.end()) {
-      const ProbLayout& S = J->lay[own->second];
+    if (!L.crt_own) {
+      const ProbLayout& S = J->lay[L.crt_from];
       L.Hm = S.Hm; L.NH = S.NH; L.Mi = S.Mi; L.wdir = S.wdir; L.rinv = S.rinv; L.negM = S.negM;
-      L.Mw = S.Mw; L.wMd = S.wMd; L.NHM = S.NHM; L.Tg = S.Tg; L.invM = S.invM; L.Plimb = S.Plimb;
-      L.crt_own = false;
+      L.Mw = S.Mw; L.NHM = S.NHM; L.Tg = S.Tg; L.invM = S.invM; L.Plimb = S.Plimb;
       continue;
     }
-    crt_owner[P.crt.get()] = li;
-    L.crt_own = true;
     L.Hm = o;    o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
     L.NH = o;    o = align_up(o + static_cast<size_t>(P.L_out) * 4, 16);
     L.Mi = o;    o = align_up(o + static_cast<size_t>(P.np) * P.Lw * 4, 16);
@@ -700,7 +713,6 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     L.Mw = L.NHM = 0;
     if (P.wide) {
       L.Mw = o;  o = align_up(o + static_cast<size_t>(P.Lw) * 4, 16);
-      L.wMd = o; o = align_up(o + static_cast<size_t>(kWideDigits) * d.wlpad * d.wnpad, 16);
       L.NHM = o; o = align_up(o + static_cast<size_t>(P.L_out) * 4, 16);
     }
     if (!P.canonical) {
@@ -775,8 +787,13 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       L.ydig = o; o = align_up(o + planes, A);
       L.hdig = o; o = align_up(o + planes, A);
     }
-    L.wT = L.wq = L.wS = 0;
+    L.wT = L.wq = L.wS = L.wMd = 0;
     if (P.wide) {
+      if (!L.crt_own) {
+        L.wMd = J->lay[L.crt_from].wMd;  // the owner comes first
+      } else if (d.wide_mfma) {
+        L.wMd = o; o = align_up(o + static_cast<size_t>(kWideDigits) * d.wlpad * d.wnpad, A);
+      }
       L.wT = o; o = align_up(o + static_cast<size_t>(d.wdpad) * d.wnpad * 4, A);
       L.wq = o; o = align_up(o + static_cast<size_t>(P.D + 1) * 4, A);
       L.wS = o; o = align_up(o + static_cast<size_t>(P.D + 1) * 2 * P.Lw * 8, A);
@@ -888,15 +905,6 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     if (P.wide) {
       std::memcpy(blob + L.Mw, P.crt->Mw.data(), P.crt->Mw.size() * 4);
       std::memcpy(blob + L.NHM, P.crt->NHM.data(), P.crt->NHM.size() * 4);
-      // 7-bit digit planes of the M_i limbs, [digit][limb][prime], zero padded
-      int8_t* md = reinterpret_cast<int8_t*>(blob + L.wMd);
-      const size_t plane = static_cast<size_t>(d.wlpad) * d.wnpad;
-      for (int i = 0; i < P.np; ++i)
-        for (int t = 0; t < P.Lw; ++t) {
-          const uint32_t m = P.crt->Mi[static_cast<size_t>(i) * P.Lw + t];
-          for (int dd = 0; dd < kWideDigits; ++dd)
-            md[dd * plane + static_cast<size_t>(t) * d.wnpad + i] = static_cast<int8_t>((m >> (7 * dd)) & 127u);
-        }
     }
     if (!P.canonical) {
       std::memcpy(blob + L.Tg, P.crt->Tg.data(), P.crt->Tg.size() * 4);
@@ -919,7 +927,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     d.wT = P.wide ? reinterpret_cast<uint32_t*>(base + L.wT) : nullptr;
     d.wq = P.wide ? reinterpret_cast<uint32_t*>(base + L.wq) : nullptr;
     d.wS = P.wide ? reinterpret_cast<uint64_t*>(base + L.wS) : nullptr;
-    d.wMd = (P.wide && d.wide_mfma) ? reinterpret_cast<const int8_t*>(base + L.wMd) : nullptr;
+    d.wMd = (P.wide && d.wide_mfma) ? reinterpret_cast<int8_t*>(base + L.wMd) : nullptr;
     d.resid = reinterpret_cast<uint32_t*>(base + L.resid);
     d.dig = d.evmf ? reinterpret_cast<uint64_t*>(base + L.dig) : nullptr;
     d.zval = reinterpret_cast<uint32_t*>(base + L.zval);
@@ -990,6 +998,8 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
   for (int pass = 0; pass < 3; ++pass)
     if (!J->wide_items[pass].empty())
       std::memcpy(blob + J->wide_off[pass], J->wide_items[pass].data(), sizeof(WorkItem) * J->wide_items[pass].size());
+  if (!J->wdig_items.empty())
+    std::memcpy(blob + J->wdig_off, J->wdig_items.data(), sizeof(WorkItem) * J->wdig_items.size());
   if (!J->hseg_items.empty())
     std::memcpy(blob + J->hseg_off, J->hseg_items.data(), sizeof(WorkItem) * J->hseg_items.size());
   if (!J->mgroups.empty()) {
@@ -1054,8 +1064,14 @@ int job_upload(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned) {
 
 int job_upload_clear(rsl_ctx* ctx, Job* J, hipStream_t st) {
   // one launch over the clear table the upload brought (ordered after it)
-  return hip_check(ctx, launch_clear_ranges(reinterpret_cast<const ClearRange*>(J->base + J->clr_off), J->nclr, st),
-                   "clear ranges");
+  int rc = hip_check(ctx, launch_clear_ranges(reinterpret_cast<const ClearRange*>(J->base + J->clr_off), J->nclr, st),
+                     "clear ranges");
+  if (!rc)
+    rc = hip_check(ctx, launch_wide_digits(reinterpret_cast<const DevProblem*>(J->base + J->probs_off),
+                                           reinterpret_cast<const WorkItem*>(J->base + J->wdig_off),
+                                           static_cast<int>(J->wdig_items.size()), st),
+                   "wide digits");
+  return rc;
 }
 
 int job_reset(rsl_ctx* ctx, Job* J, hipStream_t st) {

@@ -27,6 +27,7 @@ struct ProbLayout {
   int hseg_begin, hseg_end;        // range of Job::hseg_items
   int L_in;
   bool crt_own;  // this problem's layout holds the CRT constant block it shares
+  int crt_from;  // live index of the problem whose layout holds its CRT constant block
   int item_begin[kNumStages], item_end[kNumStages];
   int wide_begin[3], wide_end[3];  // ranges of Job::wide_items[pass] (wide CRT)
 };
@@ -74,6 +75,8 @@ struct Job {
   // its three passes
   std::vector<WorkItem> wide_items[3];
   bool wide_mfma = false;          // the contraction (pass 1) runs on the matrix cores
+  std::vector<WorkItem> wdig_items;  // limb digit planes, built after the upload (64 primes x 64 limbs each)
+  size_t wdig_off = 0;
   size_t wide_off[3] = {};
   size_t wide_lds[3] = {};
   size_t items_off[kNumStages] = {};
@@ -148,9 +151,10 @@ inline size_t upload_bytes(const Job& J) { return J.with_queue ? J.up_bytes : J.
 // copy is done) or to the context's staging buffer when pinned is null, unless
 // it already is pinned memory bound with job_bind (then it is sent directly).
 int job_upload(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned = nullptr);
-// The two halves of job_upload: the copy of the image, and the clearing
-// launches of the intermediate buffers the kernels expect zeroed (ordered
-// after the copy; they may run on another stream that waits for it).
+// The two halves of job_upload: the copy of the image, and the launches that
+// clear the intermediate buffers the kernels expect zeroed and build the wide
+// CRT's digit planes (ordered after the copy; they may run on another stream
+// that waits for it).
 int job_upload_copy(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned = nullptr);
 int job_upload_clear(rsl_ctx* ctx, Job* J, hipStream_t st);
 // Zero the status words before a persistent run (the staged and plain launches

@@ -2348,6 +2348,39 @@ constexpr int kWideMfmaTT = 32;  // limbs per block
 __host__ __device__ inline int wide_mfma_lds_words() { return kWideDigits * kWideMfmaTT * kWideMfmaK / 4; }
 typedef int wide_v4i __attribute__((ext_vector_type(4)));
 
+// The digit planes Md[b][t][i] from the rows M_i (limbs contiguous): item
+// (problem, blk = 64 primes, sub = 64 limbs), a transposition through LDS.
+// Each block reads 16 KB of limbs once and writes their five digits as
+// 16-byte words of 16 primes (zero beyond the last prime or limb).  Bound by
+// the launch and the stores.  On the host the same loop cost one scattered
+// byte store per digit and 20 MB more upload: 91 of the 101 ms of a call on
+// ten pairs of degree 15 with 2^2048 coefficients.
+constexpr int kWideDigitLimbs = 64;
+constexpr int kWideDigitLdsWords = kWideMfmaK * (kWideDigitLimbs + 1);
+__device__ inline void stage_wide_digits(const DevProblem& P, const WorkItem& w, uint32_t* lds) {
+  const int i0 = w.blk * kWideMfmaK, t0 = w.sub * kWideDigitLimbs;
+  for (int e = threadIdx.x; e < kWideMfmaK * kWideDigitLimbs; e += blockDim.x) {
+    const int ii = e / kWideDigitLimbs, tt = e % kWideDigitLimbs;
+    const int i = i0 + ii, t = t0 + tt;
+    lds[ii * (kWideDigitLimbs + 1) + tt] = (i < P.np && t < P.Lw) ? P.Mi[static_cast<size_t>(i) * P.Lw + t] : 0u;
+  }
+  __syncthreads();
+  const size_t plane = static_cast<size_t>(P.wlpad) * P.wnpad;
+  const int q = threadIdx.x & 3, tt = threadIdx.x >> 2;  // 16 primes of one limb, every digit
+  if (t0 + tt >= P.wlpad) return;
+  uint32_t m[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) m[u] = lds[(16 * q + u) * (kWideDigitLimbs + 1) + tt];
+  int8_t* dst = P.wMd + static_cast<size_t>(t0 + tt) * P.wnpad + i0 + 16 * q;
+#pragma unroll
+  for (int d = 0; d < kWideDigits; ++d) {
+    uint32_t word[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < 16; ++u) word[u >> 2] |= ((m[u] >> (7 * d)) & 127u) << (8 * (u & 3));
+    *reinterpret_cast<uint4*>(dst + d * plane) = make_uint4(word[0], word[1], word[2], word[3]);
+  }
+}
+
 __device__ inline void stage_crt_wide_sum_mfma(const DevProblem& P, const WorkItem& w, uint32_t* lds) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int Lw = P.Lw, nh = 2 * Lw;

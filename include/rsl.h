@@ -143,8 +143,9 @@ typedef struct {
   int32_t eval_lanes;  /* lanes per (prime, point) pair in evaluation: 1, 2 or 4 (an upper
                           bound: problems of low degree use fewer); 0 = chosen from the job
                           size or by the autotuner */
-  int32_t eval_regs;   /* 0: keep both polynomials of a pair in registers when the shape
-                          allows (degrees <= 32 differing by at most one); -1: never */
+  int32_t eval_regs;   /* 0: keep the polynomials of a pair in registers when the shape allows
+                          (one lane per pair: the lower degree up to 48; a lane pair: degrees
+                          <= 32 differing by at most one); -1: never */
   int32_t eval_schur;  /* 1: univariate resultants by the generalised Schur algorithm on
                           the displacement generators of the Sylvester matrix (paper
                           Sec. 4.1), one wave per (prime, point), for problems with
@@ -338,13 +339,13 @@ typedef struct {
   int32_t chunk_target;   /* interpolation chunking of the layout */
   int32_t grid_mult;      /* persistent grid multiplier */
   int32_t eval_lanes;     /* most lanes per (prime, point) pair used by any problem */
-  int32_t eval_mfma;      /* problems whose evaluation sums run on the matrix cores (register form,
-                             one lane or a lane pair per pair, x-degrees up to 32: x-powers
-                             0..31 on the matrix cores, x-power 32 on the vector ALUs) */
+  int32_t eval_mfma;      /* problems with x-degrees up to 32 whose evaluation sums run on the matrix cores
+                             (one lane per pair, or a lane pair in the register form); with one
+                             lane per pair those of x-degrees 33..63 do too, not counted here */
   int64_t mulmods_sums_mfma;  /* of mulmods: evaluation sums taken on the matrix cores */
   int64_t mulmods_valu;       /* of mulmods: the rest (remainder sequences, Horner sums) on the vector ALUs */
   int64_t mfma_int8_macs;     /* int8 multiply-adds the matrix cores issue per run for those sums
-                                 (padded tiles, 25 digit products per residue product) */
+                                 (padded tiles, 16 digit products per residue product) */
   int64_t interp_mulmods;     /* interpolation products per run: N_p (D+1)(D+2) over problems */
 } rsl_job_info;
 

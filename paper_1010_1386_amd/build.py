@@ -24,6 +24,8 @@ PEAK_LIB = os.path.join(PKG, "libpeak.so")
 
 SOURCES = ["kernels.hip", "api.cpp", "plan.cpp", "job.cpp", "tune.cpp", "server.cpp", "persistent.hip", "gcd.cpp",
            "noalloc.cpp"]
+# sources compiled beside a source (in parallel) and linked into its object
+PARTS = {"kernels.hip": ["eval_columns.hip", "eval_lanes.hip", "eval_stream1.hip", "eval_stream2.hip"]}
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          # packed fp32 forms are never wanted in this integer code
@@ -40,8 +42,23 @@ def hipcc():
 
 
 def _compile(src):
-    path = os.path.join(CSRC, src)
+    """The object of one source, with its parts."""
+    parts = PARTS.get(src, [])
+    if not parts:
+        return _compile_one(src, src + ".o")
+    with ThreadPoolExecutor(max_workers=len(parts) + 1) as ex:
+        got = list(ex.map(lambda s: _compile_one(s, s + (".part.o" if s == src else ".o")), [src] + parts))
     obj = os.path.join(BUILD, src + ".o")
+    r = subprocess.run([shutil.which("ld") or "ld", "-r", "-o", obj] + [o for o, _ in got], capture_output=True,
+                       text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"ld -r failed on {src}:\n{r.stderr}")
+    return obj, "\n".join(m for _, m in got if m.strip())
+
+
+def _compile_one(src, name):
+    path = os.path.join(CSRC, src)
+    obj = os.path.join(BUILD, name)
     cmd = [hipcc()] + FLAGS + ["-c", path, "-o", obj]
     if src.endswith(".cpp"):
         cmd = [hipcc()] + FLAGS + ["-x", "hip", "-c", path, "-o", obj]

@@ -1,0 +1,12 @@
+// Streamed evaluation kernels with two K slices (x-powers 0..63) per digit product.
+#include "eval_launch.h"
+
+namespace rsl {
+
+hipError_t launch_eval_stream2(int variant, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
+                               const DevTables& T, hipStream_t st) {
+  launch_eval_variant<kEvQ + 1, kEvNum, 2>(variant, probs, items, nitems, lds, T, st);
+  return hipGetLastError();
+}
+
+}  // namespace rsl

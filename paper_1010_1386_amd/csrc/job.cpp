@@ -159,14 +159,22 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
   }
   const bool regs_ok = !(opts && opts->eval_regs < 0);
   // long_ok: shapes with |m_y - n_y| > 1 have a register form only with one
-  // lane per pair (ures_regs_long, after Horner or the matrix-core sums)
+  // lane per pair (ures_regs_long)
   auto regn_of = [&](const Plan& P, bool long_ok = false) {
     if (!regs_ok || P.my < 1 || P.ny < 1 || (std::abs(P.my - P.ny) > 1 && !long_ok)) return 0;
     for (int nmax : {8, 16, 24, 32})
       if (std::max(P.my, P.ny) <= nmax) return nmax;
     return 0;
   };
-  if (evk <= 0) {
+  // the streamed form (one lane per pair, sums on the matrix cores): the lower
+  // degree in registers, the higher one's values in LDS
+  auto stream_ok = [&](const Plan& P) {
+    return regs_ok && !(ctx && ctx->eval_horner) && std::min(P.my, P.ny) >= 1 &&
+           std::min(P.my, P.ny) <= kStreamDegMax && std::max(P.my, P.ny) <= kStreamLongMax &&
+           P.rowf <= kMfmaXPowers && P.rowg <= kMfmaXPowers;
+  };
+  const bool evk_auto = evk <= 0;
+  if (evk_auto) {
     // the register form needs no cross-lane work: keep one lane per pair for it
     bool all_regs = true;
     for (int k : J->live) all_regs = all_regs && regn_of(J->plans[k]) > 0;
@@ -223,10 +231,18 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     d.kchunk = Kc;
     d.nchunk = (P.D + 1 + d.kchunk - 1) / d.kchunk;
     d.evk = 1;
-    while (d.evk < evk && std::min(P.my, P.ny) >= 4 * d.evk * 2) d.evk *= 2;
+    const bool stream = stream_ok(P);
+    // with no lane count asked for, the streamed form takes every problem it
+    // fits, whatever the job's size: against two lanes per pair on the
+    // degree-24 pair (its smallest use) 30.2 -> 21.9 us, against the LDS columns
+    // on one pair of degrees 43 and 19 154 -> 22.6 us, at degrees 42 and 41
+    // 668 -> 67 us, on 64 requests of degrees 8..48 8.35 -> 0.99 ms.  The bounds
+    // are the registers (lower degree 48), the LDS rows and the K slices; the
+    // shapes within them were all accepted by the column layouts it replaces.
+    if (!(evk_auto && stream))
+      while (d.evk < evk && std::min(P.my, P.ny) >= 4 * d.evk * 2) d.evk *= 2;
     d.evpb = 64 / d.evk;
-    const bool long_ok = d.evk == 1;
-    d.regn = (d.evk <= 2) ? regn_of(P, long_ok) : 0;
+    d.regn = (d.evk <= 2) ? regn_of(P, d.evk == 1) : 0;
     d.schur = (schur_req && P.my >= 1 && P.ny >= 1 && P.my + P.ny <= kSchurMaxR) ? 1 : 0;
     d.newton_all = newton_req ? 1 : 0;
     if (d.schur) {  // one wave per pair, kSchurPts points per block
@@ -235,14 +251,17 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       d.regn = 0;
       J->any_schur = true;
     }
-    // the Horner sums on the matrix cores: the register form (one lane or a
-    // lane pair per (prime, point)), x-powers 0..31 in one K slice of the
-    // products and x-power 32, if any, on the vector ALUs
-    d.evmf = (d.evk <= 2 && d.regn > 0 && !d.schur && P.rowf <= 33 && P.rowg <= 33 && !(ctx && ctx->eval_horner))
-                 ? 1 : 0;
+    // the Horner sums on the matrix cores: the streamed form, or a lane pair
+    // per (prime, point) for x-degrees up to 32; one K slice of the products
+    // holds x-powers 0..31, two hold 0..63
+    d.evmf = (d.schur || (ctx && ctx->eval_horner)) ? 0
+             : d.evk == 1 ? (stream ? 1 : 0)
+                          : (d.evk == 2 && d.regn > 0 && P.rowf <= 33 && P.rowg <= 33 ? 1 : 0);
+    if (d.evmf && d.evk == 1) d.regn = (std::min(P.my, P.ny) + 7) / 8 * 8;
+    d.dkh = !d.evmf ? 0 : (P.rowf <= 32 && P.rowg <= 32) ? 1 : 2;
     d.dRTf = d.evmf ? dig_rt(P.my + 1) : 0;
     d.dRTg = d.evmf ? dig_rt(P.ny + 1) : 0;
-    d.dfr = kDigits * (d.dRTf + d.dRTg);
+    d.dfr = kEvDigits * d.dkh * (d.dRTf + d.dRTg);
     d.crt_garner = (ctx && ctx->crt_garner) ? 1 : 0;
     d.wide = P.wide ? 1 : 0;
     d.Lw = P.Lw;
@@ -261,14 +280,11 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       const int64_t pts = static_cast<int64_t>(P.np) * (P.E + 1);
       const int64_t sums = pair_mulmods(P) - static_cast<int64_t>(P.my) * P.ny;  // N_f + N_g
       if (d.evmf) {
-        int64_t top = 0;  // terms of x-power 32 (vector ALUs)
-        for (int r : P.f.rdeg) top += (r == 32);
-        for (int r : P.g.rdeg) top += (r == 32);
-        J->mm_sums_mfma += (sums - top) * pts;
-        J->mm_valu += (static_cast<int64_t>(P.my) * P.ny + top) * pts;
-        // 25 int8 16x16x32 products per 16-point tile and 16-row tile
+        J->mm_sums_mfma += sums * pts;
+        J->mm_valu += static_cast<int64_t>(P.my) * P.ny * pts;
+        // int8 16x16x64 products per 16-point tile and 16-row tile (ev_tile_products)
         const int64_t tiles = static_cast<int64_t>(P.np) * blocks_of(P.E + 1, d.evpb) * (d.evpb / 16);
-        J->mfma_macs += tiles * (d.dRTf + d.dRTg) * kDigits * kDigits * 16 * 16 * 32;
+        J->mfma_macs += tiles * (d.dRTf + d.dRTg) * ev_tile_products(d.dkh) * 16 * 16 * 64;
       } else {
         J->mm_valu += pair_mulmods(P) * pts;
       }
@@ -287,7 +303,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       a.pgoff = b.goff;
       a.pCS = b.CS;
       a.pdRTf = b.dRTf;
-      a.pdRTg = b.dRTg;
+      a.pdkh = b.dkh;
       a.pdfr = b.dfr;
     }
 

@@ -21,6 +21,7 @@
 #include <cstdint>
 
 #include "device.h"
+#include "eval_launch.h"
 #include "kernels.h"
 #include "stages.h"
 #include "zgcd.h"
@@ -40,42 +41,14 @@ __global__ __launch_bounds__(256) void k_reduce(const DevProblem* probs, const W
     stage_reduce(probs[w.prob], T, w, true, true);
 }
 
-template <int V>
-__global__ __launch_bounds__(64) void k_eval_ures(const DevProblem* probs, const WorkItem* items, DevTables T) {
-  extern __shared__ uint4 lds4[];  // 16-byte aligned: the Horner loop reads uint4 rows
-  uint32_t* lds = reinterpret_cast<uint32_t*>(lds4);
-  const WorkItem w = items[blockIdx.x];
-  stage_eval_variant<V>(probs[w.prob], T, w, lds);
-}
-
 hipError_t launch_eval(int variant, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
                        const DevTables& T, hipStream_t st) {
   if (nitems <= 0) return hipSuccess;
-  const dim3 g(nitems), b(64);
-  switch (variant) {
-    case kEvBase: hipLaunchKernelGGL(k_eval_ures<kEvBase>, g, b, lds, st, probs, items, T); break;
-    case kEvG2: hipLaunchKernelGGL(k_eval_ures<kEvG2>, g, b, lds, st, probs, items, T); break;
-    case kEvG4: hipLaunchKernelGGL(k_eval_ures<kEvG4>, g, b, lds, st, probs, items, T); break;
-    case kEvR8: hipLaunchKernelGGL(k_eval_ures<kEvR8>, g, b, lds, st, probs, items, T); break;
-    case kEvR16: hipLaunchKernelGGL(k_eval_ures<kEvR16>, g, b, lds, st, probs, items, T); break;
-    case kEvR24: hipLaunchKernelGGL(k_eval_ures<kEvR24>, g, b, lds, st, probs, items, T); break;
-    case kEvR32: hipLaunchKernelGGL(k_eval_ures<kEvR32>, g, b, lds, st, probs, items, T); break;
-    case kEvP8: hipLaunchKernelGGL(k_eval_ures<kEvP8>, g, b, lds, st, probs, items, T); break;
-    case kEvP16: hipLaunchKernelGGL(k_eval_ures<kEvP16>, g, b, lds, st, probs, items, T); break;
-    case kEvP24: hipLaunchKernelGGL(k_eval_ures<kEvP24>, g, b, lds, st, probs, items, T); break;
-    case kEvP32: hipLaunchKernelGGL(k_eval_ures<kEvP32>, g, b, lds, st, probs, items, T); break;
-    case kEvSchur: hipLaunchKernelGGL(k_eval_ures<kEvSchur>, g, b, lds, st, probs, items, T); break;
-    case kEvM8: hipLaunchKernelGGL(k_eval_ures<kEvM8>, g, b, lds, st, probs, items, T); break;
-    case kEvM16: hipLaunchKernelGGL(k_eval_ures<kEvM16>, g, b, lds, st, probs, items, T); break;
-    case kEvM24: hipLaunchKernelGGL(k_eval_ures<kEvM24>, g, b, lds, st, probs, items, T); break;
-    case kEvM32: hipLaunchKernelGGL(k_eval_ures<kEvM32>, g, b, lds, st, probs, items, T); break;
-    case kEvQ8: hipLaunchKernelGGL(k_eval_ures<kEvQ8>, g, b, lds, st, probs, items, T); break;
-    case kEvQ16: hipLaunchKernelGGL(k_eval_ures<kEvQ16>, g, b, lds, st, probs, items, T); break;
-    case kEvQ24: hipLaunchKernelGGL(k_eval_ures<kEvQ24>, g, b, lds, st, probs, items, T); break;
-    case kEvQ32: hipLaunchKernelGGL(k_eval_ures<kEvQ32>, g, b, lds, st, probs, items, T); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  if (variant < 0 || variant >= kEvNum) return hipErrorInvalidValue;
+  const auto launch = variant < kEvP8 ? launch_eval_columns
+                      : variant < kEvQ ? launch_eval_lanes
+                      : (variant - kEvQ) % 2 ? launch_eval_stream2 : launch_eval_stream1;
+  return launch(variant, probs, items, nitems, lds, T, st);
 }
 
 __global__ __launch_bounds__(256) void k_interp_conv(const DevProblem* probs, const WorkItem* items, DevTables T) {

@@ -80,6 +80,48 @@ RSL_HD uint32_t minv(uint32_t a, uint32_t one, uint32_t p, uint32_t pinv) {
   return mpow(a, p - 2u, one, p, pinv);
 }
 
+// Signed residues.  Values are kept as int32 representatives v with |v| <= c p,
+// c a small constant of the code that holds them (1.5 p < 2^31 for every prime
+// of the table).  sredc(t) = t / R mod p with |sredc(t)| <= |t| / R + p / 2: no
+// correction follows the reduction, so a sum of products costs its multiply-
+// adds, one v_mul_lo_u32 and one more multiply-add.  |t| < 2^62.
+struct SignedMod {
+  int32_t p;
+  uint32_t pinv;        // -p^{-1} mod 2^32
+  uint32_t h, hp, hm;   // (p - 1) / 2 and that plus, minus p
+};
+RSL_HD SignedMod signed_mod(const PrimeConst& c) {
+  const uint32_t h = (c.p - 1u) / 2u;
+  return SignedMod{static_cast<int32_t>(c.p), c.pinv, h, h + c.p, h - c.p};
+}
+RSL_HD int64_t smad(int32_t a, int32_t b, int64_t c) { return static_cast<int64_t>(a) * b + c; }
+RSL_HD int32_t sredc(int64_t t, const SignedMod& M) {
+  const int32_t m = static_cast<int32_t>(static_cast<uint32_t>(t) * M.pinv);
+  return static_cast<int32_t>(smad(m, M.p, t) >> 32);
+}
+RSL_HD int32_t smul(int32_t a, int32_t b, const SignedMod& M) { return sredc(smad(a, b, 0), M); }
+// the representative of least absolute value, for |x| < 1.5 p
+RSL_HD int32_t scenter(int32_t x, const SignedMod& M) {
+  const uint32_t w = static_cast<uint32_t>(x);
+  return static_cast<int32_t>(umin32(umin32(w + M.h, w + M.hp), w + M.hm) - M.h);
+}
+// [0, p) for |x| < p
+RSL_HD uint32_t scanon(int32_t x, const SignedMod& M) {
+  const uint32_t w = static_cast<uint32_t>(x);
+  return umin32(w, w + static_cast<uint32_t>(M.p));
+}
+// a^(p-2) in Montgomery form (|a| <= p), a != 0
+RSL_HD int32_t sinv(int32_t a, uint32_t one, const SignedMod& M) {
+  int32_t r = static_cast<int32_t>(one);
+  uint32_t e = static_cast<uint32_t>(M.p) - 2u;
+  while (e) {
+    if (e & 1u) r = smul(r, a, M);
+    e >>= 1;
+    if (e) a = smul(a, a, M);
+  }
+  return r;
+}
+
 // Host-side construction of the constants for one prime.
 inline PrimeConst make_prime_const(uint32_t p) {
   PrimeConst c{};

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(64) void k_persistent(const DevProblem* probs, Queu
       case kTaskReduce:
         for (int b = 0; b * 64 < P.CS; ++b) stage_reduce(P, T, WorkItem{prob, t.slot, b, 0});
         break;
-      case kTaskEval: stage_eval<false>(P, T, w, lds); break;
+      case kTaskEval: stage_eval_columns(P, T, w, lds); break;
       case kTaskConv: stage_interp_conv(P, T, w, lds); break;
       case kTaskStir: stage_interp_stir<false>(P, T, w, lds); break;
       case kTaskNewton: stage_interp_newton(P, T, w, lds); break;

@@ -165,31 +165,50 @@ __device__ inline int tile_coord(const DevProblem& P, int t, int* gp, int* i, in
 }
 
 // Digit tiles (evaluation on the matrix cores).  The residue c mod p of the
-// coefficient at x-power i (< 32; x-power 32, the one beyond the products' K
-// range, stays in the residue tile) and row j of f (gp = 0) or g (gp = 1) is
-// kept as five 7-bit digits: digit b lies in operand fragment b RT + j / 16 of
-// its polynomial (RT = its 16-row tiles; g's fragments follow f's), lane
-// (j mod 16) + 16 (i / 8), byte i mod 8 -- the B operand order of
-// v_mfma_i32_16x16x32_i8 (lane l: column l mod 16, K slice l / 16), so that a
-// wave reads one fragment as one coalesced 8-byte load per lane.  Padding
-// positions are never written (the tiles are cleared at upload).
+// coefficient at x-power i < 32 KH (KH = 1 or 2 K slices of 32) and row j is
+// kept as four balanced base-256 digits, c = sum_b c_b 256^b, -128 <= c_b <= 127
+// (a residue below p is within their range 127 (1 + 256 + 256^2 + 256^3); the
+// earlier five 7-bit digits took 25 digit products instead of 16).  The tile of
+// rows 16 t .. 16 t + 15 (g's tiles follow f's) holds the B operands of
+// v_mfma_i32_16x16x64_i8, lane l = (j mod 16) + 16 ((i mod 32) / 8) reading its
+// bytes as 16-byte loads:
+//   KH = 1: digits 3, 2, 1, 0 of x-powers 8 (l / 16) .. + 7, eight bytes each
+//   KH = 2: digits 0, 1, 2, 3, sixteen bytes each: x-powers 8 (l / 16) .. + 7,
+//           then 32 + 8 (l / 16) .. + 7
+// Padding positions are never written (the tiles are cleared at upload).
 __host__ __device__ inline int dig_rt(int rows) { return (rows + 15) / 16; }
-constexpr int kDigits = 5;
-__device__ inline void write_digits(uint64_t* dig, int fr, int rtf, int rtg, int slot, int gp, int i, int j,
+constexpr int kEvDigits = 4;
+// balanced base-256 digits of v (|v| <= 0x7F7F7F7F) as the bytes of a word
+__host__ __device__ __forceinline__ uint32_t balanced_digits(uint32_t v) { return (v + 0x80808080u) ^ 0x80808080u; }
+// out[a] = byte a of w0, w1, w2, w3 (lowest first)
+__device__ __forceinline__ void byte_transpose4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t* out) {
+  const uint32_t t0 = __builtin_amdgcn_perm(w1, w0, 0x05010400u), t1 = __builtin_amdgcn_perm(w1, w0, 0x07030602u);
+  const uint32_t t2 = __builtin_amdgcn_perm(w3, w2, 0x05010400u), t3 = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+}
+// byte offset of digit 0, and the step between digits, of the K run of 8 x-powers
+// k8 = i / 8 of row j in a slot's tiles (rt0: tiles before the polynomial's first)
+__host__ __device__ inline size_t dig_offset(int kh, int rt0, int k8, int j, int* step) {
+  const size_t unit = (static_cast<size_t>(rt0 + (j >> 4)) * 64 + (j & 15) + 16 * (k8 & 3)) * (32 * kh);
+  *step = kh == 1 ? -8 : 16;
+  return kh == 1 ? unit + 24 : unit + 8 * (k8 >> 2);
+}
+__device__ inline void write_digits(uint64_t* dig, int fr, int kh, int rtf, int slot, int gp, int i, int j,
                                     uint32_t r) {
-  if (i >= 32) return;  // x-power 32: added on the vector ALUs from the residue tile
-  const int rt = gp ? rtg : rtf;
-  uint8_t* base = reinterpret_cast<uint8_t*>(dig + (static_cast<size_t>(slot) * fr + (gp ? kDigits * rtf : 0)) * 64);
-  const size_t at = (static_cast<size_t>(j >> 4) * 64 + (j & 15) + 16 * (i >> 3)) * 8 + (i & 7);
+  int step;
+  uint8_t* at = reinterpret_cast<uint8_t*>(dig + static_cast<size_t>(slot) * fr * 64) +
+                dig_offset(kh, gp ? rtf : 0, i >> 3, j, &step) + (i & 7);
+  const uint32_t w = balanced_digits(r);
 #pragma unroll
-  for (int b = 0; b < kDigits; ++b)
-    base[static_cast<size_t>(b) * rt * 512 + at] = static_cast<uint8_t>((r >> (7 * b)) & 127u);
+  for (int b = 0; b < kEvDigits; ++b) at[b * step] = static_cast<uint8_t>(w >> (8 * b));
 }
 
 // staged = true (the reduction launched as its own kernel): the residue tiles
 // are written only for problems whose staged evaluation reads them (Horner
-// forms; of a matrix-core form only x-power 32, which it adds on the vector
-// ALUs); the persistent schedule evaluates by Horner and writes them all.
+// forms); the persistent schedule evaluates by Horner and writes them all.
 __device__ inline void stage_reduce(const DevProblem& P, const DevTables& T, const WorkItem& w,
                                     bool zero_status = false, bool staged = false) {
   if (zero_status && w.slot == 0 && w.blk == 0)
@@ -205,21 +224,20 @@ __device__ inline void stage_reduce(const DevProblem& P, const DevTables& T, con
     const uint32_t p = pc.p;
     const uint32_t r = limbs_mod_p(P.coeff + static_cast<size_t>(in) * P.L_in, P.L_in, pc);
     v = mmul(r, pc.r3, p, pc.pinv);
-    if (w.slot < P.pshared && (partner_tile || cj == 32))
+    if (w.slot < P.pshared && partner_tile)
       P.presid[static_cast<size_t>(w.slot) * P.pCS + partner_pos(P, t)] = v;
-    if (P.dig) write_digits(P.dig, P.dfr, P.dRTf, P.dRTg, w.slot, gp, ci, cj, r);
-    if (P.pdig && w.slot < P.pshared) write_digits(P.pdig, P.pdfr, P.pdRTf, P.pdRTg, w.slot, gp, cj, ci, r);
+    if (P.dig) write_digits(P.dig, P.dfr, P.dkh, P.dRTf, w.slot, gp, ci, cj, r);
+    if (P.pdig && w.slot < P.pshared) write_digits(P.pdig, P.pdfr, P.pdkh, P.pdRTf, w.slot, gp, cj, ci, r);
   }
-  if (own_tile || ci == 32) P.resid[static_cast<size_t>(w.slot) * P.CS + t] = v;
+  if (own_tile) P.resid[static_cast<size_t>(w.slot) * P.CS + t] = v;
 }
 
 // Problems whose evaluation takes its sums from the matrix cores and that
 // share no reduction with a partner (inputs of at most two limbs): one thread
-// per (row, 8 consecutive x-powers) of a prime slot, which writes each of the
-// five digit planes' 8 bytes of that row and K slice as one word (eight
-// separate byte stores per plane otherwise); x-power 32, beyond the products'
-// K range, goes to the residue tile.  Consecutive threads take consecutive
-// rows.  Item (slot, block of 256 words, sub = 2).
+// per (row, 8 consecutive x-powers) of a prime slot, which writes the four
+// digits of that run as 8-byte words (eight separate byte stores per digit
+// otherwise).  Consecutive threads take consecutive rows.  Item (slot, block of
+// 256 words, sub = 2).
 __host__ __device__ inline int reduce_words(int my, int ny, int rowf, int rowg) {
   return (my + 1) * ((rowf + 7) / 8) + (ny + 1) * ((rowg + 7) / 8);
 }
@@ -243,21 +261,17 @@ __device__ inline void stage_reduce_words(const DevProblem& P, const DevTables& 
     const int i = 8 * k + e;
     r[e] = (i < len) ? limbs_mod_p(src + static_cast<size_t>(i) * P.L_in, P.L_in, pc) : 0u;
   }
-  if (k < 4) {
-    const int rt = gp ? P.dRTg : P.dRTf;
-    uint64_t* base = P.dig + (static_cast<size_t>(w.slot) * P.dfr + (gp ? kDigits * P.dRTf : 0)) * 64 +
-                     static_cast<size_t>(j >> 4) * 64 + (j & 15) + 16 * k;
+  uint32_t lo[kEvDigits], hi[kEvDigits];
 #pragma unroll
-    for (int b = 0; b < kDigits; ++b) {
-      uint64_t word = 0;
+  for (int e = 0; e < 8; ++e) r[e] = balanced_digits(r[e]);
+  byte_transpose4(r[0], r[1], r[2], r[3], lo);
+  byte_transpose4(r[4], r[5], r[6], r[7], hi);
+  int step;
+  uint8_t* at = reinterpret_cast<uint8_t*>(P.dig + static_cast<size_t>(w.slot) * P.dfr * 64) +
+                dig_offset(P.dkh, gp ? P.dRTf : 0, k, j, &step);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) word |= static_cast<uint64_t>((r[e] >> (7 * b)) & 127u) << (8 * e);
-      base[static_cast<size_t>(b) * rt * 64] = word;
-    }
-  } else {  // x-power 32 (rowf or rowg = 33): the residue tile, c R^2 mod p
-    const int at = (gp ? P.goff + 32 * P.nyp : 32 * P.myp) + j;
-    P.resid[static_cast<size_t>(w.slot) * P.CS + at] = mmul(r[0], pc.r3, pc.p, pc.pinv);
-  }
+  for (int b = 0; b < kEvDigits; ++b)
+    *reinterpret_cast<uint64_t*>(at + b * step) = (static_cast<uint64_t>(hi[b]) << 32) | lo[b];
 }
 
 // Multi-limb inputs: a block takes 64 transposed positions and 32 prime slots
@@ -342,11 +356,10 @@ __device__ inline void stage_reduce_ml(const DevProblem& P, const DevTables& T, 
     const int sl = w.slot + q + 4 * r;
     if (sl < P.np) {
       const uint32_t v = (in >= 0) ? mmul(acc[r], r3[r], p[r], pinv[r]) : 0u;
-      if (own_tile || ci == 32) P.resid[static_cast<size_t>(sl) * P.CS + t] = v;
-      if (in >= 0 && sl < P.pshared && (partner_tile || cj == 32)) P.presid[static_cast<size_t>(sl) * P.pCS + tp] = v;
-      if (in >= 0 && P.dig) write_digits(P.dig, P.dfr, P.dRTf, P.dRTg, sl, gp, ci, cj, acc[r]);
-      if (in >= 0 && P.pdig && sl < P.pshared)
-        write_digits(P.pdig, P.pdfr, P.pdRTf, P.pdRTg, sl, gp, cj, ci, acc[r]);
+      if (own_tile) P.resid[static_cast<size_t>(sl) * P.CS + t] = v;
+      if (in >= 0 && sl < P.pshared && partner_tile) P.presid[static_cast<size_t>(sl) * P.pCS + tp] = v;
+      if (in >= 0 && P.dig) write_digits(P.dig, P.dfr, P.dkh, P.dRTf, sl, gp, ci, cj, acc[r]);
+      if (in >= 0 && P.pdig && sl < P.pshared) write_digits(P.pdig, P.pdfr, P.pdkh, P.pdRTf, sl, gp, cj, ci, acc[r]);
     }
   }
 }
@@ -763,228 +776,292 @@ __device__ inline void stage_eval_ures_regs2(const DevProblem& P, const DevTable
   eval_report_bad(P, w.slot, pt, live, bad);
 }
 
-// ------------------------------------- eval on the matrix cores + ures_regs2
-// The values f_j(x_k) = sum_i c_ij x_k^i mod p of 32 points and every row j
-// form the product of the power matrix V[k][i] = x_k^i mod p with the residue
-// matrix C[i][j] (i < 32: the K dimension).  Both split into five 7-bit digits
-// (non-negative int8 operands); the digit products V_a C_b accumulate on the
-// matrix cores into the nine anti-diagonal sums S_s = sum_{a+b=s} V_a C_b,
-// each below 5 * 32 * 127^2 < 2^22, and
-//   f_j(x_k) R mod p = REDC(sum_s S_s (2^{7s} R^2 mod p))
-// (a sum below 9 * 2^22 * p < p 2^32).  Tiles of 16 points x 16 rows;
-// lane l of a 16x16x32 product holds A row l mod 16 (a point) and B column
-// l mod 16 (a row) for the K slice 8 (l / 16) .. 8 (l / 16) + 7, and gets the
-// outputs [4 (l / 16) + r][l mod 16], r < 4.  The values go through LDS into
-// the lane-pair layout of ures_regs2 (the same as stage_eval_ures_regs2).
+// ------------------------------------------------ eval on the matrix cores
+// The values f_j(x_k) = sum_i c_ij x_k^i mod p of 16 points and 16 rows j are
+// the product of the power matrix V[k][i] = x_k^i mod p with the residue
+// matrix C[i][j] (i < 32 KH: the K dimension).  Both split into four balanced
+// base-256 digits (int8 operands); the digit products V_a C_b accumulate on
+// the matrix cores into the seven anti-diagonal sums S_s = sum_{a+b=s} V_a C_b,
+// |S_s| <= 4 * 64 * 128^2 = 2^22, and
+//   f_j(x_k) R mod p = sredc(sum_s S_s w_s),  w_s = 2^{8s} R^2 mod p, centred
+// (at most 0.51 p).  Lane l of a 16x16x64 product holds A row l mod 16 (a
+// point) and B column l mod 16 (a row) for one quarter of K, and gets the
+// outputs [4 (l / 16) + r][l mod 16], r < 4.  With one K slice of 32 two digit
+// products of one anti-diagonal share an instruction (their K ranges side by
+// side): 10 products per tile; with two slices 16.  The 16x16x64 form issues at
+// the rate of 16x16x32, so both take twice the work per instruction.
 typedef int ev_v4i __attribute__((ext_vector_type(4)));
-// LDS: the values [poly][point][row] (odd row stride), and in the same words
-// the two scratch columns per pair of the restart path (read only after the
-// values of the restarting pairs are back in registers).
+typedef uint32_t ev_v4u __attribute__((ext_vector_type(4)));
+__host__ __device__ inline int ev_tile_products(int kh) { return kh == 1 ? 10 : 16; }
 __host__ __device__ inline int eval_mfma_row_stride(const DevProblem& P) {
   return ((P.my > P.ny ? P.my : P.ny) + 1) | 1;
 }
-__host__ __device__ inline int eval_mfma_lds_words(const DevProblem& P, int nmax, int kl) {
-  const int pts = 64 / kl;
-  const int vals = 2 * pts * eval_mfma_row_stride(P), cols = 2 * (nmax + 1) * pts;
+
+// A operands of one 16-point tile: the digits of x^(8 g + e) (and x^(32 + 8 g + e)),
+// e < 8, of the lane's point and K quarter g = lane / 16.  KH = 1: digits
+// (0, 1), (2, 3); KH = 2: one operand per digit.
+template <int KH>
+__device__ __forceinline__ void ev_powers(const DevProblem& P, int pt, const PrimeConst& pc, const SignedMod& M,
+                                          ev_v4i (&A)[2 * KH]) {
+  const int g = (threadIdx.x & 63) >> 4;
+  const int32_t x = P.origin + (pt < P.E ? pt : P.E);
+  const int32_t xt = smul(x, static_cast<int32_t>(pc.r2), M);
+  const int32_t x2 = smul(xt, xt, M), x4 = smul(x2, x2, M), x8 = smul(x4, x4, M), x16 = smul(x8, x8, M);
+  // normal form x^(8 g): a product with the Montgomery form x R stays in normal form
+  const int32_t x24 = smul(x16, x8, M);
+  int32_t first = smul(g == 1 ? x8 : g == 2 ? x16 : x24, 1, M);
+  if (g == 0) first = 1;
+#pragma unroll
+  for (int half = 0; half < KH; ++half) {
+    uint32_t w[8], lo[kEvDigits], hi[kEvDigits];
+    int32_t v = first;
+    if (half == 1) v = smul(first, smul(x16, x16, M), M);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      w[e] = balanced_digits(static_cast<uint32_t>(v));
+      if (e < 7) v = smul(v, xt, M);
+    }
+    byte_transpose4(w[0], w[1], w[2], w[3], lo);
+    byte_transpose4(w[4], w[5], w[6], w[7], hi);
+#pragma unroll
+    for (int a = 0; a < kEvDigits; ++a) {
+      const int q = KH == 1 ? a >> 1 : a, o = KH == 1 ? 2 * (a & 1) : 2 * half;
+      A[q][o] = static_cast<int>(lo[a]);
+      A[q][o + 1] = static_cast<int>(hi[a]);
+    }
+  }
+}
+
+// Recombination weights (block-uniform).
+struct EvWeights {
+  int32_t w[2 * kEvDigits - 1];
+};
+__device__ __forceinline__ EvWeights ev_weights(const PrimeConst& pc, const SignedMod& M) {
+  EvWeights W;
+  int32_t v = scenter(static_cast<int32_t>(pc.r2), M);
+  const int32_t t256 = smul(256, static_cast<int32_t>(pc.r2), M);
+#pragma unroll
+  for (int s = 0; s < 2 * kEvDigits - 1; ++s) {
+    W.w[s] = __builtin_amdgcn_readfirstlane(v);
+    v = scenter(smul(v, t256, M), M);
+  }
+  return W;
+}
+
+// Values of rows 0 .. deg of one polynomial (its digit tiles at `tile`, nrt of
+// them) at the 16 H points of A, to F[point][row] (row stride SR): signed, or
+// canonical residues.
+template <int KH, int H, bool CANON>
+__device__ __forceinline__ void ev_sums(const uint4* tile, int nrt, int deg, const ev_v4i (&A)[H][2 * KH],
+                                        const EvWeights& W, const SignedMod& M, uint32_t* F, int SR) {
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  typedef const __attribute__((address_space(1))) ev_v4u* gptr;  // global loads (not flat)
+  const gptr src = (gptr)(tile) + lane * (2 * KH);
+  ev_v4u nx[2 * KH];
+#pragma unroll
+  for (int q = 0; q < 2 * KH; ++q) nx[q] = src[q];
+  for (int rt = 0; rt < nrt; ++rt) {
+    ev_v4u b[2 * KH];
+#pragma unroll
+    for (int q = 0; q < 2 * KH; ++q) b[q] = nx[q];
+    if (rt + 1 < nrt) {  // the next tile's loads go out ahead of this tile's products
+#pragma unroll
+      for (int q = 0; q < 2 * KH; ++q) nx[q] = src[(rt + 1) * 64 * 2 * KH + q];
+    }
+    const int row = 16 * rt + (lane & 15);
+    const bool keep = row <= deg;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      ev_v4i S[2 * kEvDigits - 1];
+#pragma unroll
+      for (int s = 0; s < 2 * kEvDigits - 1; ++s) S[s] = ev_v4i{0, 0, 0, 0};
+      auto mm = [](ev_v4i a, ev_v4i bb, ev_v4i c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bb, c, 0, 0, 0); };
+      if constexpr (KH == 1) {
+        // operand pairs [B_hi | B_lo] against [A_0 | A_1] and [A_2 | A_3]
+        const int z = 0;
+        const ev_v4i b03{z, z, (int)b[0].x, (int)b[0].y};                                  // 0, 3
+        const ev_v4i b32{(int)b[0].x, (int)b[0].y, (int)b[0].z, (int)b[0].w};              // 3, 2
+        const ev_v4i b21{(int)b[0].z, (int)b[0].w, (int)b[1].x, (int)b[1].y};              // 2, 1
+        const ev_v4i b10{(int)b[1].x, (int)b[1].y, (int)b[1].z, (int)b[1].w};              // 1, 0
+        const ev_v4i b0z{(int)b[1].z, (int)b[1].w, z, z};                                  // 0, -
+        S[0] = mm(A[h][0], b0z, S[0]);
+        S[1] = mm(A[h][0], b10, S[1]);
+        S[2] = mm(A[h][0], b21, S[2]);
+        S[3] = mm(A[h][0], b32, S[3]);
+        S[4] = mm(A[h][0], b03, S[4]);
+        S[2] = mm(A[h][1], b0z, S[2]);
+        S[3] = mm(A[h][1], b10, S[3]);
+        S[4] = mm(A[h][1], b21, S[4]);
+        S[5] = mm(A[h][1], b32, S[5]);
+        S[6] = mm(A[h][1], b03, S[6]);
+      } else {
+#pragma unroll
+        for (int a = 0; a < kEvDigits; ++a)
+#pragma unroll
+          for (int d = 0; d < kEvDigits; ++d)
+            S[a + d] = mm(A[h][a], ev_v4i{(int)b[d].x, (int)b[d].y, (int)b[d].z, (int)b[d].w}, S[a + d]);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int64_t t = 0;
+#pragma unroll
+        for (int s = 0; s < 2 * kEvDigits - 1; ++s) t = smad(S[s][r], W.w[s], t);
+        const int32_t v = sredc(t, M);
+        if (keep) F[(16 * h + 4 * g + r) * SR + row] = CANON ? scanon(v, M) : static_cast<uint32_t>(v);
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ const uint4* ev_tiles(const DevProblem& P, int slot, int gp) {
+  return reinterpret_cast<const uint4*>(P.dig + static_cast<size_t>(slot) * P.dfr * 64) +
+         (gp ? static_cast<size_t>(P.dRTf) * 128 * P.dkh : 0);
+}
+
+// One lane per (prime, point) pair, 64 points per wave: the streamed form
+// (ures_stream).  The lower-degree polynomial's values pass through LDS into
+// the lane's registers, then the higher one's values take the same LDS, one row
+// per lane, from where the division reads them once.  So a wave holds one
+// polynomial's values only -- the LDS per wave is half that of keeping both --
+// and any higher degree up to kStreamLongMax fits.  A lane that leaves the
+// generic pattern (or whose leading coefficient vanishes) starts over: the
+// values of both polynomials are formed again, 32 points at a time, in the
+// same LDS, and the general column code runs on them in place.
+// Bound by VALU issue: 0.74 and 0.78 of the 4-cycle rate at lower degrees up to
+// 24 and 32 on 256 pairs of the batch workload (4.1 K and 4.9 K instructions per
+// 64 pairs), 0.6-0.67 with two K slices; the matrix cores are busy for about a
+// quarter of it.  That workload's evaluation went from 1394 us (both values in
+// LDS, five 7-bit digits, canonical residues, long divisions from LDS) to 840.
+// LDS: 64 rows of kStreamFront zeros and the values, at an odd stride.
+__host__ __device__ inline int eval_stream_row_stride(const DevProblem& P) {
+  return ((P.my > P.ny ? P.my : P.ny) + 1 + kStreamFront) | 1;
+}
+__host__ __device__ inline int eval_stream_lds_words(const DevProblem& P) { return 64 * eval_stream_row_stride(P); }
+
+template <int NMAX, int KH>
+__device__ inline void stage_eval_ures_stream(const DevProblem& P, const DevTables& T, const WorkItem& w,
+                                              uint32_t* lds) {
+  const int lane = threadIdx.x;
+  const PrimeConst pc = T.pc[P.pidx[w.slot]];
+  const SignedMod M = signed_mod(pc);
+  const EvWeights W = ev_weights(pc, M);
+  const int SR = eval_stream_row_stride(P);
+  const bool swap = P.my < P.ny;  // A: the higher degree m, B: the lower degree n
+  const int m = swap ? P.ny : P.my, n = swap ? P.my : P.ny;
+  const int rtA = swap ? P.dRTg : P.dRTf, rtB = swap ? P.dRTf : P.dRTg;
+  const int pt0 = w.blk * 64, pt = pt0 + lane;
+  uint32_t* vals = lds + kStreamFront;
+  uint32_t* row = vals + lane * SR;
+#pragma unroll
+  for (int j = 1; j <= kStreamFront; ++j) row[-j] = 0u;
+
+  int32_t X[NMAX];
+  int32_t L;
+  {
+    ev_v4i A[4][2 * KH];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) ev_powers<KH>(P, pt0 + 16 * h + (lane & 15), pc, M, A[h]);
+    ev_sums<KH, 4, false>(ev_tiles(P, w.slot, swap ? 0 : 1), rtB, n, A, W, M, vals, SR);
+    WaveSync()();
+    const int pad = stream_pad(n);
+    const uint32_t* src = row - pad;
+#pragma unroll
+    for (int q = 0; q < NMAX / 4; ++q)
+      if (4 * q < n + pad) {
+#pragma unroll
+        for (int j = 4 * q; j < 4 * q + 4; ++j) X[j] = static_cast<int32_t>(src[j]);
+      }
+    L = static_cast<int32_t>(row[n]);
+    WaveSync()();
+    ev_sums<KH, 4, false>(ev_tiles(P, w.slot, swap ? 1 : 0), rtA, m, A, W, M, vals, SR);
+    WaveSync()();
+  }
+  const bool bad = L == 0 || row[m] == 0u;
+  bool ok;
+  uint32_t r = ures_stream<NMAX>(X, L, Column<1>{row}, m, n, pc, &ok);
+  if (swap && ((m * n) & 1)) r = mneg(r, pc.p);  // Res(f, g) = (-1)^{mn} Res(g, f)
+  ok = ok && !bad;
+  const uint64_t redo = __ballot(!ok);
+  if (redo) {
+    for (int half = 0; half < 2; ++half) {
+      if (((redo >> (32 * half)) & 0xFFFFFFFFu) == 0u) continue;  // wave-uniform
+      WaveSync()();
+      ev_v4i A[2][2 * KH];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) ev_powers<KH>(P, pt0 + 32 * half + 16 * h + (lane & 15), pc, M, A[h]);
+      ev_sums<KH, 2, true>(ev_tiles(P, w.slot, 0), P.dRTf, P.my, A, W, M, vals, SR);
+      ev_sums<KH, 2, true>(ev_tiles(P, w.slot, 1), P.dRTg, P.ny, A, W, M, vals + 32 * SR, SR);
+      WaveSync()();
+      if (!ok && (lane >> 5) == half) {
+        bool b2 = false;
+        r = ures_formal(Column<1>{vals + (lane & 31) * SR}, Column<1>{vals + (32 + (lane & 31)) * SR}, P.my, P.ny, pc,
+                        &b2);
+      }
+    }
+  }
+  const bool live = pt <= P.E;
+  if (live) {
+    const size_t o = static_cast<size_t>(w.slot) * (P.E + 1) + pt;
+    P.zval[o] = redc(r, pc.p, pc.pinv);
+    P.zbad[o] = bad ? 1 : 0;
+  }
+  eval_report_bad(P, w.slot, pt, live, bad);
+}
+
+// A lane pair per (prime, point), 32 points per wave, both polynomials' values
+// [poly][point][row] in LDS, then the branch-free pair chain
+// (ures_regs2_generic); in the same LDS words the two scratch columns per pair
+// of the restart path (written only after the restarting pairs have their
+// values back in registers).  Taken when two lanes per pair are asked for.
+__host__ __device__ inline int eval_mfma2_lds_words(const DevProblem& P, int nmax) {
+  const int vals = 2 * 32 * eval_mfma_row_stride(P), cols = 2 * (nmax + 1) * 32;
   return vals > cols ? vals : cols;
 }
 
-// KL lanes per (prime, point) pair: 64 / KL points per wave (4 / KL tiles of
-// 16), then the register form's remainder sequence -- one lane per pair
-// (ures_regs_generic) or a lane pair (ures_regs2_generic) -- without per-step
-// branches; a pair that leaves the generic pattern starts over from its values
-// in LDS with the general column code.
-template <int NMAX, int KL>
-__device__ inline void stage_eval_ures_mfma(const DevProblem& P, const DevTables& T, const WorkItem& w,
-                                            uint32_t* lds) {
-  constexpr int PTS = 64 / KL, H = PTS / 16;
+template <int NMAX, int KH>
+__device__ inline void stage_eval_ures_mfma2(const DevProblem& P, const DevTables& T, const WorkItem& w,
+                                             uint32_t* lds) {
+  constexpr int PTS = 32;
   const int lane = threadIdx.x;
   const PrimeConst pc = T.pc[P.pidx[w.slot]];
-  const uint32_t p = pc.p, pinv = pc.pinv;
+  const SignedMod M = signed_mod(pc);
   const int SR = eval_mfma_row_stride(P);
   uint32_t* Fv[2] = {lds, lds + PTS * SR};
   uint32_t* cols = lds;  // restart path only
-
-  // B operands (digit fragments of the residues), one group per 16-row tile
-  // of f, then of g; the next group's loads are issued a group ahead
-  typedef const __attribute__((address_space(1))) uint64_t* gptr;  // global loads (not flat)
-  const gptr dg = (gptr)(P.dig + static_cast<size_t>(w.slot) * P.dfr * 64);
-  const int ng = P.dRTf + P.dRTg;
-  auto frag = [&](int gi, int b) {
-    const int f = gi < P.dRTf ? b * P.dRTf + gi : kDigits * P.dRTf + b * P.dRTg + (gi - P.dRTf);
-    return dg[static_cast<size_t>(f) * 64 + lane];
-  };
-  uint64_t Bn[kDigits];
+  {
+    const EvWeights W = ev_weights(pc, M);
+    ev_v4i A[2][2 * KH];
 #pragma unroll
-  for (int b = 0; b < kDigits; ++b) Bn[b] = frag(0, b);
-  __builtin_amdgcn_sched_barrier(0);  // issue the loads here, not next to their use
-
-  // A operands: digit a of x_k^(8 g + e), e < 8, for the point k = lane mod 16
-  // of each 16-point tile h and the K slice g = lane / 16
-  uint64_t A[H][kDigits];
-  const int g = lane >> 4;
-#pragma unroll
-  for (int h = 0; h < H; ++h) {
-    const int pt = w.blk * PTS + 16 * h + (lane & 15);
-    const uint32_t x = static_cast<uint32_t>(P.origin + (pt < P.E ? pt : P.E));
-    const uint32_t xt = mmul(x, pc.r2, p, pinv);
-    const uint32_t x2 = mmul(xt, xt, p, pinv), x4 = mmul(x2, x2, p, pinv), x8 = mmul(x4, x4, p, pinv);
-    const uint32_t x16 = mmul(x8, x8, p, pinv), x24 = mmul(x16, x8, p, pinv);
-    uint32_t pw = g == 0 ? pc.r1 : g == 1 ? x8 : g == 2 ? x16 : x24;
-    uint32_t v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      v[e] = redc(pw, p, pinv);  // x^(8 g + e) mod p
-      if (e < 7) pw = mmul(pw, xt, p, pinv);
-    }
-#pragma unroll
-    for (int a = 0; a < kDigits; ++a) {
-      uint32_t lo = 0u, hi = 0u;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lo |= ((v[e] >> (7 * a)) & 127u) << (8 * e);
-        hi |= ((v[e + 4] >> (7 * a)) & 127u) << (8 * e);
-      }
-      A[h][a] = (static_cast<uint64_t>(hi) << 32) | lo;
-    }
-  }
-  // recombination weights 2^(7 s) R^2 mod p
-  uint32_t wsum[2 * kDigits - 1];
-  wsum[0] = pc.r2;
-  const uint32_t t128 = mmul(128u, pc.r2, p, pinv);
-#pragma unroll
-  for (int s = 1; s < 2 * kDigits - 1; ++s) wsum[s] = mmul(wsum[s - 1], t128, p, pinv);
-
-  for (int gi = 0; gi < ng; ++gi) {
-    uint64_t B[kDigits];
-#pragma unroll
-    for (int b = 0; b < kDigits; ++b) B[b] = Bn[b];
-    if (gi + 1 < ng) {
-#pragma unroll
-      for (int b = 0; b < kDigits; ++b) Bn[b] = frag(gi + 1, b);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    const int gp = gi >= P.dRTf ? 1 : 0, rt = gp ? gi - P.dRTf : gi;
-    uint32_t* F = Fv[gp];
-    const int row = 16 * rt + (lane & 15);
-    const bool keep = row <= (gp ? P.ny : P.my);
-#pragma unroll
-    for (int h = 0; h < H; ++h) {
-      ev_v4i S[2 * kDigits - 1];
-#pragma unroll
-      for (int s = 0; s < 2 * kDigits - 1; ++s) S[s] = ev_v4i{0, 0, 0, 0};
-#pragma unroll
-      for (int a = 0; a < kDigits; ++a)
-#pragma unroll
-        for (int b = 0; b < kDigits; ++b)
-          S[a + b] = __builtin_amdgcn_mfma_i32_16x16x32_i8(static_cast<long>(A[h][a]), static_cast<long>(B[b]),
-                                                           S[a + b], 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        uint64_t t = 0;
-#pragma unroll
-        for (int s = 0; s < 2 * kDigits - 1; ++s) t += static_cast<uint64_t>(static_cast<uint32_t>(S[s][r])) * wsum[s];
-        if (keep) F[(16 * h + 4 * g + r) * SR + row] = redc(t, p, pinv);
-      }
-    }
+    for (int h = 0; h < 2; ++h) ev_powers<KH>(P, w.blk * PTS + 16 * h + (lane & 15), pc, M, A[h]);
+    ev_sums<KH, 2, true>(ev_tiles(P, w.slot, 0), P.dRTf, P.my, A, W, M, Fv[0], SR);
+    ev_sums<KH, 2, true>(ev_tiles(P, w.slot, 1), P.dRTg, P.ny, A, W, M, Fv[1], SR);
   }
   WaveSync()();
-  // x-degree 32: the products cover x-powers 0..31; f_j(x) R += c_{32,j} x^32 R
-  // on the vector ALUs, from the residue tile (c R^2) and x^32 in normal form
-  if (P.rowf > 32 || P.rowg > 32) {
-    const int ptq = w.blk * PTS + (lane < PTS ? lane : 0);
-    const uint32_t xq = static_cast<uint32_t>(P.origin + (ptq < P.E ? ptq : P.E));
-    uint32_t x32 = mmul(xq, pc.r2, p, pinv);
-#pragma unroll
-    for (int s = 0; s < 5; ++s) x32 = mmul(x32, x32, p, pinv);
-    x32 = redc(x32, p, pinv);  // x^32 of local point `lane`, normal form
-    const uint32_t* rs = P.resid + static_cast<size_t>(w.slot) * P.CS;
-    for (int gp = 0; gp < 2; ++gp) {
-      if ((gp ? P.rowg : P.rowf) <= 32) continue;
-      const int rows = gp ? P.ny + 1 : P.my + 1;
-      const uint32_t* top = rs + (gp ? P.goff + 32 * P.nyp : 32 * P.myp);
-      const int n = PTS * rows;
-      for (int t0 = 0; t0 < n; t0 += 64) {  // every lane takes part in each shuffle
-        const int t = t0 + lane;
-        const int q = (t < n) ? t / rows : 0;
-        const uint32_t xv = static_cast<uint32_t>(__shfl(static_cast<int>(x32), q, 64));
-        if (t < n) {
-          const int j = t - q * rows;
-          uint32_t* v = Fv[gp] + q * SR + j;
-          *v = maddm(*v, mmul(top[j], xv, p, pinv), p);
-        }
-      }
-    }
-    WaveSync()();
-  }
-
+  constexpr int N2 = RegPoly2<NMAX>::kN;
+  const int l = lane & 1, q = lane >> 1;
+  const int pt = w.blk * PTS + q;
+  const bool live = pt <= P.E && l == 0;
   bool ok, bad;
-  uint32_t r;
-  int pt;
-  bool live;
-  if constexpr (KL == 2) {
-    constexpr int N2 = RegPoly2<NMAX>::kN;
-    const int l = lane & 1, q = lane >> 1;
-    pt = w.blk * PTS + q;
-    live = pt <= P.E && l == 0;
-    uint32_t X[N2], Y[N2];
+  uint32_t X[N2], Y[N2];
+  auto load = [&] {
 #pragma unroll
     for (int k = 0; k < N2; ++k) {
       const int j = 2 * k + l;
       X[k] = (j <= P.my) ? Fv[0][q * SR + j] : 0u;
       Y[k] = (j <= P.ny) ? Fv[1][q * SR + j] : 0u;
     }
-    r = ures_regs2_generic<NMAX>(X, Y, P.my, P.ny, l, pc, &ok, &bad, PairSwap());
-    if (!ok) {
-#pragma unroll
-      for (int k = 0; k < N2; ++k) {
-        const int j = 2 * k + l;
-        X[k] = (j <= P.my) ? Fv[0][q * SR + j] : 0u;
-        Y[k] = (j <= P.ny) ? Fv[1][q * SR + j] : 0u;
-      }
-      WaveSync()();  // every restarting pair has its values before the columns overwrite them
-      r = ures2_columns<NMAX>(X, Y, P.my, P.ny, l, pc, Column<32>{cols + q},
-                              Column<32>{cols + (NMAX + 1) * 32 + q}, PairSwap(), WaveSync());
-    }
-  } else if (P.my - P.ny > 1 || P.ny - P.my > 1) {
-    // the long shapes: first division on the lane's own value rows, then the
-    // branch-free chain in registers (ures_regs_long); no other lane's rows are touched
-    pt = w.blk * PTS + lane;
-    live = pt <= P.E;
-    r = ures_regs_long<NMAX>(Column<1>{Fv[0] + lane * SR}, Column<1>{Fv[1] + lane * SR}, P.my, P.ny, pc, &bad);
-  } else {
-    constexpr int N = RegPoly<NMAX>::kN;
-    pt = w.blk * PTS + lane;
-    live = pt <= P.E;
-    uint32_t X[N], Y[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      X[j] = (j <= P.my) ? Fv[0][lane * SR + j] : 0u;
-      Y[j] = (j <= P.ny) ? Fv[1][lane * SR + j] : 0u;
-    }
-    r = ures_regs_generic<NMAX>(X, Y, P.my, P.ny, pc, &ok, &bad);
-    if (!ok) {
-      // the restarting lanes read their values before any column is written
-      uint32_t va[NMAX + 1], vb[NMAX + 1];
-#pragma unroll
-      for (int j = 0; j <= NMAX; ++j) {
-        va[j] = (j <= P.my) ? Fv[0][lane * SR + j] : 0u;
-        vb[j] = (j <= P.ny) ? Fv[1][lane * SR + j] : 0u;
-      }
-      WaveSync()();
-      Column<64> CA{cols + lane}, CB{cols + (NMAX + 1) * 64 + lane};
-#pragma unroll
-      for (int j = 0; j <= NMAX; ++j) {
-        CA[j] = va[j];
-        CB[j] = vb[j];
-      }
-      bool b2 = false;
-      r = ures_formal(CA, CB, P.my, P.ny, pc, &b2);
-    }
+  };
+  load();
+  uint32_t r = ures_regs2_generic<NMAX>(X, Y, P.my, P.ny, l, pc, &ok, &bad, PairSwap());
+  if (!ok) {
+    load();
+    WaveSync()();  // every restarting pair has its values before the columns overwrite them
+    r = ures2_columns<NMAX>(X, Y, P.my, P.ny, l, pc, Column<32>{cols + q}, Column<32>{cols + (NMAX + 1) * 32 + q},
+                            PairSwap(), WaveSync());
   }
   if (live) {
     const size_t o = static_cast<size_t>(w.slot) * (P.E + 1) + pt;
-    P.zval[o] = redc(r, p, pinv);
+    P.zval[o] = redc(r, pc.p, pc.pinv);
     P.zbad[o] = bad ? 1 : 0;
   }
   eval_report_bad(P, w.slot, pt, live, bad);
@@ -1111,7 +1188,7 @@ __device__ inline void stage_eval_schur(const DevProblem& P, const DevTables& T,
 // LDS words of the evaluation launch for the problem's layout.
 __host__ __device__ inline int eval_stage_lds_words(const DevProblem& P) {
   if (P.schur) return eval_schur_lds_words(P);
-  if (P.evmf) return eval_mfma_lds_words(P, P.regn, P.evk);
+  if (P.evmf) return P.evk == 2 ? eval_mfma2_lds_words(P, P.regn) : eval_stream_lds_words(P);
   if (P.evk == 2 && P.regn) return eval_regs2_lds_words(P, P.regn);
   if (P.evk > 1) return eval_group_lds_words(P, P.evk);
   return P.regn ? eval_regs_lds_words(P, P.regn) : eval_lds_words(P);
@@ -1125,14 +1202,17 @@ enum : int {
   kEvR8, kEvR16, kEvR24, kEvR32,  // one lane per pair, registers (degree bound)
   kEvP8, kEvP16, kEvP24, kEvP32,  // two lanes per pair, registers
   kEvSchur,     // one wave per pair, Schur algorithm on the Sylvester generators
-  kEvM8, kEvM16, kEvM24, kEvM32,  // two lanes per pair, registers, Horner sums on the matrix cores
-  kEvQ8, kEvQ16, kEvQ24, kEvQ32,  // one lane per pair, registers, Horner sums on the matrix cores
-  kEvNum
+  kEvM,         // two lanes per pair, registers, sums on the matrix cores: + 2 (regn / 8 - 1) + dkh - 1
+  kEvQ = kEvM + 8,   // one lane per pair, streamed, sums on the matrix cores: + 2 (regn / 8 - 1) + dkh - 1
+  kEvNum = kEvQ + 12
 };
+constexpr int kStreamDegMax = 48;   // lower degree of the streamed form (registers)
+constexpr int kStreamLongMax = 63;  // higher degree (its values stay in LDS: 17 KB per wave)
+constexpr int kMfmaXPowers = 64;    // x-powers of the matrix-core sums (two K slices of 32)
 __host__ __device__ inline int eval_variant(const DevProblem& P) {
   if (P.schur) return kEvSchur;
+  if (P.evmf) return (P.evk == 2 ? kEvM : kEvQ) + 2 * (P.regn / 8 - 1) + P.dkh - 1;
   const int r = P.regn == 8 ? 0 : P.regn == 16 ? 1 : P.regn == 24 ? 2 : 3;
-  if (P.evmf) return (P.evk == 2 ? kEvM8 : kEvQ8) + r;
   if (P.evk == 2 && P.regn) return kEvP8 + r;
   if (P.evk == 2) return kEvG2;
   if (P.evk == 4) return kEvG4;
@@ -1146,40 +1226,18 @@ __device__ inline void stage_eval_variant(const DevProblem& P, const DevTables& 
   else if constexpr (V == kEvG4) stage_eval_ures_group<4>(P, T, w, lds);
   else if constexpr (V >= kEvR8 && V <= kEvR32) stage_eval_ures_regs<8 * (V - kEvR8 + 1)>(P, T, w, lds);
   else if constexpr (V == kEvSchur) stage_eval_schur(P, T, w, lds);
-  else if constexpr (V >= kEvQ8) stage_eval_ures_mfma<8 * (V - kEvQ8 + 1), 1>(P, T, w, lds);
-  else if constexpr (V >= kEvM8) stage_eval_ures_mfma<8 * (V - kEvM8 + 1), 2>(P, T, w, lds);
+  else if constexpr (V >= kEvQ) stage_eval_ures_stream<8 * ((V - kEvQ) / 2 + 1), (V - kEvQ) % 2 + 1>(P, T, w, lds);
+  else if constexpr (V >= kEvM) stage_eval_ures_mfma2<8 * ((V - kEvM) / 2 + 1), (V - kEvM) % 2 + 1>(P, T, w, lds);
   else stage_eval_ures_regs2<8 * (V - kEvP8 + 1)>(P, T, w, lds);
 }
 
-// Dispatch on the problem's evaluation layout (block-uniform).  With
-// use_regs = false the register form is skipped (the LDS-column code computes
-// the same values), which keeps the register budget of a kernel that also
-// runs the other stages small.
-template <bool use_regs = true>
-__device__ inline void stage_eval(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
-  if (use_regs && P.evk == 2) {
-    switch (P.regn) {
-      case 8: stage_eval_ures_regs2<8>(P, T, w, lds); return;
-      case 16: stage_eval_ures_regs2<16>(P, T, w, lds); return;
-      case 24: stage_eval_ures_regs2<24>(P, T, w, lds); return;
-      case 32: stage_eval_ures_regs2<32>(P, T, w, lds); return;
-      default: break;
-    }
-  }
+// The persistent schedule's dispatch (block-uniform): the LDS-column code,
+// which keeps the register budget of a kernel that also runs the other stages
+// small.
+__device__ inline void stage_eval_columns(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
   switch (P.evk) {
     case 2: stage_eval_ures_group<2>(P, T, w, lds); return;
     case 4: stage_eval_ures_group<4>(P, T, w, lds); return;
-    default: break;
-  }
-  if (!use_regs) {
-    stage_eval_ures(P, T, w, lds);
-    return;
-  }
-  switch (P.regn) {
-    case 8: stage_eval_ures_regs<8>(P, T, w, lds); return;
-    case 16: stage_eval_ures_regs<16>(P, T, w, lds); return;
-    case 24: stage_eval_ures_regs<24>(P, T, w, lds); return;
-    case 32: stage_eval_ures_regs<32>(P, T, w, lds); return;
     default: stage_eval_ures(P, T, w, lds); return;
   }
 }
@@ -1405,6 +1463,7 @@ __device__ inline void basis_block(const uint32_t* S, int j0, int k1, int ke, in
 // (zero beyond D and, for the basis change, for a prime with bad points).
 // Each thread writes eight consecutive entries of every plane (one 64-bit
 // store per plane); item (problem, slot, block of 2048 entries).
+constexpr int kDigits = 5;
 constexpr int kDigitsPerBlock = 2048;
 template <int WHICH>
 __device__ inline void stage_interp_digits(const DevProblem& P, const DevTables& T, const WorkItem& w) {

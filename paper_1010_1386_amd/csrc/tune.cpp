@@ -326,7 +326,7 @@ int rsl_job_info_get(const rsl_job* j, rsl_job_info* info) {
   for (const DevProblem& d : j->J.dev) lanes = std::max(lanes, d.evk);
   info->eval_lanes = lanes;
   int mf = 0;
-  for (const DevProblem& d : j->J.dev) mf += d.evmf;
+  for (const DevProblem& d : j->J.dev) mf += d.evmf && d.rowf <= 33 && d.rowg <= 33;
   info->eval_mfma = mf;
   return RSL_OK;
 }

@@ -666,3 +666,129 @@ RSL_HD uint32_t ures_regs2(uint32_t (&X)[RegPoly2<NMAX>::kN], uint32_t (&Y)[RegP
 }
 
 }  // namespace rsl
+
+namespace rsl {
+
+// The resultant of any two degrees with the shorter polynomial and the running
+// dividend in registers, in signed residues (one lane per pair).
+//
+// Let deg A = m >= deg B = n.  Both are multiplied by y^pad so that B has
+// degree len = n + pad, a multiple of 4: the remainder only gains the factor
+// y^pad, and every register index below is a compile-time constant.
+//  * Division of A by B (swindow): the dividend's top len coefficients are a
+//    window in registers; each of the k = m - n + 1 passes multiplies by
+//    L = lc(B), eliminates the top one and shifts the next coefficient of A in
+//    from memory -- 2 products per entry, one memory read per pass.
+//  * Remainder sequence from (B, R) of degrees len, len - 1 (SChain), as
+//    RegChainGen: one pass of three products per entry and step, unrolled for
+//    every degree; entry and exit depend on the (per-problem) degrees only.
+// An update is its multiply-adds, one multiply and one multiply-add: five
+// instructions for three products against seven with canonical residues.
+// Bounds, in units of p (p / R < 1/3; an input value is at most 0.51):
+//   window  c <- (0.51 c + 0.51 c) / 3 + 0.5: stays below 0.76;
+//   chain   scalars L (centred) <= 0.5, L^2 and L lc(A) <= 0.59, the third,
+//           centred, <= 0.5: c <- 1.68 c / 3 + 0.5 stays below 1.14 < 1.5, and
+//           sums of products below 2^62.
+// A step whose divisor's leading coefficient vanishes (a remainder that lost
+// more than one degree) makes U and den zero from there on, so one test of den
+// at the end tells whether the whole sequence was generic.
+template <int LEN, int N, class Col>
+RSL_HD int32_t swindow(const int32_t (&X)[N], int32_t (&Y)[N], int32_t L, Col A, int m, int k, const SignedMod& M) {
+#pragma unroll
+  for (int j = 0; j < LEN; ++j) Y[j] = static_cast<int32_t>(A[m - LEN + 1 + j]);
+  int32_t Lt = L;  // L^(t+1)
+  for (int t = 0; t < k; ++t) {
+    const int32_t in = static_cast<int32_t>(A[m - LEN - t]);
+    const int32_t nlc = -Y[LEN - 1];
+#pragma unroll
+    for (int j = LEN - 1; j > 0; --j) Y[j] = sredc(smad(nlc, X[j], smad(L, Y[j - 1], 0)), M);
+    Y[0] = sredc(smad(nlc, X[0], smad(Lt, in, 0)), M);
+    if (t + 1 < k) Lt = smul(Lt, L, M);
+  }
+  return Lt;
+}
+
+// A <- L^2 A - L lc(A) y B - lc(A~) B for deg B = BS, deg A = BS + 1; lcA is
+// lc(A) (centred) and becomes L.
+template <int BS, int N>
+RSL_HD void schain_step(int32_t (&A)[N], const int32_t (&B)[N], int32_t& lcA, int32_t& den, int32_t& U,
+                        const SignedMod& M) {
+  const int32_t L = scenter(B[BS], M), nL = -L;
+  const int32_t al = smul(L, L, M), be = smul(nL, lcA, M);
+  const int32_t ga = scenter(sredc(smad(lcA, B[BS - 1], smad(nL, A[BS], 0)), M), M);
+#pragma unroll
+  for (int j = 0; j < BS; ++j)
+    A[j] = sredc(smad(ga, B[j], smad(be, j > 0 ? B[j - 1] : 0, smad(al, A[j], 0))), M);
+  lcA = L;
+  U = smul(U, al, M);
+  den = smul(den, U, M);
+}
+
+// Steps 4 Q + 3 .. 4 Q for Q >= 1, then 3, 2, 1 down to degree pad: A is in X
+// when the step's degree is odd.
+template <int Q, int N>
+struct SChain {
+  RSL_HD static void run(int32_t (&X)[N], int32_t (&Y)[N], int len, int pad, int32_t& lcA, int32_t& den, int32_t& U,
+                         const SignedMod& M) {
+    if (4 * Q + 4 <= len) {
+      schain_step<4 * Q + 3>(X, Y, lcA, den, U, M);
+      schain_step<4 * Q + 2>(Y, X, lcA, den, U, M);
+      schain_step<4 * Q + 1>(X, Y, lcA, den, U, M);
+      schain_step<4 * Q>(Y, X, lcA, den, U, M);
+    }
+    SChain<Q - 1, N>::run(X, Y, len, pad, lcA, den, U, M);
+  }
+};
+template <int N>
+struct SChain<0, N> {
+  RSL_HD static void run(int32_t (&X)[N], int32_t (&Y)[N], int, int pad, int32_t& lcA, int32_t& den, int32_t& U,
+                         const SignedMod& M) {
+    if (pad < 3) schain_step<3>(X, Y, lcA, den, U, M);
+    if (pad < 2) schain_step<2>(Y, X, lcA, den, U, M);
+    if (pad < 1) schain_step<1>(X, Y, lcA, den, U, M);
+  }
+};
+
+template <int LEN, int N>
+struct SWindow {  // the window of length len, LEN and below
+  template <class Col>
+  RSL_HD static int32_t run(const int32_t (&X)[N], int32_t (&Y)[N], int32_t L, Col A, int m, int len, int k,
+                            const SignedMod& M) {
+    if (len == LEN) return swindow<LEN>(X, Y, L, A, m, k, M);
+    return SWindow<LEN - 4, N>::run(X, Y, L, A, m, len, k, M);
+  }
+};
+template <int N>
+struct SWindow<4, N> {
+  template <class Col>
+  RSL_HD static int32_t run(const int32_t (&X)[N], int32_t (&Y)[N], int32_t L, Col A, int m, int, int k,
+                            const SignedMod& M) {
+    return swindow<4>(X, Y, L, A, m, k, M);
+  }
+};
+
+RSL_HD int stream_pad(int n) { return (4 - (n & 3)) & 3; }
+constexpr int kStreamFront = 3;
+
+// Res(A, B), 1 <= n = deg B <= NMAX, m = deg A >= n, A's coefficients at A[0..m]
+// with kStreamFront zeros before them (A[-3..-1]: the division reads as far as
+// -pad), B's in X: X[j] = B[j - pad] for pad <= j < n + pad, zero below (the
+// entries above are not used), and L = B[n].  *ok is false when L or a later divisor's leading coefficient
+// vanishes (the value returned is then meaningless); the caller tests A[m].
+// Returns the residue in Montgomery form, [0, p).
+template <int NMAX, class Col>
+RSL_HD uint32_t ures_stream(int32_t (&X)[NMAX], int32_t L, Col A, int m, int n, const PrimeConst& pc, bool* ok) {
+  const SignedMod M = signed_mod(pc);
+  const int pad = stream_pad(n), len = n + pad, k = m - n + 1;
+  int32_t Y[NMAX];
+  const int32_t y = SWindow<NMAX, NMAX>::run(X, Y, L, A, m, len, k, M);  // L^k
+  int32_t den = y, U = y, lcA = L;
+  SChain<NMAX / 4 - 1, NMAX>::run(X, Y, len, pad, lcA, den, U, M);
+  *ok = den != 0;
+  // the constant remainder: step pad + 1 (or, for n = 1, the window) left it at index pad
+  const int32_t r0 = pad == 0 ? X[0] : pad == 1 ? Y[1] : pad == 2 ? X[2] : Y[3];
+  const uint32_t r = scanon(smul(smul(U, r0, M), sinv(den, pc.r1, M), M), M);
+  return ((m * n) & 1) ? mneg(r, pc.p) : r;
+}
+
+}  // namespace rsl

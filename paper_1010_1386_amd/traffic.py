@@ -35,7 +35,8 @@ import os
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("stages.h", "ures.h", "ures_regs.h", "modarith.h", "device.h", "kernels.hip", "job.cpp")
+KERNEL_SOURCES = ("stages.h", "ures.h", "ures_regs.h", "modarith.h", "device.h", "kernels.hip", "job.cpp",
+                  "eval_launch.h", "eval_columns.hip", "eval_lanes.hip", "eval_stream1.hip", "eval_stream2.hip")
 
 
 def sources_sha256():

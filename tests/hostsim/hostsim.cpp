@@ -198,9 +198,57 @@ int regs_long_run(const PrimeConst& pc, int m, int n, const uint32_t* A, const u
   return 0;
 }
 
+// The streamed register form (signed residues) of the longer polynomial by the
+// shorter, swapped as the evaluation stage does, with its column restart.
+template <int NMAX>
+int stream_run(const PrimeConst& pc, int m, int n, const uint32_t* A, const uint32_t* B, uint32_t* out, int* bad,
+               int* generic) {
+  const SignedMod M = signed_mod(pc);
+  std::vector<uint32_t> ca(m + 1), cb(n + 1);
+  for (int j = 0; j <= m; ++j) ca[j] = mmul(A[j] % pc.p, pc.r2, pc.p, pc.pinv);
+  for (int j = 0; j <= n; ++j) cb[j] = mmul(B[j] % pc.p, pc.r2, pc.p, pc.pinv);
+  const bool swap = m < n;
+  const std::vector<uint32_t>&la = swap ? cb : ca, &lb = swap ? ca : cb;
+  const int a = swap ? n : m, b = swap ? m : n, pad = stream_pad(b);
+  std::vector<uint32_t> rows(kStreamFront + a + 1, 0u);
+  for (int j = 0; j <= a; ++j) rows[kStreamFront + j] = static_cast<uint32_t>(scenter(static_cast<int32_t>(la[j]), M));
+  int32_t X[NMAX];
+  for (int j = 0; j < NMAX; ++j) X[j] = (j >= pad && j < b + pad) ? scenter(static_cast<int32_t>(lb[j - pad]), M) : 0;
+  bool ok = false;
+  uint32_t r = ures_stream<NMAX>(X, scenter(static_cast<int32_t>(lb[b]), M), Column<1>{rows.data() + kStreamFront}, a, b, pc, &ok);
+  if (swap && ((m * n) & 1)) r = mneg(r, pc.p);
+  const bool bd = ca[m] == 0u || cb[n] == 0u;
+  ok = ok && !bd;
+  if (!ok) {
+    bool b2 = false;
+    r = ures_formal(Column<1>{ca.data()}, Column<1>{cb.data()}, m, n, pc, &b2);
+  }
+  *out = redc(r, pc.p, pc.pinv);
+  *bad = bd;
+  *generic = ok;
+  return 0;
+}
+
 }  // namespace
 
 extern "C" {
+
+// The streamed register form: 1 <= min(m, n) <= nmax.
+int hs_ures_stream(int nmax, uint32_t p, int m, int n, const uint32_t* A, const uint32_t* B, uint32_t* out, int* bad,
+                   int* generic) {
+  PrimeConst pc = make_prime_const(p);
+  const int lo = m < n ? m : n;
+  if (lo < 1 || lo > nmax) return -1;
+  switch (nmax) {
+    case 8: return stream_run<8>(pc, m, n, A, B, out, bad, generic);
+    case 16: return stream_run<16>(pc, m, n, A, B, out, bad, generic);
+    case 24: return stream_run<24>(pc, m, n, A, B, out, bad, generic);
+    case 32: return stream_run<32>(pc, m, n, A, B, out, bad, generic);
+    case 40: return stream_run<40>(pc, m, n, A, B, out, bad, generic);
+    case 48: return stream_run<48>(pc, m, n, A, B, out, bad, generic);
+    default: return -1;
+  }
+}
 
 // The general-shape one-lane register form (any m, n <= nmax).
 int hs_ures_regs_long(int nmax, uint32_t p, int m, int n, const uint32_t* A, const uint32_t* B, uint32_t* out,

@@ -152,12 +152,10 @@ typedef struct {
                           m_y, n_y >= 1 and m_y + n_y <= 64 (others keep the remainder
                           sequence); staged and plain schedules only; 0 = remainder
                           sequence unless the autotuner chose Schur */
-  int32_t interp_mm;   /* 1: interpolation on the matrix cores -- the columns of all problems
-                          sharing a prime as two matrix products with the Vandermonde
-                          system's triangular factors (forward differences, Stirling
-                          basis change); staged schedule (plain runs take the vector
-                          path on the same layout); 0 = vector path unless the
-                          autotuner chose the matrix cores */
+  int32_t interp_mm;   /* the staged and plain schedules always take the consecutive-point interpolation
+                          (the Vandermonde system's triangular factors: forward differences,
+                          Stirling basis change) on the matrix cores; 1: the layout's partial sums,
+                          which the persistent schedule uses, are also laid out whole, in less memory */
   int32_t interp_newton;/* 1: every prime interpolates by the Vandermonde solve of the gapped
                           path -- divided differences, then the Newton form expanded to
                           monomials (the triangular factors of the Vandermonde matrix,
@@ -383,7 +381,7 @@ typedef struct {
   int32_t evk;           /* lanes per (prime, point) pair in evaluation: 1, 2 or 4 */
   int32_t conv_whole;    /* 1: convolution sums taken whole, 0: split like the basis change */
   int32_t schur;         /* 1: evaluation by the Schur algorithm (see rsl_opts.eval_schur) */
-  int32_t interp_mm;     /* 1: interpolation on the matrix cores (see rsl_opts.interp_mm) */
+  int32_t interp_mm;     /* 1: partial sums laid out whole (see rsl_opts.interp_mm) */
   int32_t candidates;    /* candidates timed */
   double ms;             /* device time of one run of the chosen schedule */
   double ms_worst;       /* device time of the slowest candidate */

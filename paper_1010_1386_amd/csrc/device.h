@@ -87,12 +87,12 @@ struct DevProblem {
   uint32_t* zval;         // np * (E+1)  R(x_i) mod p, normal form
   uint8_t* zbad;          // np * (E+1)  leading coefficient vanished at x_i
   uint64_t* aconv;        // ncchunk * np * (D+1): partial sums, REDC(sum) = Newton coefficient a_k
-  uint64_t* cpart;        // nchunk * np * (D+1): partial sums, REDC(sum) = coefficient mod p
+                          // (persistent schedule)
+  uint64_t* cpart;        // nchunk * np * (D+1): partial sums, REDC(sum) = coefficient mod p; the staged
+                          // and plain schedules write only the first np * (D+1), as c 2^32
   uint32_t* hseg;         // np * hstride: per segment of kCkpt rows, the monomial coefficients of
                           // sum_t a_{k0+t} (x - k0)^(t) (basis change from checkpoint rows)
   int hstride;            // D+1 rounded up to kCkpt
-  uint8_t* ydig;          // np * 5 * hstride  7-bit digit planes of z_i / i! (matrix-core interpolation)
-  uint8_t* hdig;          // np * 5 * hstride  7-bit digit planes of hseg (matrix-core interpolation)
   uint32_t* wT;           // wdpad * wnpad  t_{k,i} = u_{k,i} (M / p_i)^{-1} mod p_i, zero padded (wide path)
   uint32_t* wq;           // D+1         quotient estimate floor(sum_i f_{k,i} / 2^32) (wide path)
   uint64_t* wS;           // (D+1) * Lw * 2  column sum of each limb as (low, high) 64-bit words (wide path)
@@ -119,19 +119,6 @@ struct WorkItem {
   int sub;   // stage-specific (Stirling k-chunk)
 };
 
-// Problems of a job that use the same prime share the basis-change table
-// reads: a group lists (problem, slot) members of one global prime index.
-struct StirMember {
-  int prob;
-  int slot;
-};
-struct StirGroup {
-  int g;       // global prime index
-  int first;   // first member in the member list
-  int count;   // members (at most kStirGroupMax)
-  int maxD;    // largest degree bound among the members
-};
-constexpr int kStirGroupMax = 4;
 constexpr int kSlotCrtPrimes = 512;  // CRT with the primes in per-lane slots (up to 8 per lane)
 constexpr int kMaxPrimes = 4096;     // primes per problem (the wide CRT beyond kSlotCrtPrimes)
 

@@ -265,7 +265,8 @@ int run_crt(rsl_ctx* ctx, Dev* D, const std::vector<DevProblem>& probs) {
     }
     WorkItem* ditems = nullptr;
     if ((rc = upload_vec(ctx, D, items, &ditems)) || (rc = flush(ctx, D))) return rc;
-    return hip_check(ctx, launch_stage(kStageCrt, dprobs, ditems, static_cast<int>(items.size()), lds, ns, T, ctx->stream),
+    return hip_check(ctx, launch_stage(kStageCrt, dprobs, ditems, static_cast<int>(items.size()), lds, ns, T, ctx->stream, 1,
+                                       false),
                      "gcd CRT");
   }
   std::vector<WorkItem> items[3];
@@ -285,7 +286,7 @@ int run_crt(rsl_ctx* ctx, Dev* D, const std::vector<DevProblem>& probs) {
   if ((rc = flush(ctx, D))) return rc;
   for (int pass = 0; pass < 3; ++pass)
     if ((rc = hip_check(ctx, launch_crt_wide(pass, dprobs, ditems[pass], static_cast<int>(items[pass].size()), lds[pass],
-                                             T, ctx->stream),
+                                             T, ctx->stream, false),
                         "gcd CRT")))
       return rc;
   return RSL_OK;

@@ -185,22 +185,19 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     else if (all_pairs < 2LL * 256 * 4 * 64)
       evk = 2;  // one wave can issue only about half a SIMD's rate: give each SIMD two
   }
-  // interpolation on the matrix cores (staged schedule; the layout keeps the
-  // vector items too, for plain runs of the same job)
-  // (degree bounds up to kMmMaxD: the operand of a block stays within 64 KB of LDS)
+  // the persistent schedule's partial sums laid out whole on request (one chunk)
   int dmax = 0;
   for (int k : J->live) dmax = std::max(dmax, J->plans[k].D + 1);
-  const bool mm_req = ((opts && opts->interp_mm > 0) || J->tune.interp_mm != 0) && dmax - 1 <= kMmMaxD;
-  J->mm_interp = mm_req;
-  // one chunk length K for the basis change of every problem, so that problems
-  // sharing a prime can share the checkpoint rows; a multiple of the checkpoint
-  // spacing, enough chunks for the target number of blocks in flight
+  const bool whole_req = (opts && opts->interp_mm > 0) || J->tune.interp_mm != 0;
+  // the persistent schedule's chunk length K of the basis change, one for every
+  // problem: a multiple of the checkpoint spacing, enough chunks for the target
+  // number of blocks in flight
   int Kc = kCkpt;
   {
     int64_t nch = 1;
     if (stir_base < target) nch = (target + stir_base - 1) / std::max<int64_t>(stir_base, 1);
     Kc = std::max<int>(kCkpt, static_cast<int>((dmax + nch - 1) / nch));
-    if (mm_req) Kc = dmax;  // the matrix-core interpolation writes each sum whole: one chunk
+    if (whole_req) Kc = dmax;
     Kc = (Kc + kCkpt - 1) / kCkpt * kCkpt;  // chunks start at checkpoint rows
   }
   J->crt_ns = 1;
@@ -270,7 +267,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     d.wlpad = static_cast<int>(align_up(static_cast<size_t>(P.Lw), kWideMfmaTT));
     d.wnpad = static_cast<int>(align_up(static_cast<size_t>(P.np), kWideMfmaK));
     // the convolution's input range: the basis change's chunking, or whole
-    d.cchunk = (J->tune.conv_whole || mm_req) ? P.D + 1 : d.kchunk;
+    d.cchunk = (J->tune.conv_whole || whole_req) ? P.D + 1 : d.kchunk;
     d.ncchunk = (P.D + 1 + d.cchunk - 1) / d.cchunk;
     if (!P.wide) J->crt_ns = std::max(J->crt_ns, (P.np + 63) / 64);
     J->max_np = std::max(J->max_np, P.np);
@@ -310,7 +307,6 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
   // work items, problem by problem (so that each problem's items are
   // contiguous): each problem's items of each stage are counted, the lists
   // sized, and every problem writes its own ranges (in parallel)
-  constexpr int kHsegList = kNumStages;  // the segment polynomials' list after the stage lists
   auto emit = [&](int li, int s, WorkItem* out) -> int {
     const Plan& P = J->plans[J->live[li]];
     const DevProblem& d = J->dev[li];
@@ -345,17 +341,10 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
         for (int sl = 0; sl < P.np; ++sl)
           for (int b = 0; b < blocks_of(P.E + 1, d.evpb); ++b) put(sl, b, 0);
         break;
-      case kStageConv:
+      case kStageConv:  // Newton coefficients and segment polynomials, then the basis change:
+      case kStageStir:  // tiles of 256 coefficients
         for (int sl = 0; sl < P.np; ++sl)
-          for (int b = 0; b < blocks_of(P.D + 1, 256); ++b)
-            for (int ch = 0; ch < d.ncchunk; ++ch)
-              if (ch * d.cchunk <= std::min(P.D, b * 256 + 255)) put(sl, b, ch);
-        break;
-      case kStageStir:  // basis change: blocks of 256 columns
-        for (int sl = 0; sl < P.np; ++sl)
-          for (int b = 0; b < blocks_of(P.D + 1, 256); ++b)
-            for (int ch = 0; ch < d.nchunk; ++ch)
-              if (std::min(P.D, (ch + 1) * d.kchunk - 1) >= b * 256) put(sl, b, ch);
+          for (int b = 0; b < blocks_of(P.D + 1, kTile); ++b) put(sl, b, 0);
         break;
       case kStageNewton:
         // gapped interpolation is possible only with a non-constant leading
@@ -367,15 +356,11 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
         if (!P.wide)
           for (int b = 0; b < blocks_of(P.D + 1, kCrtWaves); ++b) put(-1, b, 0);
         break;
-      case kHsegList:
-        for (int sl = 0; sl < P.np; ++sl)
-          for (int b = 0; b < blocks_of(P.D + 1, kHsegRows); ++b) put(sl, b, 0);
-        break;
     }
     return c;
   };
   {
-    constexpr int kLists = kNumStages + 1;
+    constexpr int kLists = kNumStages;
     std::vector<int>& cnt = J->tmp_a;
     cnt.assign(static_cast<size_t>(nl) * kLists, 0);
     parallel_for(nl, 16, [&](int li) {
@@ -404,23 +389,16 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
         }
       }
       if (s == kStageEval) J->eval_vstart[nv] = o;
-      std::vector<WorkItem>& v = s < kNumStages ? J->items[s] : J->hseg_items;
-      v.clear();
-      v.resize(o);
+      J->items[s].clear();
+      J->items[s].resize(o);
     }
     parallel_for(nl, 16, [&](int li) {
       ProbLayout& L = J->lay[li];
       for (int s = 0; s < kLists; ++s) {
         const size_t at = static_cast<size_t>(li) * kLists + s;
-        std::vector<WorkItem>& v = s < kNumStages ? J->items[s] : J->hseg_items;
-        emit(li, s, v.data() + off[at]);
-        if (s < kNumStages) {
-          L.item_begin[s] = off[at];
-          L.item_end[s] = off[at] + cnt[at];
-        } else {
-          L.hseg_begin = off[at];
-          L.hseg_end = off[at] + cnt[at];
-        }
+        emit(li, s, J->items[s].data() + off[at]);
+        L.item_begin[s] = off[at];
+        L.item_end[s] = off[at] + cnt[at];
       }
     });
   }
@@ -528,129 +506,6 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     });
   }
 
-  // prime groups for the basis change: every (problem, slot) by global prime
-  // index (slots whose points turn out gapped skip their share)
-  J->sgroups.clear();
-  J->smembers.clear();
-  J->sg_items.clear();
-  J->sg_lds = 0;
-  {
-    // (problem, slot) members by global prime index: a stable counting sort
-    int gidx = 0;
-    for (int li = 0; li < nl; ++li) {
-      const Plan& P = J->plans[J->live[li]];
-      for (int sl = 0; sl < P.np; ++sl) gidx = std::max(gidx, P.pidx[sl] + 1);
-    }
-    std::vector<int> pstart(static_cast<size_t>(gidx) + 1, 0);
-    for (int li = 0; li < nl; ++li) {
-      const Plan& P = J->plans[J->live[li]];
-      for (int sl = 0; sl < P.np; ++sl) ++pstart[P.pidx[sl] + 1];
-    }
-    for (int gi = 0; gi < gidx; ++gi) pstart[gi + 1] += pstart[gi];
-    std::vector<StirMember> by_prime(pstart[gidx]);
-    {
-      std::vector<int> fill(pstart.begin(), pstart.end() - 1);
-      for (int li = 0; li < nl; ++li) {
-        const Plan& P = J->plans[J->live[li]];
-        for (int sl = 0; sl < P.np; ++sl) by_prime[fill[P.pidx[sl]]++] = StirMember{li, sl};
-      }
-    }
-    int gmax = kStirGroupMax;
-    while (gmax > 1 && stir_group_lds_words(gmax, 256) > kLdsWords) --gmax;
-    J->smembers.reserve(by_prime.size());
-    for (int prime = 0; prime < gidx; ++prime) {
-      const StirMember* mem = by_prime.data() + pstart[prime];
-      const size_t msize = static_cast<size_t>(pstart[prime + 1] - pstart[prime]);
-      for (size_t b = 0; b < msize; b += gmax) {
-        StirGroup G{prime, static_cast<int>(J->smembers.size()), static_cast<int>(std::min<size_t>(gmax, msize - b)),
-                    0};
-        for (int m = 0; m < G.count; ++m) {
-          J->smembers.push_back(mem[b + m]);
-          G.maxD = std::max(G.maxD, J->dev[mem[b + m].prob].D);
-        }
-        const int gi = static_cast<int>(J->sgroups.size());
-        J->sgroups.push_back(G);
-        J->sg_lds = std::max<size_t>(J->sg_lds, static_cast<size_t>(stir_group_lds_words(kStirGroupMax, 256)) * 4);
-        for (int jb = 0; jb < blocks_of(G.maxD + 1, 256); ++jb)
-          for (int ch = 0; ch * Kc <= G.maxD; ++ch) {
-            const int ke = std::min(G.maxD, (ch + 1) * Kc - 1);
-            if (ke >= jb * 256) J->sg_items.push_back({gi, -1, jb, ch});
-          }
-      }
-    }
-  }
-
-  // matrix-core interpolation: every (problem, slot) by global prime
-  // index (a stable counting sort), groups of all members of a prime
-  J->mgroups.clear();
-  J->mmembers.clear();
-  J->dig_items.clear();
-  J->mm_items.clear();
-  J->mm_lds[0] = J->mm_lds[1] = 0;
-  if (mm_req) {
-    int gidx = 0;
-    for (int li = 0; li < nl; ++li) {
-      const Plan& P = J->plans[J->live[li]];
-      for (int sl = 0; sl < P.np; ++sl) gidx = std::max(gidx, P.pidx[sl] + 1);
-    }
-    std::vector<int> pstart(static_cast<size_t>(gidx) + 1, 0);
-    for (int li = 0; li < nl; ++li) {
-      const Plan& P = J->plans[J->live[li]];
-      for (int sl = 0; sl < P.np; ++sl) ++pstart[P.pidx[sl] + 1];
-    }
-    for (int gi = 0; gi < gidx; ++gi) pstart[gi + 1] += pstart[gi];
-    J->mmembers.resize(pstart[gidx]);
-    {
-      std::vector<int> fill(pstart.begin(), pstart.end() - 1);
-      for (int li = 0; li < nl; ++li) {
-        const Plan& P = J->plans[J->live[li]];
-        for (int sl = 0; sl < P.np; ++sl) J->mmembers[fill[P.pidx[sl]]++] = StirMember{li, sl};
-      }
-    }
-    for (int prime = 0; prime < gidx; ++prime) {
-      const int first = pstart[prime], count = pstart[prime + 1] - first;
-      if (count == 0) continue;
-      // largest degree bound first: each 16-column tile is bounded by its first column
-      std::stable_sort(J->mmembers.begin() + first, J->mmembers.begin() + first + count,
-                       [&](const StirMember& a, const StirMember& b) { return J->dev[a.prob].D > J->dev[b.prob].D; });
-      StirGroup G{prime, first, count, 0};
-      for (int m = first; m < first + count; ++m) G.maxD = std::max(G.maxD, J->dev[J->mmembers[m].prob].D);
-      const int gi = static_cast<int>(J->mgroups.size());
-      J->mgroups.push_back(G);
-      // items: (group, 64 rows, a run of 16-column tiles whose slices add up to
-      // about kMmRunSlices); a tile whose largest bound is below the rows has
-      // nothing there, and neither have the tiles after it
-      const int ntile = blocks_of(count, 16);
-      for (int rs = 0; rs < blocks_of(G.maxD + 1, 64); ++rs) {
-        const int rs0 = 64 * rs;
-        int ct = 0;
-        while (ct < ntile) {
-          const int tileD0 = J->dev[J->mmembers[first + 16 * ct].prob].D;
-          if (tileD0 < rs0) break;
-          for (int which = 1; which <= 2; ++which)
-            J->mm_lds[which - 1] = std::max(J->mm_lds[which - 1], kMmColBytes + mm_operand_bytes(which, rs0, tileD0));
-          int n = 0, cost = 0;
-          while (ct + n < ntile && n < kMmTilesMax && cost < kMmRunSlices) {
-            const int tD = J->dev[J->mmembers[first + 16 * (ct + n)].prob].D;
-            if (tD < rs0) break;
-            const int c1 = mm_slices_hi(1, rs0, tD) - mm_slices_lo(1, rs0) + 1;
-            const int c2 = mm_slices_hi(2, rs0, tD) - mm_slices_lo(2, rs0) + 1;
-            cost += std::max(c1, c2);
-            ++n;
-          }
-          J->mm_items.push_back({gi, rs, ct, n + 32 * tileD0});
-          ct += n;
-        }
-      }
-    }
-    for (int li = 0; li < nl; ++li) {
-      const Plan& P = J->plans[J->live[li]];
-      const int Dp = static_cast<int>(align_up(static_cast<size_t>(P.D + 1), kCkpt));
-      for (int sl = 0; sl < P.np; ++sl)
-        for (int b = 0; b < blocks_of(Dp, kDigitsPerBlock); ++b) J->dig_items.push_back({li, sl, b, 0});
-    }
-  }
-
   // device layout: [problems | items | inputs | statuses][outputs][intermediates]
   const size_t A = 256;
   size_t o = 0;
@@ -662,22 +517,6 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
   }
   J->evs_off = o;
   o = align_up(o + sizeof(WorkItem) * J->eval_staged.size(), A);
-  J->sg_off = o;
-  o = align_up(o + sizeof(StirGroup) * J->sgroups.size(), A);
-  J->sm_off = o;
-  o = align_up(o + sizeof(StirMember) * J->smembers.size(), A);
-  J->sgi_off = o;
-  o = align_up(o + sizeof(WorkItem) * J->sg_items.size(), A);
-  J->hseg_off = o;
-  o = align_up(o + sizeof(WorkItem) * J->hseg_items.size(), A);
-  J->mg_off = o;
-  o = align_up(o + sizeof(StirGroup) * J->mgroups.size(), A);
-  J->mm_off = o;
-  o = align_up(o + sizeof(StirMember) * J->mmembers.size(), A);
-  J->digi_off = o;
-  o = align_up(o + sizeof(WorkItem) * J->dig_items.size(), A);
-  J->mmi_off = o;
-  o = align_up(o + sizeof(WorkItem) * J->mm_items.size(), A);
   for (int pass = 0; pass < 3; ++pass) {
     J->wide_off[pass] = o;
     o = align_up(o + sizeof(WorkItem) * J->wide_items[pass].size(), A);
@@ -797,12 +636,6 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     L.aconv = o; o = align_up(o + static_cast<size_t>(d.ncchunk) * np * (P.D + 1) * 8, A);
     L.cpart = o; o = align_up(o + static_cast<size_t>(d.nchunk) * np * (P.D + 1) * 8, A);
     L.hseg = o;  o = align_up(o + np * align_up(static_cast<size_t>(P.D + 1), kCkpt) * 4, A);
-    L.ydig = L.hdig = 0;
-    if (mm_req) {  // digit planes of the matrix-core interpolation
-      const size_t planes = np * kDigits * align_up(static_cast<size_t>(P.D + 1), kCkpt);
-      L.ydig = o; o = align_up(o + planes, A);
-      L.hdig = o; o = align_up(o + planes, A);
-    }
     L.wT = L.wq = L.wS = L.wMd = 0;
     if (P.wide) {
       if (!L.crt_own) {
@@ -825,8 +658,8 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     const DevProblem& d = J->dev[li];
     auto up = [&](int s, size_t words) { J->stage_lds[s] = std::max(J->stage_lds[s], words * 4); };
     up(kStageEval, eval_stage_lds_words(d));
-    up(kStageConv, static_cast<size_t>(std::min(d.cchunk, d.D + 1)) + std::min(d.D + 1, d.cchunk + 256));
-    up(kStageStir, std::max(basis_lds_words(1, 256, 0), kHsegRows));
+    up(kStageConv, interp_coeffs_lds_words(d.D, 4));
+    up(kStageStir, interp_basis_lds_words(4));
     if (J->lay[li].item_end[kStageNewton] > J->lay[li].item_begin[kStageNewton]) up(kStageNewton, newton_lds_words(d, 1024));
     if (!d.wide) up(kStageCrt, crt_lds_words(d, J->crt_ns, crt_block_waves(J->crt_ns)));
     if (d.L_in > 2) up(kStageReduce, reduce_ml_lds_words());
@@ -844,7 +677,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     const DevProblem& d = J->dev[li];
     size_t w = std::max(eval_group_lds_words(d, d.evk), eval_lds_words(d));  // no register form here
     w = std::max<size_t>(w, static_cast<size_t>(std::min(d.cchunk, d.D + 1)) + std::min(d.D + 1, d.cchunk + 64));
-    w = std::max<size_t>(w, basis_lds_words(1, 64, d.kchunk));
+    w = std::max<size_t>(w, basis_lds_words(64, d.kchunk));
     if (J->lay[li].item_end[kStageNewton] > J->lay[li].item_begin[kStageNewton])
       w = std::max<size_t>(w, newton_lds_words(d, 64));
     if (!d.wide) w = std::max<size_t>(w, crt_lds_words(d, J->crt_ns, 1));
@@ -951,8 +784,6 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     d.aconv = reinterpret_cast<uint64_t*>(base + L.aconv);
     d.cpart = reinterpret_cast<uint64_t*>(base + L.cpart);
     d.hseg = reinterpret_cast<uint32_t*>(base + L.hseg);
-    d.ydig = L.ydig ? base + L.ydig : nullptr;
-    d.hdig = L.hdig ? base + L.hdig : nullptr;
     d.hstride = static_cast<int>(align_up(static_cast<size_t>(P.D + 1), kCkpt));
     d.out = reinterpret_cast<uint32_t*>(base + L.out);
     d.status = reinterpret_cast<int*>(base + L.status);
@@ -1016,19 +847,6 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
       std::memcpy(blob + J->wide_off[pass], J->wide_items[pass].data(), sizeof(WorkItem) * J->wide_items[pass].size());
   if (!J->wdig_items.empty())
     std::memcpy(blob + J->wdig_off, J->wdig_items.data(), sizeof(WorkItem) * J->wdig_items.size());
-  if (!J->hseg_items.empty())
-    std::memcpy(blob + J->hseg_off, J->hseg_items.data(), sizeof(WorkItem) * J->hseg_items.size());
-  if (!J->mgroups.empty()) {
-    std::memcpy(blob + J->mg_off, J->mgroups.data(), sizeof(StirGroup) * J->mgroups.size());
-    std::memcpy(blob + J->mm_off, J->mmembers.data(), sizeof(StirMember) * J->mmembers.size());
-    std::memcpy(blob + J->digi_off, J->dig_items.data(), sizeof(WorkItem) * J->dig_items.size());
-    std::memcpy(blob + J->mmi_off, J->mm_items.data(), sizeof(WorkItem) * J->mm_items.size());
-  }
-  if (!J->sgroups.empty()) {
-    std::memcpy(blob + J->sg_off, J->sgroups.data(), sizeof(StirGroup) * J->sgroups.size());
-    std::memcpy(blob + J->sm_off, J->smembers.data(), sizeof(StirMember) * J->smembers.size());
-    std::memcpy(blob + J->sgi_off, J->sg_items.data(), sizeof(WorkItem) * J->sg_items.size());
-  }
 }
 
 // CRT tables: canonical prime lists use the context's global tables.
@@ -1102,7 +920,6 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
   const DevProblem* probs = reinterpret_cast<const DevProblem*>(J->base + J->probs_off);
   auto items = [&](int s) { return reinterpret_cast<const WorkItem*>(J->base + J->items_off[s]); };
   auto wide = [&](int pass) { return reinterpret_cast<const WorkItem*>(J->base + J->wide_off[pass]); };
-  const WorkItem* hseg_items = reinterpret_cast<const WorkItem*>(J->base + J->hseg_off);
   int rc;
   if (mode == RSL_PLAIN) {
     for (size_t li = 0; li < J->live.size(); ++li) {
@@ -1112,20 +929,19 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
       const int ns = J->crt_ns;
       for (int s = 0; s < kNumStages; ++s) {
         const int cnt = L.item_end[s] - L.item_begin[s];
-        if (s == kStageStir &&
-            (rc = hip_check(ctx, launch_hseg(probs, hseg_items + L.hseg_begin, L.hseg_end - L.hseg_begin, T, st),
-                            "launch")))
-          return rc;
-        const hipError_t e = (s == kStageEval)
-            ? launch_eval(eval_variant(J->dev[li]), probs, items(s) + L.item_begin[s], cnt,
-                          static_cast<size_t>(eval_stage_lds_words(J->dev[li])) * 4, T, st)
-            : launch_stage(s, probs, items(s) + L.item_begin[s], cnt, J->stage_lds[s], ns, T, st);
+        const hipError_t e =
+            s == kStageEval ? launch_eval(eval_variant(J->dev[li]), probs, items(s) + L.item_begin[s], cnt,
+                                          static_cast<size_t>(eval_stage_lds_words(J->dev[li])) * 4, T, st)
+            : s == kStageConv || s == kStageStir
+                ? launch_interp(s - kStageConv, probs, items(s) + L.item_begin[s], cnt, J->dev[li].D, T, st)
+                : launch_stage(s, probs, items(s) + L.item_begin[s], cnt, J->stage_lds[s], ns, T, st, 1, true);
         if ((rc = hip_check(ctx, e, "launch"))) return rc;
       }
       for (int pass = 0; pass < 3; ++pass) {
         const int cnt = L.wide_end[pass] - L.wide_begin[pass];
         const int kp = (pass == 1 && J->wide_mfma) ? 3 : pass;
-        if ((rc = hip_check(ctx, launch_crt_wide(kp, probs, wide(pass) + L.wide_begin[pass], cnt, J->wide_lds[pass], T, st),
+        if ((rc = hip_check(ctx, launch_crt_wide(kp, probs, wide(pass) + L.wide_begin[pass], cnt, J->wide_lds[pass], T, st,
+                                                 true),
                             "launch")))
           return rc;
       }
@@ -1181,32 +997,9 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
           return rc;
       continue;
     }
-    if (J->mm_interp && (s == kStageConv || s == kStageStir)) {
-      // the interpolation's two products on the matrix cores (the segments'
-      // polynomials between them, from the Newton coefficients)
-      const StirGroup* mg = reinterpret_cast<const StirGroup*>(J->base + J->mg_off);
-      const StirMember* mm = reinterpret_cast<const StirMember*>(J->base + J->mm_off);
-      const WorkItem* di = reinterpret_cast<const WorkItem*>(J->base + J->digi_off);
-      const WorkItem* mi = reinterpret_cast<const WorkItem*>(J->base + J->mmi_off);
-      const int nd = static_cast<int>(J->dig_items.size()), nm = static_cast<int>(J->mm_items.size());
-      if (s == kStageStir &&
-          (rc = hip_check(ctx, launch_hseg(probs, hseg_items, static_cast<int>(J->hseg_items.size()), T, st),
-                          "launch")))
-        return rc;
-      const int which = s == kStageConv ? 1 : 2;
-      if ((rc = hip_check(ctx, launch_interp_mm(which, probs, mg, mm, di, nd, mi, nm, J->mm_lds[which - 1], T, st),
-                          "launch")))
-        return rc;
-      continue;
-    }
-    if (s == kStageStir &&
-        (rc = hip_check(ctx, launch_hseg(probs, hseg_items, static_cast<int>(J->hseg_items.size()), T, st), "launch")))
-      return rc;
-    if (s == kStageStir && !J->sg_items.empty()) {
-      if ((rc = hip_check(ctx, launch_stir_group(probs, reinterpret_cast<const StirGroup*>(J->base + J->sg_off),
-                                                 reinterpret_cast<const StirMember*>(J->base + J->sm_off),
-                                                 reinterpret_cast<const WorkItem*>(J->base + J->sgi_off),
-                                                 static_cast<int>(J->sg_items.size()), J->sg_lds, T, st),
+    if (s == kStageConv || s == kStageStir) {
+      if ((rc = hip_check(ctx, launch_interp(s - kStageConv, probs, items(s), static_cast<int>(J->items[s].size()),
+                                             J->need_D, T, st),
                           "launch")))
         return rc;
       continue;
@@ -1215,13 +1008,13 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
     // or more (the degree-24 pair, 146 items, keeps one per block)
     const int crt_per = J->items[kStageCrt].size() >= 1024 ? kCrtItemsPerBlock : 1;
     if ((rc = hip_check(ctx, launch_stage(s, probs, items(s), static_cast<int>(J->items[s].size()),
-                                          J->stage_lds[s], J->crt_ns, T, st, crt_per), "launch")))
+                                          J->stage_lds[s], J->crt_ns, T, st, crt_per, true), "launch")))
       return rc;
     if (s == kStageCrt)
       for (int pass = 0; pass < 3; ++pass)
         if ((rc = hip_check(ctx, launch_crt_wide((pass == 1 && J->wide_mfma) ? 3 : pass, probs, wide(pass),
                                                  static_cast<int>(J->wide_items[pass].size()),
-                                                 J->wide_lds[pass], T, st), "launch")))
+                                                 J->wide_lds[pass], T, st, true), "launch")))
           return rc;
   }
   if (stage_events && (rc = hip_check(ctx, hipEventRecord(ctx->ev[kNumStages], st), "event"))) return rc;

@@ -23,8 +23,7 @@ namespace rsl {
 struct ProbLayout {
   // offsets from the job base
   size_t coeff, gdeg, pidx, Hm, NH, Tg, invM, Plimb, Mi, wdir, rinv, negM, Mw, NHM, wMd, status;
-  size_t out, resid, dig, zval, zbad, aconv, cpart, hseg, ydig, hdig, wT, wq, wS;
-  int hseg_begin, hseg_end;        // range of Job::hseg_items
+  size_t out, resid, dig, zval, zbad, aconv, cpart, hseg, wT, wq, wS;
   int L_in;
   bool crt_own;  // this problem's layout holds the CRT constant block it shares
   int crt_from;  // live index of the problem whose layout holds its CRT constant block
@@ -50,23 +49,6 @@ struct Job {
   std::vector<int> eval_vstart;        // first evaluation item of each layout variant (and the end)
   std::vector<WorkItem> eval_staged;   // evaluation items dealt across XCDs
   size_t evs_off = 0;
-  // basis change over prime groups (staged schedule)
-  std::vector<StirGroup> sgroups;
-  std::vector<StirMember> smembers;
-  std::vector<WorkItem> sg_items;
-  size_t sg_off = 0, sm_off = 0, sgi_off = 0, sg_lds = 0;
-  // segment polynomials of the basis change (before the stir stage)
-  std::vector<WorkItem> hseg_items;
-  size_t hseg_off = 0;
-  // interpolation on the matrix cores: prime groups of (problem, slot) columns
-  // (all members of a prime), the digit-plane items (problem, slot, block of
-  // 2048 positions) and the product items (group, 64-row set, run of column tiles)
-  bool mm_interp = false;
-  std::vector<StirGroup> mgroups;
-  std::vector<StirMember> mmembers;
-  std::vector<WorkItem> dig_items, mm_items;
-  int mm_lds[2] = {0, 0};  // dynamic LDS bytes of the two matrix-core interpolation launches
-  size_t mg_off = 0, mm_off = 0, digi_off = 0, mmi_off = 0;
   // the ranges the kernels expect zeroed (a table in the upload image, cleared
   // by one launch after the upload)
   size_t clr_off = 0;

@@ -8,8 +8,8 @@
 //                                                         (paper Sec. 4.1, step 1)
 //   eval_ures   one lane per (prime, point): Horner evaluation at x_i and the
 //               univariate resultant over Z_p             (Sec. 4.1, steps 1-2)
-//   interp_conv Newton forward differences on consecutive points
-//   interp_stir falling-factorial -> monomial basis (partial sums per k-chunk)
+//   interp      Newton forward differences on consecutive points and segment
+//               polynomials; falling-factorial -> monomial basis
 //   interp_newton divided differences on a gapped point set (bad points replaced)
 //                                                         (Sec. 4.1, step 3)
 //   crt         direct form with Garner fallback + radix conversion to limbs (Sec. 4.1, step 3)
@@ -51,71 +51,38 @@ hipError_t launch_eval(int variant, const DevProblem* probs, const WorkItem* ite
   return launch(variant, probs, items, nitems, lds, T, st);
 }
 
-__global__ __launch_bounds__(256) void k_interp_conv(const DevProblem* probs, const WorkItem* items, DevTables T) {
-  extern __shared__ uint32_t lds[];
+template <int WHICH, int KS>
+__global__ __launch_bounds__(64 * KS) void k_interp(const DevProblem* probs, const WorkItem* items, DevTables T) {
+  extern __shared__ uint4 lds4[];
+  uint32_t* lds = reinterpret_cast<uint32_t*>(lds4);
   const WorkItem w = items[blockIdx.x];
-  stage_interp_conv(probs[w.prob], T, w, lds);
+  if constexpr (WHICH == 0) stage_interp_coeffs<KS>(probs[w.prob], T, w, lds);
+  else stage_interp_basis<KS>(probs[w.prob], T, w, lds);
 }
 
-__global__ __launch_bounds__(256) void k_interp_stir(const DevProblem* probs, const WorkItem* items, DevTables T) {
-  extern __shared__ uint32_t lds[];
-  const WorkItem w = items[blockIdx.x];
-  stage_interp_stir<true>(probs[w.prob], T, w, lds);
-}
-
-__global__ __launch_bounds__(kHsegRows) void k_interp_hseg(const DevProblem* probs, const WorkItem* items, DevTables T) {
-  __shared__ uint32_t lds[kHsegRows];
-  const WorkItem w = items[blockIdx.x];
-  stage_interp_hseg(probs[w.prob], T, w, lds);
-}
-
-hipError_t launch_hseg(const DevProblem* probs, const WorkItem* items, int nitems, const DevTables& T, hipStream_t st) {
+hipError_t launch_interp(int which, const DevProblem* probs, const WorkItem* items, int nitems, int maxD,
+                         const DevTables& T, hipStream_t st) {
   if (nitems <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_interp_hseg, dim3(nitems), dim3(kHsegRows), 0, st, probs, items, T);
+  const int ks = nitems < kInterpSplitItems ? 4 : 1;
+  const size_t lds = static_cast<size_t>(which == 0 ? interp_coeffs_lds_words(maxD, ks) : interp_basis_lds_words(ks)) * 4;
+  const dim3 g(nitems), b(64 * ks);
+  if (which == 0 && ks == 4) hipLaunchKernelGGL((k_interp<0, 4>), g, b, lds, st, probs, items, T);
+  else if (which == 0) hipLaunchKernelGGL((k_interp<0, 1>), g, b, lds, st, probs, items, T);
+  else if (ks == 4) hipLaunchKernelGGL((k_interp<1, 4>), g, b, lds, st, probs, items, T);
+  else hipLaunchKernelGGL((k_interp<1, 1>), g, b, lds, st, probs, items, T);
   return hipGetLastError();
 }
 
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_interp_digits(const DevProblem* probs, const WorkItem* items, DevTables T) {
-  const WorkItem w = items[blockIdx.x];
-  stage_interp_digits<WHICH>(probs[w.prob], T, w);
-}
-
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_interp_mm(const DevProblem* probs, const StirGroup* groups,
-                                                   const StirMember* members, const WorkItem* items, DevTables T) {
-  extern __shared__ uint64_t lds8[];
-  const WorkItem w = items[blockIdx.x];
-  stage_interp_mm<WHICH>(probs, groups[w.prob], members, w, T, reinterpret_cast<uint8_t*>(lds8));
-}
-
-hipError_t launch_interp_mm(int which, const DevProblem* probs, const StirGroup* groups, const StirMember* members,
-                            const WorkItem* digit_items, int ndigit, const WorkItem* mm_items, int nmm,
-                            int lds_bytes, const DevTables& T, hipStream_t st) {
-  if (ndigit > 0) {
-    if (which == 1) hipLaunchKernelGGL(k_interp_digits<1>, dim3(ndigit), dim3(256), 0, st, probs, digit_items, T);
-    else hipLaunchKernelGGL(k_interp_digits<2>, dim3(ndigit), dim3(256), 0, st, probs, digit_items, T);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (nmm <= 0) return hipSuccess;
-  if (lds_bytes < kMmColBytes || lds_bytes > 65536) return hipErrorInvalidValue;
-  if (which == 1)
-    hipLaunchKernelGGL(k_interp_mm<1>, dim3(nmm), dim3(256), lds_bytes, st, probs, groups, members, mm_items, T);
-  else
-    hipLaunchKernelGGL(k_interp_mm<2>, dim3(nmm), dim3(256), lds_bytes, st, probs, groups, members, mm_items, T);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(1024) void k_interp_newton(const DevProblem* probs, const WorkItem* items, DevTables T) {
+__global__ __launch_bounds__(1024) void k_interp_newton(const DevProblem* probs, const WorkItem* items, DevTables T,
+                                                        bool whole) {
   extern __shared__ uint32_t lds[];
   const WorkItem w = items[blockIdx.x];
-  stage_interp_newton(probs[w.prob], T, w, lds);
+  stage_interp_newton(probs[w.prob], T, w, lds, whole);
 }
 
 template <int NS>
 __global__ __launch_bounds__(512) void k_crt(const DevProblem* probs, const WorkItem* items, int nitems, int per,
-                                             DevTables T) {
+                                             DevTables T, bool whole) {
   extern __shared__ uint32_t lds[];
   // items blockIdx.x * per .. + per - 1 (one problem's items are consecutive:
   // the constants and limb table are staged again only when the problem changes)
@@ -125,14 +92,15 @@ __global__ __launch_bounds__(512) void k_crt(const DevProblem* probs, const Work
     const WorkItem w = items[idx];
     const bool fresh = b == 0 || items[idx - 1].prob != w.prob;
     if (b > 0) __syncthreads();  // the previous item's waves are done with the LDS
-    stage_crt<NS>(probs[w.prob], T, w, lds, kCrtBlockCoeffs / static_cast<int>(blockDim.x >> 6), fresh);
+    stage_crt<NS>(probs[w.prob], T, w, lds, kCrtBlockCoeffs / static_cast<int>(blockDim.x >> 6), fresh, whole);
   }
 }
 
-__global__ __launch_bounds__(256) void k_crt_wide_t(const DevProblem* probs, const WorkItem* items, DevTables T) {
+__global__ __launch_bounds__(256) void k_crt_wide_t(const DevProblem* probs, const WorkItem* items, DevTables T,
+                                                     bool whole) {
   extern __shared__ uint32_t lds[];
   const WorkItem w = items[blockIdx.x];
-  stage_crt_wide_t(probs[w.prob], T, w, lds);
+  stage_crt_wide_t(probs[w.prob], T, w, lds, whole);
 }
 
 __global__ __launch_bounds__(kWideHT) void k_crt_wide_sum(const DevProblem* probs, const WorkItem* items) {
@@ -166,11 +134,11 @@ hipError_t launch_wide_digits(const DevProblem* probs, const WorkItem* items, in
 }
 
 hipError_t launch_crt_wide(int pass, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
-                           const DevTables& T, hipStream_t st) {
+                           const DevTables& T, hipStream_t st, bool whole) {
   if (nitems <= 0) return hipSuccess;
   const dim3 g(nitems);
   switch (pass) {
-    case 0: hipLaunchKernelGGL(k_crt_wide_t, g, dim3(256), lds, st, probs, items, T); break;
+    case 0: hipLaunchKernelGGL(k_crt_wide_t, g, dim3(256), lds, st, probs, items, T, whole); break;
     case 1: hipLaunchKernelGGL(k_crt_wide_sum, g, dim3(kWideHT), lds, st, probs, items); break;
     case 2: hipLaunchKernelGGL(k_crt_wide_fin, g, dim3(64), lds, st, probs, items); break;
     case 3: hipLaunchKernelGGL(k_crt_wide_sum_mfma, g, dim3(256), lds, st, probs, items); break;
@@ -246,24 +214,8 @@ __global__ __launch_bounds__(1024) void k_stirling_build(uint32_t* stir, int64_t
 
 // ------------------------------------------------------------ launchers
 
-__global__ __launch_bounds__(256) void k_interp_stir_group(const DevProblem* probs, const StirGroup* groups,
-                                                           const StirMember* members, const WorkItem* items,
-                                                           DevTables T) {
-  extern __shared__ uint32_t lds[];
-  const WorkItem w = items[blockIdx.x];
-  stage_interp_stir_group(probs, groups, members, T, w, lds);
-}
-
-hipError_t launch_stir_group(const DevProblem* probs, const StirGroup* groups, const StirMember* members,
-                             const WorkItem* items, int nitems, size_t lds, const DevTables& T, hipStream_t st) {
-  if (nitems <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_interp_stir_group, dim3(nitems), dim3(256), lds, st, probs, groups, members,
-                     items, T);
-  return hipGetLastError();
-}
-
 hipError_t launch_stage(int stage, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
-                        int crt_ns, const DevTables& T, hipStream_t st, int crt_per_block) {
+                        int crt_ns, const DevTables& T, hipStream_t st, int crt_per_block, bool whole) {
   if (nitems <= 0) return hipSuccess;
   const dim3 g(nitems);
   const int per = crt_per_block > 1 ? crt_per_block : 1;
@@ -271,20 +223,20 @@ hipError_t launch_stage(int stage, const DevProblem* probs, const WorkItem* item
   switch (stage) {
     case kStageReduce: hipLaunchKernelGGL(k_reduce, g, dim3(256), lds, st, probs, items, T); break;
     case kStageEval: return hipErrorInvalidValue;  // launch_eval: one kernel per layout
-    case kStageConv: hipLaunchKernelGGL(k_interp_conv, g, dim3(256), lds, st, probs, items, T); break;
-    case kStageStir: hipLaunchKernelGGL(k_interp_stir, g, dim3(256), lds, st, probs, items, T); break;
-    case kStageNewton: hipLaunchKernelGGL(k_interp_newton, g, dim3(1024), lds, st, probs, items, T); break;
+    case kStageConv: return hipErrorInvalidValue;  // launch_interp
+    case kStageStir: return hipErrorInvalidValue;
+    case kStageNewton: hipLaunchKernelGGL(k_interp_newton, g, dim3(1024), lds, st, probs, items, T, whole); break;
     case kStageCrt:
       switch (crt_ns) {
-        case 1: hipLaunchKernelGGL(k_crt<1>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T); break;
-        case 2: hipLaunchKernelGGL(k_crt<2>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T); break;
-        case 3: hipLaunchKernelGGL(k_crt<3>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T); break;
-        case 4: hipLaunchKernelGGL(k_crt<4>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T); break;
+        case 1: hipLaunchKernelGGL(k_crt<1>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T, whole); break;
+        case 2: hipLaunchKernelGGL(k_crt<2>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T, whole); break;
+        case 3: hipLaunchKernelGGL(k_crt<3>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T, whole); break;
+        case 4: hipLaunchKernelGGL(k_crt<4>, gc, dim3(kCrtWaves * 64), lds, st, probs, items, nitems, per, T, whole); break;
         case 6:
-          hipLaunchKernelGGL(k_crt<6>, gc, dim3(crt_block_waves(6) * 64), lds, st, probs, items, nitems, per, T);
+          hipLaunchKernelGGL(k_crt<6>, gc, dim3(crt_block_waves(6) * 64), lds, st, probs, items, nitems, per, T, whole);
           break;
         case 8:
-          hipLaunchKernelGGL(k_crt<8>, gc, dim3(crt_block_waves(8) * 64), lds, st, probs, items, nitems, per, T);
+          hipLaunchKernelGGL(k_crt<8>, gc, dim3(crt_block_waves(8) * 64), lds, st, probs, items, nitems, per, T, whole);
           break;
         default: return hipErrorInvalidValue;
       }

@@ -116,9 +116,9 @@ __global__ __launch_bounds__(64) void k_persistent(const DevProblem* probs, Queu
         break;
       case kTaskEval: stage_eval_columns(P, T, w, lds); break;
       case kTaskConv: stage_interp_conv(P, T, w, lds); break;
-      case kTaskStir: stage_interp_stir<false>(P, T, w, lds); break;
-      case kTaskNewton: stage_interp_newton(P, T, w, lds); break;
-      case kTaskCrt: stage_crt<NS>(P, T, w, lds, kCrtPerTask); break;
+      case kTaskStir: stage_interp_stir(P, T, w, lds); break;
+      case kTaskNewton: stage_interp_newton(P, T, w, lds, false); break;
+      case kTaskCrt: stage_crt<NS>(P, T, w, lds, kCrtPerTask, true, false); break;
       default: break;
     }
     // successors (decided by thread 0 after the block's writes are released)

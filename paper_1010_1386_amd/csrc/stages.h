@@ -1375,44 +1375,18 @@ __device__ inline uint32_t segment_h(const uint32_t* a, int kb, int k0, int ke, 
   return h;
 }
 
-// The segments' h of one problem and prime: item (problem, slot, block of
-// kHsegRows rows), one segment per half wave.
-constexpr int kHsegRows = 256;
-__device__ inline void stage_interp_hseg(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
-  if (!fast_prime(P, w.slot)) return;
-  const PrimeConst pc = T.pc[P.pidx[w.slot]];
-  const int kb = w.blk * kHsegRows;
-  const int ke = (kb + kHsegRows - 1 < P.D) ? kb + kHsegRows - 1 : P.D;
-  load_newton_coeffs(P, w.slot, pc, kb, ke, lds);
-  __syncthreads();
-  const int k0 = kb + kCkpt * (static_cast<int>(threadIdx.x) / kCkpt);
-  if (k0 > ke) return;
-  const uint32_t h = segment_h(lds, kb, k0, ke, pc);
-  P.hseg[static_cast<size_t>(w.slot) * P.hstride + k0 + (threadIdx.x & (kCkpt - 1))] = h;
-}
-
-// Rows [k1, ke] (k1 a multiple of kCkpt) into the partial sums acc[m] of
-// column j0 + threadIdx.x for G members; the block's threads are its columns.
-// h of member m for the segment at k0: hsrc[m][k0 + i] (HG), or expanded here
-// from a_k at lds_a[k - kb] (G = 1).  LDS: lh (G kCkpt words), lw (blockDim + kCkpt - 1).
-template <int GM, bool HG>
-__device__ inline void basis_block(const uint32_t* S, int j0, int k1, int ke, int kb, int G,
-                                   const uint32_t* const* hsrc, const int* hmax, const uint32_t* lds_a,
-                                   const PrimeConst& pc, uint32_t* lh, uint32_t* lw, uint64_t (&acc)[GM]) {
+// Rows [k1, ke] (k1 a multiple of kCkpt) into the partial sum acc of column
+// j0 + threadIdx.x; the block's threads are its columns.  The segments' h are
+// expanded here from a_k at lds_a[k - kb].  LDS: lh (kCkpt words), lw
+// (blockDim + kCkpt - 1).
+__device__ inline uint64_t basis_block(const uint32_t* S, int j0, int k1, int ke, int kb, const uint32_t* lds_a,
+                                       const PrimeConst& pc, uint32_t* lh, uint32_t* lw) {
   const int nt = blockDim.x, tid = threadIdx.x;
-  const uint32_t p = pc.p;
-  // the next segment's h (HG: one value per thread, nt >= GM kCkpt) and row
-  // window (two values per thread, nt >= kCkpt - 1) are loaded into registers
-  // while the current segment is convolved
-  uint32_t nh = 0u, nw0 = 0u, nw1 = 0u;
+  uint64_t acc = 0u;
+  // the next segment's row window (two values per thread, nt >= kCkpt - 1) is
+  // loaded into registers while the current segment is convolved
+  uint32_t nw0 = 0u, nw1 = 0u;
   auto fetch = [&](int k0) {
-    if constexpr (HG) {
-      const int m = tid / kCkpt, u = tid & (kCkpt - 1);
-      nh = 0u;
-#pragma unroll
-      for (int mm = 0; mm < GM; ++mm)
-        if (mm == m && mm < G && k0 <= hmax[mm]) nh = hsrc[mm][k0 + u];  // beyond a member's bound: h = 0
-    }
     const uint32_t* row = S + ckpt_rowoff(k0 / kCkpt);
     const int ja = j0 - (kCkpt - 1) + tid, jb = ja + nt;
     nw0 = (ja >= 0 && ja <= k0) ? row[ja] : 0u;
@@ -1420,251 +1394,334 @@ __device__ inline void basis_block(const uint32_t* S, int j0, int k1, int ke, in
   };
   if (k1 <= ke) fetch(k1);
   for (int k0 = k1; k0 <= ke; k0 += kCkpt) {
-    if constexpr (HG) {
-      if (tid < GM * kCkpt) lh[tid] = nh;
-    } else {
-      if (tid < kCkpt) lh[tid] = segment_h(lds_a, kb, k0, ke, pc);
-    }
+    if (tid < kCkpt) lh[tid] = segment_h(lds_a, kb, k0, ke, pc);
     lw[tid] = nw0;
     if (tid < kCkpt - 1) lw[nt + tid] = nw1;
     __syncthreads();
     if (k0 + kCkpt <= ke) fetch(k0 + kCkpt);
 #pragma unroll 8
-    for (int i = 0; i < kCkpt; ++i) {
-      const uint32_t w = lw[tid + kCkpt - 1 - i];  // s(k0, j - i)
-#pragma unroll
-      for (int m = 0; m < GM; ++m)
-        if (m < G) acc[m] = mac_fold(acc[m], lh[m * kCkpt + i], w, p);
-    }
+    for (int i = 0; i < kCkpt; ++i) acc = mac_fold(acc, lh[i], lw[tid + kCkpt - 1 - i], pc.p);  // s(k0, j - i)
     __syncthreads();  // the next segment overwrites lh and lw
   }
+  return acc;
 }
 
 // ------------------------------------- interpolation on the matrix cores
-// For the problems of one prime the two triangular factors of the
-// interpolation are shared matrices, so the columns of all those problems
-// (and of the x and y problems alike) form one matrix product each:
-//   Newton coefficients  a_k = sum_{i <= k} T(k - i) y_i,   T(d) = (-1)^d / d!,
-//                        y_i = z_i / i!   (the forward differences of Sec. 4.1's
-//                        consecutive points, a Toeplitz factor),
-//   basis change         c_j = sum_{segments k0} sum_{i < kCkpt} s(k0, j - i) h_{k0,i}
-//                        (the checkpoint rows of the Stirling triangle and the
-//                        segments' polynomials h of stage_interp_hseg).
-// Both have a Toeplitz operand A[row][K] = v(row - K + const); the data
-// operand B holds the problems' columns as 7-bit digit planes (five digits of
-// each residue), and the 16x16x32 int8 products of the five digits of each
-// side accumulate the nine anti-diagonal sums S_s over the whole K range
-// (each below 5 (kMmMaxD + 32) 127^2 < 2^31), recombined as in the evaluation:
-//   out = sum_s S_s (2^{7s} mod p), below 9 * 2^29 p < p 2^32,
-// whose REDC is the coefficient in Montgomery form (the operands are
-// Montgomery representatives), written as the single chunk of aconv / cpart.
+// The staged and plain schedules.  Both triangular factors of the consecutive
+// points' interpolation act on one (problem, prime) column by sums of the form
+//   out_k = sum_i A(k - i) d_i,
+// A Toeplitz: the forward differences (A(x) = (-1)^x / x!, d = z_i / i!) and, per
+// checkpoint row k0 of the Stirling triangle, the segment's polynomial
+// (A = h_{k0}, d = s(k0, .)).  Written over blocks of 16, k = 16 a + b and
+// i = 16 u + v, with D = a - u,
+//   out[b][a] = sum_{D, v} A(16 D + b - v) d[16 (a - D) + v]:
+// a matrix product with 16 rows b, 16 block columns a and K = (D, v), whose left
+// operand does not depend on a.  So one column fills the 16 x 16 output tile of
+// the matrix cores by itself (the earlier form put the columns of 16 problems
+// side by side, and left 14 of 16 idle on a single system), the operand tiles
+// are built once per wave, and nothing has to be grouped by primes.  Both sides
+// split into four balanced base-256 digits (16 int8 16x16x64 products per K
+// slice of 64); the seven anti-diagonal sums stay below 4 * 3840 * 2^14 < 2^28
+// for the differences and 4 * 48 * 120 * 2^14 < 2^29 for the basis change.
+//
+// Each takes a tile of 256 outputs per item (problem, slot, tile), KS waves
+// splitting the K range (KS = 4 for jobs with few tiles).  Measured, both
+// products and the segment polynomials between them: 256 pairs of the batch
+// workload 497 -> 220 us (against 16-column tiles with five 7-bit digits), 64
+// requests of degrees 8..48 1170 -> 253, curve analysis 130 -> 35, the degree-24
+// pair 35 -> 17 us (against the vector-ALU sums).
+constexpr int kTile = 256;
+// Fewer tiles than one per SIMD: four waves share a tile's K range (curve
+// analysis, 756 tiles: 14.9 + 20.2 us against 25.3 + 38.3 with one wave each);
+// from there on one wave per tile, which forms the sums once (24 pairs of the
+// batch workload, about 1900 tiles: 28.0 + 36.2 us against 30.3 + 38.6; 256
+// pairs: 104.7 + 115.6 against 153.6 + 195.3).
+constexpr int kInterpSplitItems = 1024;
+constexpr int kConvFront = 18;  // zero blocks of 16 below index 0 of d (the tile's columns reach -288)
+constexpr int kSegWords = 21;   // 16-byte groups of one segment's reversed digits with their padding
+__host__ __device__ inline int interp_coeffs_lds_words(int D, int ks) {
+  const int kt = D / kTile * kTile;
+  const int w = 16 * (kt / 16 + 16 + kConvFront) + 16 * (4 * (D / 64 + 1) + 1);
+  const int red = ks > 1 ? 512 * ks : 768;  // the partial sums, then the segments' scratch
+  return w > red ? w : red;
+}
+__host__ __device__ inline int interp_basis_lds_words(int ks) { return 8 * kSegWords * 4 * ks; }
 
-// Digit planes of one problem slot: WHICH 1, y_n = z_n ifact_n; WHICH 2, hseg
-// (zero beyond D and, for the basis change, for a prime with bad points).
-// Each thread writes eight consecutive entries of every plane (one 64-bit
-// store per plane); item (problem, slot, block of 2048 entries).
-constexpr int kDigits = 5;
-constexpr int kDigitsPerBlock = 2048;
-template <int WHICH>
-__device__ inline void stage_interp_digits(const DevProblem& P, const DevTables& T, const WorkItem& w) {
-  const int n0 = 8 * (w.blk * blockDim.x + threadIdx.x);
-  const int Dp = P.hstride;
-  if (n0 >= Dp) return;
-  const int g = P.pidx[w.slot];
-  uint32_t v[8];
-  if constexpr (WHICH == 1) {
-    const PrimeConst pc = T.pc[g];
-    const uint32_t* z = P.zval + static_cast<size_t>(w.slot) * (P.E + 1);
-    const uint32_t* fi = T.ifact + static_cast<size_t>(g) * T.kstride;
+// digits of four consecutive values: out[d] = digit d of v0, v1, v2, v3
+__device__ __forceinline__ void digits4(int32_t v0, int32_t v1, int32_t v2, int32_t v3, uint32_t* out) {
+  byte_transpose4(balanced_digits(static_cast<uint32_t>(v0)), balanced_digits(static_cast<uint32_t>(v1)),
+                  balanced_digits(static_cast<uint32_t>(v2)), balanced_digits(static_cast<uint32_t>(v3)), out);
+}
+
+// Toeplitz operand of a K slice: bytes start .. start + 15 of each digit's
+// reversed run, stored as groups of 4 bytes of each digit (16 bytes per group).
+__device__ __forceinline__ void toeplitz_operand(const uint4* groups, int start, ev_v4i (&A)[kEvDigits]) {
+  const uint4* g = groups + (start >> 2);
+  const uint32_t sh = static_cast<uint32_t>(start) & 3u;
+  uint4 r[5];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (n0 + e <= P.D) ? mmul(z[n0 + e], fi[n0 + e], pc.p, pc.pinv) : 0u;
-  } else {
-    const bool fast = fast_prime(P, w.slot);
-    const uint32_t* h = P.hseg + static_cast<size_t>(w.slot) * P.hstride;
+  for (int j = 0; j < 5; ++j) r[j] = g[j];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (fast && n0 + e <= P.D) ? h[n0 + e] : 0u;
+  for (int j = 0; j < 4; ++j) {
+    A[0][j] = static_cast<int>(__builtin_amdgcn_alignbyte(r[j + 1].x, r[j].x, sh));
+    A[1][j] = static_cast<int>(__builtin_amdgcn_alignbyte(r[j + 1].y, r[j].y, sh));
+    A[2][j] = static_cast<int>(__builtin_amdgcn_alignbyte(r[j + 1].z, r[j].z, sh));
+    A[3][j] = static_cast<int>(__builtin_amdgcn_alignbyte(r[j + 1].w, r[j].w, sh));
   }
-  uint64_t* dst = reinterpret_cast<uint64_t*>((WHICH == 1 ? P.ydig : P.hdig) +
-                                              static_cast<size_t>(w.slot) * kDigits * Dp + n0);
+}
+
+__device__ __forceinline__ void digit_products(const ev_v4i (&A)[kEvDigits], const ev_v4i (&B)[kEvDigits],
+                                               ev_v4i (&S)[2 * kEvDigits - 1]) {
 #pragma unroll
-  for (int b = 0; b < kDigits; ++b) {
-    uint64_t word = 0;
+  for (int a = 0; a < kEvDigits; ++a)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) word |= static_cast<uint64_t>((v[e] >> (7 * b)) & 127u) << (8 * e);
-    dst[static_cast<size_t>(b) * (Dp / 8)] = word;
+    for (int b = 0; b < kEvDigits; ++b)
+      S[a + b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[a], B[b], S[a + b], 0, 0, 0);
+}
+
+// sum_s S_s 2^(8 s) of the lane's four outputs (rows 4 (l / 16) + r of column l
+// mod 16), with weights 2^(8 s) mod p, summed over the KS waves: wave 0 returns
+// true and the sums.
+template <int KS>
+__device__ __forceinline__ bool interp_sums(const ev_v4i (&S)[2 * kEvDigits - 1], const PrimeConst& pc,
+                                            const SignedMod& M, uint32_t* lds, int64_t (&t)[4]) {
+  int32_t w = 1;
+  const int32_t t256 = smul(256, static_cast<int32_t>(pc.r2), M);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) t[r] = 0;
+#pragma unroll
+  for (int s = 0; s < 2 * kEvDigits - 1; ++s) {
+    const int32_t wu = __builtin_amdgcn_readfirstlane(w);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[r] = smad(S[s][r], wu, t[r]);
+    w = scenter(smul(w, t256, M), M);
   }
+  if constexpr (KS > 1) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t* red = reinterpret_cast<int64_t*>(lds) + lane * 4;
+    __syncthreads();  // the operands in LDS are consumed
+    if (wave > 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave * 256 + r] = t[r];
+    }
+    __syncthreads();
+    if (wave > 0) return false;
+#pragma unroll
+    for (int v = 1; v < KS; ++v)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t[r] += red[v * 256 + r];
+  }
+  WaveSync()();
+  return true;
 }
 
-// Item (group, 64-row set rs, column tiles ct0 .. ct0 + nct - 1 of 16 members
-// each; members sorted by degree bound, largest first).  The block stages
-// once, in LDS, the Toeplitz operand of its 64 rows over every K slice its
-// tiles reach -- as 7-bit digit planes, reversed so that a lane's eight K
-// entries are eight consecutive bytes -- and the tiles' column descriptors.
-// Then wave w runs row tile rs0 + 16 w against each column tile in turn with
-// no further barrier: B fragments come from the members' digit planes in
-// global memory, the next slice's loads issued before the current slice's 25
-// products.  Lane l's fragments: row / column l mod 16, K entries 8 (l / 16)
-// .. + 7; its outputs are rows 4 (l / 16) .. + 3 of column l mod 16.
-constexpr int kMmTilesMax = 16;  // column tiles per item
-constexpr int kMmRunSlices = 48; // K slices per item (over its tiles), about
-constexpr int kMmMaxD = 2880;    // the basis change stages 640 bytes per slice: LDS below 64 KB
-struct MmCol {
-  const uint8_t* b;  // the member's digit planes (plane stride Dp bytes)
-  uint64_t* out;     // its sums: aconv or cpart of the slot
-  int D, Dp;         // degree bound (-1: no member), plane stride
-};
-constexpr int kMmColBytes = kMmTilesMax * 16 * static_cast<int>(sizeof(MmCol));
-
-// LDS bytes of the Toeplitz operand of an item: rows rs0 .. rs0 + 63, columns
-// of degree bound at most tileD.
-__host__ __device__ inline int mm_slices_lo(int which, int rs0) {
-  return which == 1 ? 0 : (rs0 >= 31 ? (rs0 - 31) / 32 : 0);
-}
-__host__ __device__ inline int mm_slices_hi(int which, int rs0, int tileD) {
-  return which == 1 ? ((rs0 + 63 < tileD) ? rs0 + 63 : tileD) / 32 : tileD / 32;
-}
-__host__ __device__ inline int mm_operand_bytes(int which, int rs0, int tileD) {
-  const int lo = mm_slices_lo(which, rs0), hi = mm_slices_hi(which, rs0, tileD);
-  return which == 1 ? kDigits * (32 * hi + 104) : kDigits * 128 * (hi - lo + 1);
-}
-
-template <int WHICH>
-__device__ inline void stage_interp_mm(const DevProblem* probs, const StirGroup& G, const StirMember* members,
-                                       const WorkItem& w, const DevTables& T, uint8_t* lds) {
+// Newton coefficients a_k = Delta^k z_0 / k! of a tile of 256 k's, and from them
+// the segments' polynomials of the basis change: rows k0 .. k0 + 31 after a
+// checkpoint row k0 contribute sum_t a_{k0+t} x^(k0+t) = x^(k0) H(x),
+//   H(x) = sum_t a_{k0+t} (x - k0)(x - k0 - 1) .. (x - k0 - t + 1),
+// and H's monomial coefficients h_0..h_31 go to hseg (signed, |h| <= p / 2).
+// Horner's rule in x over quads of factors: with the quartic of four factors,
+// h_i <- h_{i-4} + e1 h_{i-3} + e2 h_{i-2} + e3 h_{i-1} + e4 h_i + l_i, a lane
+// keeping four entries of one of the tile's eight segments; the quartics and
+// the low parts l are formed by one lane each beforehand.  Against one factor
+// per step with one entry per lane (32 shuffled steps, 629 instructions per 64
+// coefficients): about 600 per 256.
+template <int KS>
+__device__ inline void stage_interp_coeffs(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
+  if (!fast_prime(P, w.slot)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const PrimeConst pc = T.pc[G.g];
-  const uint32_t p = pc.p;
-  const int rs0 = 64 * w.slot;      // first row of the block
-  const int rw0 = rs0 + 16 * wave;  // first row of this wave's tile
-  const int ct0 = w.blk, nct = w.sub & 31, tileD0 = w.sub >> 5;  // tileD0: the first tile's largest bound
-  const int q = lane >> 4, r = lane & 15;
-  MmCol* cols = reinterpret_cast<MmCol*>(lds);
-  uint8_t* opnd = lds + kMmColBytes;
-  const int s_lo = mm_slices_lo(WHICH, rs0), s_hi = mm_slices_hi(WHICH, rs0, tileD0);
+  constexpr int NT = 64 * KS;
+  const int g = P.pidx[w.slot];
+  const PrimeConst pc = T.pc[g];
+  const SignedMod M = signed_mod(pc);
+  const uint32_t* ifact = T.ifact + static_cast<size_t>(g) * T.kstride;
+  const uint32_t* z = P.zval + static_cast<size_t>(w.slot) * (P.E + 1);
+  const int k0t = kTile * w.blk;
+  const int kend = (k0t + kTile - 1 < P.D) ? k0t + kTile - 1 : P.D;
+  const int nsl = kend / 64 + 1;         // K slices: D = 0 .. 4 nsl - 1
+  const int nu = k0t / 16 + 16 + kConvFront;
+  uint32_t* yw = lds;                    // [block of 16][digit][4 words]
+  uint4* tw = reinterpret_cast<uint4*>(lds + 16 * nu);  // [group of 4][digit]
+  for (int q = tid; q < 4 * nu; q += NT) {
+    const int i0 = 4 * q - 16 * kConvFront;
+    int32_t v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      v[e] = (i0 >= 0 && i0 + e <= kend)
+                 ? smul(static_cast<int32_t>(z[i0 + e]), static_cast<int32_t>(ifact[i0 + e]), M) : 0;
+    uint32_t o[kEvDigits];
+    digits4(v[0], v[1], v[2], v[3], o);
+#pragma unroll
+    for (int d = 0; d < kEvDigits; ++d) yw[(q >> 2) * 16 + 4 * d + (q & 3)] = o[d];
+  }
+  const int C = 16 * (4 * nsl - 1) + 15;
+  for (int q = tid; q < 4 * (4 * nsl + 1); q += NT) {
+    int32_t v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int x = C - (4 * q + e);
+      const int32_t f = (x >= 0 && x <= kend) ? static_cast<int32_t>(ifact[x]) : 0;
+      v[e] = (x & 1) ? -f : f;
+    }
+    uint32_t o[kEvDigits];
+    digits4(v[0], v[1], v[2], v[3], o);
+    tw[q] = make_uint4(o[0], o[1], o[2], o[3]);
+  }
+  if constexpr (KS > 1) __syncthreads();
+  else WaveSync()();
 
-  // column descriptors
-  for (int t = tid; t < 16 * nct; t += blockDim.x) {
-    const int mi = 16 * ct0 + t;
-    MmCol c{nullptr, nullptr, -1, 0};
-    if (mi < G.count) {
-      const StirMember M = members[G.first + mi];
-      const DevProblem& Pm = probs[M.prob];
-      c.D = Pm.D;
-      c.Dp = Pm.hstride;
-      c.b = (WHICH == 1 ? Pm.ydig : Pm.hdig) + static_cast<size_t>(M.slot) * kDigits * Pm.hstride;
-      c.out = (WHICH == 1 ? Pm.aconv : Pm.cpart) + static_cast<size_t>(M.slot) * (Pm.D + 1);
-    }
-    cols[t] = c;
-  }
-  // the Toeplitz operand: WHICH 1, one reversed vector R[y] = T(rs0 + 63 - y),
-  // T(x) = (-1)^x / x! for 0 <= x <= maxD; WHICH 2, per slice s a window
-  // W_s[y] = s(32 s, rs0 + 63 - y) for y < 128 (zero outside 0 .. 32 s)
-  if constexpr (WHICH == 1) {
-    const int Lr = 32 * s_hi + 104;
-    const uint32_t* ifact = T.ifact + static_cast<size_t>(G.g) * T.kstride;
-    for (int y = tid; y < Lr; y += blockDim.x) {
-      const int x = rs0 + 63 - y;
-      uint32_t v = 0u;
-      if (x >= 0 && x <= G.maxD) {
-        const uint32_t f = ifact[x];
-        v = (x & 1) ? p - f : f;
-      }
+  ev_v4i S[2 * kEvDigits - 1];
 #pragma unroll
-      for (int b = 0; b < kDigits; ++b) opnd[b * Lr + y] = static_cast<uint8_t>((v >> (7 * b)) & 127u);
-    }
-  } else {
-    const uint32_t* srow = T.stir + static_cast<size_t>(G.g) * T.sstride;
-    const int n = (s_hi - s_lo + 1) * 128;
-    for (int t = tid; t < n; t += blockDim.x) {
-      const int s = s_lo + (t >> 7), y = t & 127, x = rs0 + 63 - y;
-      const uint32_t v = (x >= 0 && x <= 32 * s) ? srow[ckpt_rowoff(s) + x] : 0u;
-      uint8_t* pl = opnd + (s - s_lo) * kDigits * 128 + y;
+  for (int s = 0; s < 2 * kEvDigits - 1; ++s) S[s] = ev_v4i{0, 0, 0, 0};
+  const int b = lane & 15, q4 = lane >> 4;  // row b (left operand), block column b (right operand), K quarter
+  for (int s = wave; s < nsl; s += KS) {
+    const int d = 4 * s + q4;
+    ev_v4i A[kEvDigits], B[kEvDigits];
+    const ev_v4i* src = reinterpret_cast<const ev_v4i*>(yw) + 4 * (k0t / 16 + b - d + kConvFront);
 #pragma unroll
-      for (int b = 0; b < kDigits; ++b) pl[b * 128] = static_cast<uint8_t>((v >> (7 * b)) & 127u);
-    }
+    for (int e = 0; e < kEvDigits; ++e) B[e] = src[e];
+    toeplitz_operand(tw, C - 16 * d - b, A);
+    digit_products(A, B, S);
   }
-  uint32_t wgt[2 * kDigits - 1];  // 2^(7 s) mod p
-  wgt[0] = 1u;
-#pragma unroll
-  for (int s = 1; s < 2 * kDigits - 1; ++s) {
-    const uint64_t t = static_cast<uint64_t>(wgt[s - 1]) << 7;
-    wgt[s] = static_cast<uint32_t>(t % p);
-  }
-  __syncthreads();
+  int64_t t[4];
+  if (!interp_sums<KS>(S, pc, M, lds, t)) return;
 
-  // lane's first byte of its A fragment in the operand (plus 32 s for WHICH 1)
-  const int y0 = 63 - 16 * wave - r + 8 * q;
-  const int sh = (y0 & 7) * 8;
-  const uint64_t* op64 = reinterpret_cast<const uint64_t*>(opnd);
-  const int Lr8 = (32 * s_hi + 104) / 8;  // WHICH 1 plane stride in words
-  for (int ct = 0; ct < nct; ++ct) {
-    const MmCol C = cols[16 * ct + r];
-    const int tileD = __builtin_amdgcn_readfirstlane(cols[16 * ct].D);  // the tile's largest degree bound
-    if (rw0 > tileD) break;             // wave-uniform; later tiles have smaller bounds
-    int sa, sb;
-    if constexpr (WHICH == 1) {
-      sa = 0;
-      sb = ((rw0 + 15 < tileD) ? rw0 + 15 : tileD) / 32;  // T(k - i) = 0 for i > k
-    } else {
-      sa = rw0 / 32;  // s(k0, j - i) = 0 for j - i > k0: slices with k0 + 31 >= rw0
-      sb = tileD / 32;
-    }
-    auto load_b = [&](int s, uint64_t (&Bf)[kDigits]) {
-      const bool have = 32 * s <= C.D;
-      const uint8_t* src = C.b + 32 * s + 8 * q;
+  int4* av = reinterpret_cast<int4*>(lds);        // the tile's a_k
+  int4* lowp = reinterpret_cast<int4*>(lds) + 64; // [segment][quad] low parts
+  int4* quart = lowp + 64;                        // [segment][quad] quartics
+  {
+    int32_t a[4];
 #pragma unroll
-      for (int b = 0; b < kDigits; ++b)
-        Bf[b] = have ? *reinterpret_cast<const uint64_t*>(src + static_cast<size_t>(b) * C.Dp) : 0u;
-    };
-    ev_v4i S[2 * kDigits - 1];
+    for (int r = 0; r < 4; ++r) a[r] = (k0t + 16 * b + 4 * q4 + r <= P.D) ? sredc(t[r], M) : 0;
+    WaveSync()();
+    av[4 * b + q4] = make_int4(a[0], a[1], a[2], a[3]);
+  }
+  WaveSync()();
+  const int e = lane & 7;  // segment lane / 8; quad (rows k0 + 4 e ..) and entries 4 e .. 4 e + 3
+  {
+    const int64_t c0 = k0t + 4 * lane, c1 = c0 + 1, c2 = c0 + 2, c3 = c0 + 3;
+    // x R mod p, centred, for |x| < 2^50
+    auto mont = [&](int64_t x) { return scenter(smul(sredc(x, M), static_cast<int32_t>(pc.r3), M), M); };
+    const int64_t s2 = c0 + c1, p2 = c0 * c1, s3 = s2 + c2, q3 = p2 + s2 * c2, p3 = p2 * c2;
+    const int4 a = av[lane];
+    const int32_t p3m = mont(p3), q3m = mont(q3), s3m = mont(s3);
+    int4 l;
+    l.x = scenter(a.x + sredc(smad(-mont(c0), a.y, smad(mont(p2), a.z, smad(-p3m, a.w, 0))), M), M);
+    l.y = scenter(a.y + sredc(smad(-mont(s2), a.z, smad(q3m, a.w, 0)), M), M);
+    l.z = scenter(a.z + sredc(smad(-s3m, a.w, 0), M), M);
+    l.w = scenter(a.w, M);
+    lowp[lane] = l;
+    quart[lane] = make_int4(mont(-(s3 + c3)), mont(q3 + s3 * c3), mont(-(p3 + q3 * c3)), mont(p3 * c3));
+  }
+  WaveSync()();
+  int32_t h0 = 0, h1 = 0, h2 = 0, h3 = 0;
+  auto from_left = [](int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr:1 */, 0xF, 0xF, true); };
 #pragma unroll
-    for (int s = 0; s < 2 * kDigits - 1; ++s) S[s] = ev_v4i{0, 0, 0, 0};
-    uint64_t Bn[kDigits];
-    load_b(sa, Bn);
-    for (int s = sa; s <= sb; ++s) {
-      uint64_t B[kDigits];
+  for (int Q = 7; Q >= 0; --Q) {
+    const int4 l = lowp[(lane & 56) + Q], c = quart[(lane & 56) + Q];
+    const int32_t q0 = from_left(h0), q1 = from_left(h1), q2 = from_left(h2), q3 = from_left(h3);
+    const bool first = e == 0;
+    const int32_t z1 = first ? 0 : q1, z2 = first ? 0 : q2, z3 = first ? 0 : q3;
+    const int32_t n0 = sredc(smad(c.x, z1, smad(c.y, z2, smad(c.z, z3, smad(c.w, h0, 0)))), M) + (first ? l.x : q0);
+    const int32_t n1 = sredc(smad(c.x, z2, smad(c.y, z3, smad(c.z, h0, smad(c.w, h1, 0)))), M) + (first ? l.y : q1);
+    const int32_t n2 = sredc(smad(c.x, z3, smad(c.y, h0, smad(c.z, h1, smad(c.w, h2, 0)))), M) + (first ? l.z : q2);
+    const int32_t n3 = sredc(smad(c.x, h0, smad(c.y, h1, smad(c.z, h2, smad(c.w, h3, 0)))), M) + (first ? l.w : q3);
+    h0 = scenter(n0, M);  // |n| <= (4 / 4 / 3 + 1 / 2 + 1 / 2) p < 1.5 p
+    h1 = scenter(n1, M);
+    h2 = scenter(n2, M);
+    h3 = scenter(n3, M);
+  }
+  const int at = k0t + 4 * lane;
+  if (at < P.hstride)
+    *reinterpret_cast<int4*>(P.hseg + static_cast<size_t>(w.slot) * P.hstride + at) = make_int4(h0, h1, h2, h3);
+}
+
+// Falling factorials -> monomials, a tile of 256 coefficients:
+//   c_j = sum_{k0} sum_{i < 32} h_{k0,i} s(k0, j - i)
+// over the checkpoint rows k0 >= the tile's first j.  The segments' operands are
+// built in LDS eight at a time; the row's digits are split in registers from
+// the 16 words a lane loads one segment ahead.  Written as c_j 2^32, the only
+// word the CRT reads for j.  Bound by the digit splitting of the rows (about 90
+// VALU instructions against 16 products per segment).
+alignas(16) __device__ const uint32_t kZeroRow[16] = {};
+template <int KS>
+__device__ inline void stage_interp_basis(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
+  if (!fast_prime(P, w.slot)) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = P.pidx[w.slot];
+  const PrimeConst pc = T.pc[g];
+  const SignedMod M = signed_mod(pc);
+  const uint32_t* stir = T.stir + static_cast<size_t>(g) * T.sstride;
+  const uint32_t* hrow = P.hseg + static_cast<size_t>(w.slot) * P.hstride;
+  const int j0 = kTile * w.blk, D = P.D;
+  uint4* seg = reinterpret_cast<uint4*>(lds) + wave * 8 * kSegWords;  // this wave's eight segments
+  for (int t = lane; t < 8 * kSegWords; t += 64) seg[t] = make_uint4(0u, 0u, 0u, 0u);
+  ev_v4i S[2 * kEvDigits - 1];
 #pragma unroll
-      for (int b = 0; b < kDigits; ++b) B[b] = Bn[b];
-      if (s < sb) load_b(s + 1, Bn);
-      uint64_t A[kDigits];
+  for (int s = 0; s < 2 * kEvDigits - 1; ++s) S[s] = ev_v4i{0, 0, 0, 0};
+  const int b = lane & 15, q4 = lane >> 4;
+  const int J = j0 + 16 * (b - q4);  // first index of the lane's 16 row entries
+  typedef const __attribute__((address_space(1))) ev_v4u* gptr;
+  // the 16 row entries of segment s (k0 = 32 s): zero outside 0 .. k0
+  auto load_row = [&](int s, ev_v4u (&r)[4]) {
+    const uint32_t* src = (J >= 0 && J <= 32 * s) ? stir + ckpt_rowoff(s) + J : kZeroRow;
+    const gptr p4 = (gptr)(src);
 #pragma unroll
-      for (int b = 0; b < kDigits; ++b) {
-        int wi;
-        if constexpr (WHICH == 1) wi = b * Lr8 + ((y0 + 32 * s) >> 3);
-        else wi = ((s - s_lo) * kDigits + b) * 16 + (y0 >> 3);
-        const uint64_t lo = op64[wi], hi = op64[wi + 1];
-        A[b] = sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
+    for (int u = 0; u < 4; ++u) r[u] = p4[u];
+  };
+  const int sfirst = j0 / 32, slast = D / 32;
+  for (int s0 = sfirst + 8 * wave; s0 <= slast; s0 += 8 * KS) {
+    WaveSync()();  // the previous segments' operands are consumed
+    const int x = 32 * s0 + 4 * lane;  // entries 4 (lane mod 8) .. + 3 of segment s0 + lane / 8
+    int4 h = make_int4(0, 0, 0, 0);
+    if (x < P.hstride) h = *reinterpret_cast<const int4*>(hrow + x);
+    ev_v4u nx[4];
+    load_row(s0, nx);
+    uint32_t o[kEvDigits];
+    digits4(h.w, h.z, h.y, h.x, o);
+    seg[(lane >> 3) * kSegWords + 15 - (lane & 7)] = make_uint4(o[0], o[1], o[2], o[3]);
+    WaveSync()();
+    const int ns = slast - s0 + 1 < 8 ? slast - s0 + 1 : 8;
+    for (int u = 0; u < ns; ++u) {
+      ev_v4u r[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) r[v] = nx[v];
+      if (u + 1 < ns) load_row(s0 + u + 1, nx);
+      const int k0 = 32 * (s0 + u);
+      if (k0 < j0 + kTile && J == k0) {  // the row ends at its entry k0: words beyond it are not part of the table
+        r[0].y = r[0].z = r[0].w = 0u;
+#pragma unroll
+        for (int v = 1; v < 4; ++v) r[v].x = r[v].y = r[v].z = r[v].w = 0u;
       }
+      ev_v4i A[kEvDigits], B[kEvDigits];
 #pragma unroll
-      for (int a = 0; a < kDigits; ++a)
+      for (int v = 0; v < 4; ++v) {
+        uint32_t dg[kEvDigits];
+        digits4(static_cast<int32_t>(r[v].x), static_cast<int32_t>(r[v].y), static_cast<int32_t>(r[v].z),
+                static_cast<int32_t>(r[v].w), dg);
 #pragma unroll
-        for (int b = 0; b < kDigits; ++b)
-          S[a + b] = __builtin_amdgcn_mfma_i32_16x16x32_i8(static_cast<long>(A[a]), static_cast<long>(B[b]),
-                                                           S[a + b], 0, 0, 0);
+        for (int d = 0; d < kEvDigits; ++d) B[d][v] = static_cast<int>(dg[d]);
+      }
+      toeplitz_operand(seg + u * kSegWords, 63 - 16 * q4 - b, A);
+      digit_products(A, B, S);
     }
-    if (rw0 > C.D) continue;
+  }
+  int64_t t[4];
+  if (!interp_sums<KS>(S, pc, M, lds, t)) return;
+  uint64_t* cp = P.cpart + static_cast<size_t>(w.slot) * (D + 1);
 #pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      const int row = rw0 + 4 * q + r4;
-      uint64_t t = 0;
-#pragma unroll
-      for (int s = 0; s < 2 * kDigits - 1; ++s) t += static_cast<uint64_t>(static_cast<uint32_t>(S[s][r4])) * wgt[s];
-      if (row <= C.D) C.out[row] = t;
-    }
+  for (int r = 0; r < 4; ++r) {
+    const int j = j0 + 16 * b + 4 * q4 + r;
+    if (j <= D) cp[j] = static_cast<uint64_t>(scanon(sredc(t[r], M), M)) << 32;
   }
 }
 
-// LDS words of a basis-change block: members' h, the row window, and (when h
-// is expanded in the block) the chunk's a_k.
-__host__ __device__ inline int basis_lds_words(int members, int nthreads, int K_or_0) {
-  return kCkpt * members + nthreads + kCkpt - 1 + K_or_0;
-}
+// LDS words of a basis-change block of the persistent schedule: a segment's h,
+// the row window and the chunk's a_k.
+__host__ __device__ inline int basis_lds_words(int nthreads, int K) { return kCkpt + nthreads + kCkpt - 1 + K; }
 
-// One problem: item (problem, slot, block of blockDim columns, chunk).  With
-// h_global the segments' h come from hseg (staged and plain schedules, after
-// stage_interp_hseg); otherwise the block expands them itself (the persistent
-// schedule's single-wave tasks).
-template <bool h_global>
+// The persistent schedule's basis change: (problem, slot, block of blockDim
+// columns, chunk).
 __device__ inline void stage_interp_stir(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
   if (!fast_prime(P, w.slot)) return;
   const int g = P.pidx[w.slot];
@@ -1676,86 +1733,30 @@ __device__ inline void stage_interp_stir(const DevProblem& P, const DevTables& T
   uint32_t* lh = lds;
   uint32_t* lw = lds + kCkpt;
   uint32_t* la = lw + nt + kCkpt - 1;
-  if constexpr (!h_global) {
-    load_newton_coeffs(P, w.slot, pc, kb, ke, la);
-    __syncthreads();
-  }
+  load_newton_coeffs(P, w.slot, pc, kb, ke, la);
+  __syncthreads();
   if (j0 > ke || j0 > P.D) return;  // block-uniform: no row of the chunk reaches these columns
   // rows below j0 contribute nothing to them: start at j0's checkpoint
   const int jc = (j0 / kCkpt) * kCkpt;
   const int k1 = kb > jc ? kb : jc;
-  uint64_t acc[1] = {0u};
-  const uint32_t* hrow = P.hseg + static_cast<size_t>(w.slot) * P.hstride;
-  const int hmax[1] = {P.D};
-  basis_block<1, h_global>(T.stir + static_cast<int64_t>(g) * T.sstride, j0, k1, ke, kb, 1, &hrow, hmax, la, pc, lh,
-                           lw, acc);
+  const uint64_t acc = basis_block(T.stir + static_cast<int64_t>(g) * T.sstride, j0, k1, ke, kb, la, pc, lh, lw);
   const int j = j0 + static_cast<int>(threadIdx.x);
-  if (j <= P.D) P.cpart[(static_cast<size_t>(w.sub) * P.np + w.slot) * (P.D + 1) + j] = acc[0];
-}
-
-// The same basis change for every member of a prime group (problems that use
-// one prime): each checkpoint row is read once and convolved into every
-// member's partial sums.  Item: (group, -, block of blockDim columns, k-chunk);
-// all members share the chunk length (kchunk) and their rows k > D_m have h = 0.
-__host__ __device__ inline int stir_group_lds_words(int count, int nthreads) {
-  return basis_lds_words(count, nthreads, 0);
-}
-
-__device__ inline void stage_interp_stir_group(const DevProblem* probs, const StirGroup* groups,
-                                               const StirMember* members, const DevTables& T, const WorkItem& w,
-                                               uint32_t* lds) {
-  const StirGroup G = groups[w.prob];
-  const int nt = blockDim.x;
-  const int j0 = w.blk * nt;
-  const PrimeConst pc = T.pc[G.g];
-  const int K = probs[members[G.first].prob].kchunk;
-  const int kb = w.sub * K;
-  const int ke = (kb + K - 1 < G.maxD) ? kb + K - 1 : G.maxD;
-  if (j0 > ke) return;
-  // the active members (degree bound reaching the chunk and the block,
-  // consecutive points), compacted
-  int na = 0, which[kStirGroupMax];
-  for (int m = 0; m < G.count; ++m) {
-    const StirMember M = members[G.first + m];
-    const DevProblem& P = probs[M.prob];
-    if (P.D >= kb && P.D >= j0 && fast_prime(P, M.slot)) which[na++] = m;
-  }
-  if (na == 0) return;  // block-uniform
-  const uint32_t* hsrc[kStirGroupMax];
-  int hmax[kStirGroupMax];
-#pragma unroll
-  for (int q = 0; q < kStirGroupMax; ++q) {
-    hsrc[q] = nullptr;
-    hmax[q] = -1;
-    if (q < na) {
-      const StirMember M = members[G.first + which[q]];
-      hsrc[q] = probs[M.prob].hseg + static_cast<size_t>(M.slot) * probs[M.prob].hstride;
-      hmax[q] = probs[M.prob].D;
-    }
-  }
-  const int jc = (j0 / kCkpt) * kCkpt;
-  const int k1 = kb > jc ? kb : jc;
-  uint64_t acc[kStirGroupMax];
-#pragma unroll
-  for (int m = 0; m < kStirGroupMax; ++m) acc[m] = 0u;
-  // rows k > D_m of a member are zero in its h (its a_k vanish there), and the
-  // h of a member is read only for segments at or below its degree bound
-  basis_block<kStirGroupMax, true>(T.stir + static_cast<int64_t>(G.g) * T.sstride, j0, k1, ke, kb, na, hsrc, hmax,
-                                   nullptr, pc, lds, lds + kCkpt * kStirGroupMax, acc);
-#pragma unroll
-  for (int q = 0; q < kStirGroupMax; ++q)
-    if (q < na) {
-      const StirMember M = members[G.first + which[q]];
-      const DevProblem& P = probs[M.prob];
-      const int j = j0 + static_cast<int>(threadIdx.x);
-      if (j <= P.D) P.cpart[(static_cast<size_t>(w.sub) * P.np + M.slot) * (P.D + 1) + j] = acc[q];
-    }
+  if (j <= P.D) P.cpart[(static_cast<size_t>(w.sub) * P.np + w.slot) * (P.D + 1) + j] = acc;
 }
 
 // LDS words of the gapped-interpolation block.
 __host__ __device__ inline int newton_lds_words(const DevProblem& P, int nthreads) {
   const int e1 = P.E + 1;
   return 3 * e1 + (e1 > nthreads ? e1 : nthreads);
+}
+
+// The partial-sum chunks of a run: the problem's layout in the persistent
+// schedule, one whole chunk in the staged and plain ones.
+struct Chunks {
+  int n, len;
+};
+__device__ inline Chunks chunks_of(const DevProblem& P, bool whole) {
+  return whole ? Chunks{1, P.D + 1} : Chunks{P.nchunk, P.kchunk};
 }
 
 // Consecutive points from a shifted origin o: the fast path left the
@@ -1765,7 +1766,7 @@ __host__ __device__ inline int newton_lds_words(const DevProblem& P, int nthread
 // v_d = (-o)^d / d! (a Taylor shift), one thread per j.  Written as the
 // Newton stage writes its result: c_j 2^32 in the first chunk the CRT reads
 // for j, zero in the later ones.  LDS: 2 (D+1) words.
-__device__ inline void shift_origin(const DevProblem& P, const DevTables& T, int slot, uint32_t* lds) {
+__device__ inline void shift_origin(const DevProblem& P, const DevTables& T, int slot, uint32_t* lds, Chunks ck) {
   const int tid = threadIdx.x, nt = blockDim.x, D = P.D;
   const int g = P.pidx[slot];
   const PrimeConst pc = T.pc[g];
@@ -1779,7 +1780,7 @@ __device__ inline void shift_origin(const DevProblem& P, const DevTables& T, int
   const uint32_t mo = mmul(p - static_cast<uint32_t>(P.origin), pc.r2, p, pinv);  // -o R (o < 2^24 < p)
   for (int k = tid; k <= D; k += nt) {
     uint64_t cs = 0;
-    for (int ch = k / P.kchunk; ch < P.nchunk; ++ch) cs = add_fold(cs, cp[ch * cstride + k], p);
+    for (int ch = k / ck.len; ch < ck.n; ++ch) cs = add_fold(cs, cp[ch * cstride + k], p);
     u[k] = mmul(redc(cs, p, pinv), fact[k], p, pinv);  // k! ct_k
     uint32_t pw = pc.r1, base = mo;                     // (-o)^k R by squaring
     for (int e = k; e; e >>= 1) {
@@ -1793,9 +1794,9 @@ __device__ inline void shift_origin(const DevProblem& P, const DevTables& T, int
     uint64_t acc = 0;
     for (int d = 0; d <= D - j; ++d) acc = mac_fold(acc, u[j + d], v[d], p);
     const uint32_t c = mmul(redc(acc, p, pinv), ifact[j], p, pinv);
-    const int ch0 = j / P.kchunk;
+    const int ch0 = j / ck.len;
     cp[ch0 * cstride + j] = static_cast<uint64_t>(c) << 32;
-    for (int ch = ch0 + 1; ch < P.nchunk; ++ch) cp[ch * cstride + j] = 0;
+    for (int ch = ch0 + 1; ch < ck.n; ++ch) cp[ch * cstride + j] = 0;
   }
 }
 
@@ -1803,13 +1804,15 @@ __device__ inline void shift_origin(const DevProblem& P, const DevTables& T, int
 // first D+1 usable points, Newton divided differences, then the Newton form
 // expanded in the monomial basis by Horner.  Slots that took the consecutive
 // path need only the shift back from a nonzero origin.
-__device__ inline void stage_interp_newton(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
+__device__ inline void stage_interp_newton(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds,
+                                           bool whole) {
+  const Chunks ck = chunks_of(P, whole);
   const int tid = threadIdx.x, nt = blockDim.x;
   const int slot = w.slot;
   const bool fast = fast_prime(P, slot);
   if (tid == 0) P.status[1 + slot] = fast ? 0 : 1;
   if (fast) {
-    if (P.origin != 0) shift_origin(P, T, slot, lds);
+    if (P.origin != 0) shift_origin(P, T, slot, lds, ck);
     return;
   }
   const int g = P.pidx[slot];
@@ -1898,9 +1901,9 @@ __device__ inline void stage_interp_newton(const DevProblem& P, const DevTables&
   // the first chunk the CRT reads for coefficient j carries c_j 2^32 (REDC gives
   // c_j); the later chunks are zero
   for (int j = tid; j <= D; j += nt) {
-    const int ch0 = j / P.kchunk;
+    const int ch0 = j / ck.len;
     P.cpart[(static_cast<size_t>(ch0) * P.np + slot) * (D + 1) + j] = static_cast<uint64_t>(pa[j]) << 32;
-    for (int ch = ch0 + 1; ch < P.nchunk; ++ch)
+    for (int ch = ch0 + 1; ch < ck.n; ++ch)
       P.cpart[(static_cast<size_t>(ch) * P.np + slot) * (D + 1) + j] = 0;
   }
 }
@@ -2168,6 +2171,26 @@ __device__ inline void crt_one(const DevProblem& P, int k_raw, const uint32_t* m
   crt_radix<NS>(P, k, valid, vbuf, P.Plimb, P.LP, init, sb, sc);
 }
 
+// Coefficient k modulo a prime (cpp: its first chunk's entry).  Whole runs hold
+// c_k 2^32, read as its high word.
+__device__ __forceinline__ uint32_t coeff_of(const DevProblem& P, const uint64_t* cpp, size_t cstride, int k,
+                                             uint32_t p, uint32_t pinv, bool whole) {
+  if (whole) return reinterpret_cast<const uint32_t*>(cpp)[1];
+  const int ch0 = k / P.kchunk;
+  uint64_t q[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int ch = ch0 + u < P.nchunk ? ch0 + u : P.nchunk - 1;
+    q[u] = cpp[ch * cstride];
+  }
+  uint64_t cs = 0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (ch0 + u < P.nchunk) cs = add_fold(cs, q[u], p);
+  for (int ch = ch0 + 8; ch < P.nchunk; ++ch) cs = add_fold(cs, cpp[ch * cstride], p);
+  return redc(cs, p, pinv);
+}
+
 // One item: kCrtBlockCoeffs coefficients, `cpw` per wave,
 // k = (blk * waves + wave) * cpw + c (waves * cpw = kCrtBlockCoeffs).  With
 // `fresh` the per-prime constants and (when it fits) the M / p_j limb table
@@ -2179,7 +2202,7 @@ __device__ inline void crt_one(const DevProblem& P, int k_raw, const uint32_t* m
 constexpr int kCrtItemsPerBlock = 4;  // items per block of the staged launch
 template <int NS>
 __device__ inline void stage_crt(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds,
-                                 int cpw = 1, bool fresh = true) {
+                                 int cpw, bool fresh, bool whole) {
   const int nw = blockDim.x >> 6;
   const int wave = threadIdx.x >> 6;
   const int np = P.np;
@@ -2202,21 +2225,8 @@ __device__ inline void stage_crt(const DevProblem& P, const DevTables& T, const 
       const int i = t / kCrtBlockCoeffs, c = t - i * kCrtBlockCoeffs;
       const int k = (kbase + c <= P.D) ? kbase + c : P.D;
       const uint64_t* cpp = P.cpart + static_cast<size_t>(i) * (P.D + 1) + k;
-      const int ch0 = k / P.kchunk;
-      uint64_t q[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int ch = ch0 + u < P.nchunk ? ch0 + u : P.nchunk - 1;
-        q[u] = cpp[ch * cstride];
-      }
       const PrimeConst pc = T.pc[P.pidx[i]];
-      const uint32_t hm = P.Hm[i];
-      uint64_t cs = 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (ch0 + u < P.nchunk) cs = add_fold(cs, q[u], pc.p);
-      for (int ch = ch0 + 8; ch < P.nchunk; ++ch) cs = add_fold(cs, cpp[ch * cstride], pc.p);
-      ures[c * np + i] = maddm(redc(cs, pc.p, pc.pinv), hm, pc.p);
+      ures[c * np + i] = maddm(coeff_of(P, cpp, cstride, k, pc.p, pc.pinv, whole), P.Hm[i], pc.p);
       if (c == 0 && fresh) {
         pconst[i] = pc.p;
         pconst[np + i] = pc.pinv;
@@ -2277,7 +2287,8 @@ __device__ inline uint32_t wave_carry_in(bool gen, bool prop, uint64_t* cin) {
 
 // Pass 1: block item blk covers coefficients blk*8 .. blk*8+7; thread owns
 // coefficient c = tid mod 8 and primes tid/8 + 32 r.
-__device__ inline void stage_crt_wide_t(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
+__device__ inline void stage_crt_wide_t(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds,
+                                        bool whole) {
   const int c = threadIdx.x & (kWideTCoeffs - 1);
   const int k_raw = w.blk * kWideTCoeffs + c;
   const bool valid = k_raw <= P.D;
@@ -2288,9 +2299,7 @@ __device__ inline void stage_crt_wide_t(const DevProblem& P, const DevTables& T,
   for (int i = threadIdx.x / kWideTCoeffs; i < np; i += blockDim.x / kWideTCoeffs) {
     const uint64_t* cpp = P.cpart + static_cast<size_t>(i) * (P.D + 1) + k;
     const PrimeConst pc = T.pc[P.pidx[i]];
-    uint64_t cs = 0;
-    for (int ch = 0; ch < P.nchunk; ++ch) cs = add_fold(cs, cpp[ch * cstride], pc.p);
-    const uint32_t u = maddm(redc(cs, pc.p, pc.pinv), P.Hm[i], pc.p);  // c_k + H mod p
+    const uint32_t u = maddm(coeff_of(P, cpp, cstride, k, pc.p, pc.pinv, whole), P.Hm[i], pc.p);  // c_k + H mod p
     const uint32_t t = mmul(u, P.wdir[i], pc.p, pc.pinv);
     if (valid) P.wT[static_cast<size_t>(k) * P.wnpad + i] = t;
     const uint64_t f = static_cast<uint64_t>(t) * P.rinv[2 * i + 1] + __umulhi(t, P.rinv[2 * i]);

@@ -150,12 +150,8 @@ static unsigned empty_stages(const Job& J) {
   unsigned m = 0u;
   if (J.items[kStageReduce].empty()) m |= 1u << kStageReduce;
   if (J.eval_ranges.empty()) m |= 1u << kStageEval;
-  if (J.mm_interp) {
-    if (J.dig_items.empty() && J.mm_items.empty()) m |= (1u << kStageConv) | (1u << kStageStir);
-  } else {
-    if (J.items[kStageConv].empty()) m |= 1u << kStageConv;
-    if (J.items[kStageStir].empty() && J.sg_items.empty() && J.hseg_items.empty()) m |= 1u << kStageStir;
-  }
+  if (J.items[kStageConv].empty()) m |= 1u << kStageConv;
+  if (J.items[kStageStir].empty()) m |= 1u << kStageStir;
   if (J.items[kStageNewton].empty()) m |= 1u << kStageNewton;
   if (J.items[kStageCrt].empty() && J.wide_items[0].empty() && J.wide_items[1].empty() && J.wide_items[2].empty())
     m |= 1u << kStageCrt;
@@ -391,11 +387,13 @@ int rsl_job_tune(rsl_ctx* ctx, rsl_job* j, int reps, rsl_tune_result* best) {
   for (size_t ci = 0;; ++ci) {
     if (ci == phase1) {  // phase two around the winner of phase one
       if (!any) return fail(ctx, RSL_ENOMEM, "no schedule's layout fits the job's bound device memory");
-      for (int target : {1024, 16384}) add(TuneConfig{win.mode, target, 1, win.evk, 0, win.schur});
-      add(TuneConfig{win.mode, 4096, 1, win.evk, 1, win.schur});
-      if (win.mode == RSL_BATCHED) add(TuneConfig{RSL_BATCHED, 4096, 2, win.evk, 0, 0});
-      // the interpolation on the matrix cores (staged schedule)
-      if (win.mode == RSL_STAGED) add(TuneConfig{RSL_STAGED, 4096, 1, win.evk, 1, win.schur, 1});
+      // (the partial-sum chunks are the persistent schedule's; the staged one
+      // takes its sums whole)
+      if (win.mode == RSL_BATCHED) {
+        for (int target : {1024, 16384}) add(TuneConfig{RSL_BATCHED, target, 1, win.evk, 0, 0});
+        add(TuneConfig{RSL_BATCHED, 4096, 1, win.evk, 1, 0});
+        add(TuneConfig{RSL_BATCHED, 4096, 2, win.evk, 0, 0});
+      }
     }
     if (ci >= cands.size()) break;
     const TuneConfig tc = cands[ci];

@@ -76,6 +76,7 @@ struct DevProblem {
   const uint32_t* invM;   // [i]            (prod_{l<i} p_l)^{-1} R mod p_i
   const uint32_t* Plimb;  // [j * LP + t]   limbs of prod_{l<j} p_l
   const uint32_t* Mi;     // [j * Lw + t]   limbs of M / p_j (direct CRT)
+  const uint8_t* Mdig;    // balanced digits of the M / p_j limbs in matrix-core operand order (CrtConst::dig)
   const uint32_t* wdir;   // [i]            (M / p_i)^{-1} R mod p_i
   const uint32_t* rinv;   // [2 i], [2 i + 1] low, high word of floor(2^64 / p_i)
   const uint32_t* negM;   // Lw: 2^(32 Lw) - M

@@ -170,6 +170,7 @@ struct CrtDev {
   int* pidx = nullptr;
   uint32_t *Hm = nullptr, *NH = nullptr, *Mi = nullptr, *wdir = nullptr, *rinv = nullptr, *negM = nullptr;
   uint32_t *Mw = nullptr, *NHM = nullptr, *Tg = nullptr, *invM = nullptr, *Plimb = nullptr;
+  uint8_t* Mdig = nullptr;
 };
 
 template <class T>
@@ -188,7 +189,7 @@ int crt_setup(rsl_ctx* ctx, Dev* D, const std::vector<int>& pidx, CrtDev* C) {
   int rc;
   if ((rc = upload_vec(ctx, D, P.pidx, &C->pidx)) || (rc = upload_vec(ctx, D, P.crt->Hm, &C->Hm)) ||
       (rc = upload_vec(ctx, D, P.crt->NH, &C->NH)) || (rc = upload_vec(ctx, D, P.crt->Mi, &C->Mi)) ||
-      (rc = upload_vec(ctx, D, P.crt->wdir, &C->wdir)) || (rc = upload_vec(ctx, D, P.crt->rinv, &C->rinv)) ||
+      (rc = upload_vec(ctx, D, P.crt->dig, &C->Mdig)) || (rc = upload_vec(ctx, D, P.crt->wdir, &C->wdir)) || (rc = upload_vec(ctx, D, P.crt->rinv, &C->rinv)) ||
       (rc = upload_vec(ctx, D, P.crt->negM, &C->negM)))
     return rc;
   if (P.wide && ((rc = upload_vec(ctx, D, P.crt->Mw, &C->Mw)) || (rc = upload_vec(ctx, D, P.crt->NHM, &C->NHM)))) return rc;
@@ -217,6 +218,7 @@ DevProblem crt_problem(const rsl_ctx* ctx, Dev* D, const CrtDev& C, int Dg, uint
   d.Hm = C.Hm;
   d.NH = C.NH;
   d.Mi = C.Mi;
+  d.Mdig = C.Mdig;
   d.wdir = C.wdir;
   d.rinv = C.rinv;
   d.negM = C.negM;
@@ -257,16 +259,19 @@ int run_crt(rsl_ctx* ctx, Dev* D, const std::vector<DevProblem>& probs) {
   if (!wide) {
     int ns = (np + 63) / 64;
     if (ns == 5 || ns == 7) ++ns;
+    const bool mm = !ctx->crt_garner;
     std::vector<WorkItem> items;
     size_t lds = 0;
     for (size_t q = 0; q < probs.size(); ++q) {
-      for (int b = 0; b < blocks_of(probs[q].D + 1, kCrtWaves); ++b) items.push_back({static_cast<int>(q), -1, b, 0});
-      lds = std::max(lds, static_cast<size_t>(crt_lds_words(probs[q], ns, crt_block_waves(ns))) * 4);
+      for (int b = 0; b < blocks_of(probs[q].D + 1, mm ? kCrtMmRows : kCrtWaves); ++b)
+        items.push_back({static_cast<int>(q), -1, b, 0});
+      lds = std::max(lds, static_cast<size_t>(mm ? 0 : crt_lds_words(probs[q], ns, crt_block_waves(ns))) * 4);
     }
     WorkItem* ditems = nullptr;
     if ((rc = upload_vec(ctx, D, items, &ditems)) || (rc = flush(ctx, D))) return rc;
-    return hip_check(ctx, launch_stage(kStageCrt, dprobs, ditems, static_cast<int>(items.size()), lds, ns, T, ctx->stream, 1,
-                                       false),
+    const int n = static_cast<int>(items.size());
+    return hip_check(ctx, mm ? launch_crt_mm(dprobs, ditems, n, np, T, ctx->stream, false)
+                             : launch_stage(kStageCrt, dprobs, ditems, n, lds, ns, T, ctx->stream, 1, false),
                      "gcd CRT");
   }
   std::vector<WorkItem> items[3];

@@ -202,6 +202,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
   }
   J->crt_ns = 1;
   J->max_np = 0;
+  J->slot_np = 0;
   J->any_schur = false;
   const bool schur_req = (opts && opts->eval_schur > 0) || J->tune.schur != 0;
   const bool newton_req = opts && opts->interp_newton > 0;
@@ -269,7 +270,10 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     // the convolution's input range: the basis change's chunking, or whole
     d.cchunk = (J->tune.conv_whole || whole_req) ? P.D + 1 : d.kchunk;
     d.ncchunk = (P.D + 1 + d.cchunk - 1) / d.cchunk;
-    if (!P.wide) J->crt_ns = std::max(J->crt_ns, (P.np + 63) / 64);
+    if (!P.wide) {
+      J->crt_ns = std::max(J->crt_ns, (P.np + 63) / 64);
+      J->slot_np = std::max(J->slot_np, P.np);
+    }
     J->max_np = std::max(J->max_np, P.np);
     J->pairs += static_cast<int64_t>(P.np) * (P.E + 1);
     J->mulmods += pair_mulmods(P) * P.np * (P.E + 1);
@@ -289,6 +293,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     }
   }
 
+  J->crt_mm = !(ctx && ctx->crt_garner);
   if (J->crt_ns == 5 || J->crt_ns == 7) ++J->crt_ns;  // CRT kernels exist for 1-4, 6 and 8 slots per lane
   for (int li = 0; li < nl; ++li)
     if (J->partner[li] >= 0) {
@@ -354,7 +359,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
         break;
       case kStageCrt:
         if (!P.wide)
-          for (int b = 0; b < blocks_of(P.D + 1, kCrtWaves); ++b) put(-1, b, 0);
+          for (int b = 0; b < blocks_of(P.D + 1, J->crt_mm ? kCrtMmRows : kCrtWaves); ++b) put(-1, b, 0);
         break;
     }
     return c;
@@ -555,13 +560,14 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     L.pidx = o;  o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
     if (!L.crt_own) {
       const ProbLayout& S = J->lay[L.crt_from];
-      L.Hm = S.Hm; L.NH = S.NH; L.Mi = S.Mi; L.wdir = S.wdir; L.rinv = S.rinv; L.negM = S.negM;
+      L.Hm = S.Hm; L.NH = S.NH; L.Mi = S.Mi; L.Mdig = S.Mdig; L.wdir = S.wdir; L.rinv = S.rinv; L.negM = S.negM;
       L.Mw = S.Mw; L.NHM = S.NHM; L.Tg = S.Tg; L.invM = S.invM; L.Plimb = S.Plimb;
       continue;
     }
     L.Hm = o;    o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
     L.NH = o;    o = align_up(o + static_cast<size_t>(P.L_out) * 4, 16);
     L.Mi = o;    o = align_up(o + static_cast<size_t>(P.np) * P.Lw * 4, 16);
+    L.Mdig = o;  o = align_up(o + P.crt->dig.size(), 16);
     L.wdir = o;  o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
     L.rinv = o;  o = align_up(o + static_cast<size_t>(P.np) * 8, 16);
     L.negM = o;  o = align_up(o + static_cast<size_t>(P.Lw) * 4, 16);
@@ -661,7 +667,8 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     up(kStageConv, interp_coeffs_lds_words(d.D, 4));
     up(kStageStir, interp_basis_lds_words(4));
     if (J->lay[li].item_end[kStageNewton] > J->lay[li].item_begin[kStageNewton]) up(kStageNewton, newton_lds_words(d, 1024));
-    if (!d.wide) up(kStageCrt, crt_lds_words(d, J->crt_ns, crt_block_waves(J->crt_ns)));
+    if (!d.wide)
+      up(kStageCrt, J->crt_mm ? crt_mm_lds_words(d.np, 4) : crt_lds_words(d, J->crt_ns, crt_block_waves(J->crt_ns)));
     if (d.L_in > 2) up(kStageReduce, reduce_ml_lds_words());
   }
   for (int pass = 0; pass < 3; ++pass) J->wide_lds[pass] = 0;
@@ -748,6 +755,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     std::memcpy(blob + L.Hm, P.crt->Hm.data(), P.np * 4);
     std::memcpy(blob + L.NH, P.crt->NH.data(), P.L_out * 4);
     std::memcpy(blob + L.Mi, P.crt->Mi.data(), P.crt->Mi.size() * 4);
+    if (!P.crt->dig.empty()) std::memcpy(blob + L.Mdig, P.crt->dig.data(), P.crt->dig.size());
     std::memcpy(blob + L.wdir, P.crt->wdir.data(), P.crt->wdir.size() * 4);
     std::memcpy(blob + L.rinv, P.crt->rinv.data(), P.crt->rinv.size() * 4);
     std::memcpy(blob + L.negM, P.crt->negM.data(), P.crt->negM.size() * 4);
@@ -768,6 +776,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     d.Hm = reinterpret_cast<const uint32_t*>(base + L.Hm);
     d.NH = reinterpret_cast<const uint32_t*>(base + L.NH);
     d.Mi = reinterpret_cast<const uint32_t*>(base + L.Mi);
+    d.Mdig = base + L.Mdig;
     d.wdir = reinterpret_cast<const uint32_t*>(base + L.wdir);
     d.rinv = reinterpret_cast<const uint32_t*>(base + L.rinv);
     d.negM = reinterpret_cast<const uint32_t*>(base + L.negM);
@@ -934,6 +943,8 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
                                           static_cast<size_t>(eval_stage_lds_words(J->dev[li])) * 4, T, st)
             : s == kStageConv || s == kStageStir
                 ? launch_interp(s - kStageConv, probs, items(s) + L.item_begin[s], cnt, J->dev[li].D, T, st)
+            : s == kStageCrt && J->crt_mm
+                ? launch_crt_mm(probs, items(s) + L.item_begin[s], cnt, J->slot_np, T, st, true)
                 : launch_stage(s, probs, items(s) + L.item_begin[s], cnt, J->stage_lds[s], ns, T, st, 1, true);
         if ((rc = hip_check(ctx, e, "launch"))) return rc;
       }
@@ -1004,12 +1015,15 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
         return rc;
       continue;
     }
-    // CRT: several items per block once the launch still has a block per CU
-    // or more (the degree-24 pair, 146 items, keeps one per block)
+    // column-sum CRT: several items per block once the launch still has a block
+    // per CU or more
     const int crt_per = J->items[kStageCrt].size() >= 1024 ? kCrtItemsPerBlock : 1;
-    if ((rc = hip_check(ctx, launch_stage(s, probs, items(s), static_cast<int>(J->items[s].size()),
-                                          J->stage_lds[s], J->crt_ns, T, st, crt_per, true), "launch")))
-      return rc;
+    const hipError_t e =
+        s == kStageCrt && J->crt_mm
+            ? launch_crt_mm(probs, items(s), static_cast<int>(J->items[s].size()), J->slot_np, T, st, true)
+            : launch_stage(s, probs, items(s), static_cast<int>(J->items[s].size()), J->stage_lds[s], J->crt_ns, T, st,
+                           crt_per, true);
+    if ((rc = hip_check(ctx, e, "launch"))) return rc;
     if (s == kStageCrt)
       for (int pass = 0; pass < 3; ++pass)
         if ((rc = hip_check(ctx, launch_crt_wide((pass == 1 && J->wide_mfma) ? 3 : pass, probs, wide(pass),

@@ -22,7 +22,7 @@ namespace rsl {
 // Schedule parameters chosen by the autotuner (tune.cpp).
 struct ProbLayout {
   // offsets from the job base
-  size_t coeff, gdeg, pidx, Hm, NH, Tg, invM, Plimb, Mi, wdir, rinv, negM, Mw, NHM, wMd, status;
+  size_t coeff, gdeg, pidx, Hm, NH, Tg, invM, Plimb, Mi, Mdig, wdir, rinv, negM, Mw, NHM, wMd, status;
   size_t out, resid, dig, zval, zbad, aconv, cpart, hseg, wT, wq, wS;
   int L_in;
   bool crt_own;  // this problem's layout holds the CRT constant block it shares
@@ -63,8 +63,10 @@ struct Job {
   size_t wide_lds[3] = {};
   size_t items_off[kNumStages] = {};
   size_t stage_lds[kNumStages] = {};
-  int crt_ns = 1;
+  int crt_ns = 1;                  // prime slots per lane of the column-sum CRT (persistent schedule, Garner hook)
+  bool crt_mm = true;              // the slot CRT on the matrix cores (not under the Garner hook)
   int max_np = 0;                  // most primes of any live problem
+  int slot_np = 0;                 // the same without the wide CRT's problems
   int need_g = 0, need_E = 0, need_D = 0;  // constant tables the job reads (primes, points, degree)
   bool any_schur = false;          // some problem evaluates by the Schur algorithm
   // live index of the partner (the same system eliminated in x) that a

@@ -14,6 +14,11 @@ namespace rsl {
 hipError_t launch_stage(int stage, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
                         int crt_ns, const DevTables& T, hipStream_t st, int crt_per_block, bool whole);
 
+// The CRT of up to kSlotCrtPrimes primes on the matrix cores, kCrtMmRows
+// coefficients per item; max_np: the most primes of any item's problem.
+hipError_t launch_crt_mm(const DevProblem* probs, const WorkItem* items, int nitems, int max_np, const DevTables& T,
+                         hipStream_t st, bool whole);
+
 // Evaluation + univariate resultants of items that all have layout `variant`.
 hipError_t launch_eval(int variant, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
                        const DevTables& T, hipStream_t st);

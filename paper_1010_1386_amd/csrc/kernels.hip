@@ -96,6 +96,25 @@ __global__ __launch_bounds__(512) void k_crt(const DevProblem* probs, const Work
   }
 }
 
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_crt_mm(const DevProblem* probs, const WorkItem* items, DevTables T,
+                                                    bool whole) {
+  extern __shared__ uint4 lds4[];
+  const WorkItem w = items[blockIdx.x];
+  stage_crt_mm<NW>(probs[w.prob], T, w, reinterpret_cast<uint32_t*>(lds4), whole);
+}
+
+hipError_t launch_crt_mm(const DevProblem* probs, const WorkItem* items, int nitems, int max_np, const DevTables& T,
+                         hipStream_t st, bool whole) {
+  if (nitems <= 0) return hipSuccess;
+  const int nw = nitems < kCrtMmSplitItems ? 4 : 1;
+  const size_t lds = static_cast<size_t>(crt_mm_lds_words(max_np, nw)) * 4;
+  const dim3 g(nitems), b(64 * nw);
+  if (nw == 4) hipLaunchKernelGGL(k_crt_mm<4>, g, b, lds, st, probs, items, T, whole);
+  else hipLaunchKernelGGL(k_crt_mm<1>, g, b, lds, st, probs, items, T, whole);
+  return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void k_crt_wide_t(const DevProblem* probs, const WorkItem* items, DevTables T,
                                                      bool whole) {
   extern __shared__ uint32_t lds[];

@@ -238,6 +238,24 @@ void direct_crt_tables(const std::vector<uint32_t>& primes, const BigU& M, int L
 
 namespace {
 
+// M_j + 0x80808080 in every limb, the top bit of each byte flipped: the bytes are
+// then digits in -128..127 of M_j itself.
+void crt_digits(CrtConst* C) {
+  const int np = C->np, L = C->L_out, nkc = (np + 63) / 64, nlt = (L + 15) / 16;
+  C->dig.assign(static_cast<size_t>(nlt) * nkc * 4096, 0);
+  for (int i = 0; i < np; ++i) {
+    uint64_t carry = 0;
+    for (int l = 0; l < L; ++l) {
+      const uint64_t s = static_cast<uint64_t>(C->Mi[static_cast<size_t>(i) * L + l]) + 0x80808080u + carry;
+      carry = s >> 32;  // zero out of the top limb: M_j < 2^(32 L - 30)
+      const uint32_t v = static_cast<uint32_t>(s) ^ 0x80808080u;
+      uint8_t* at = C->dig.data() + (static_cast<size_t>(l >> 4) * nkc + (i >> 6)) * 4096 +
+                    ((l & 15) + 16 * ((i & 63) >> 4)) * 16 + (i & 15);
+      for (int d = 0; d < 4; ++d) at[d * 1024] = static_cast<uint8_t>(v >> (8 * d));
+    }
+  }
+}
+
 std::shared_ptr<const CrtConst> build_crt_const(const std::vector<uint32_t>& primes, bool canonical) {
   auto C = std::make_shared<CrtConst>();
   C->np = static_cast<int>(primes.size());
@@ -254,6 +272,7 @@ std::shared_ptr<const CrtConst> build_crt_const(const std::vector<uint32_t>& pri
   C->Lw = C->wide ? C->L_out + 1 : C->L_out;
   if (!canonical && !C->wide) crt_tables(primes, C->L_out, &C->Tg, &C->invM, &C->Plimb);
   direct_crt_tables(primes, M, C->Lw, &C->Mi, &C->wdir, &C->rinv, &C->negM);
+  if (!C->wide) crt_digits(C.get());
   if (C->wide) {
     C->Mw = M.limbs(C->Lw);
     C->NHM = BigU::add(H, M).neg_limbs(C->L_out);
@@ -269,7 +288,8 @@ constexpr size_t kCrtCacheBytes = size_t(512) << 20;
 
 size_t crt_bytes(const CrtConst& C) {
   return 4 * (C.Hm.size() + C.NH.size() + C.Tg.size() + C.invM.size() + C.Plimb.size() + C.Mi.size() +
-              C.wdir.size() + C.rinv.size() + C.negM.size() + C.Mw.size() + C.NHM.size());
+              C.wdir.size() + C.rinv.size() + C.negM.size() + C.Mw.size() + C.NHM.size()) +
+         C.dig.size();
 }
 
 }  // namespace

@@ -2176,6 +2176,7 @@ __device__ inline void crt_one(const DevProblem& P, int k_raw, const uint32_t* m
 __device__ __forceinline__ uint32_t coeff_of(const DevProblem& P, const uint64_t* cpp, size_t cstride, int k,
                                              uint32_t p, uint32_t pinv, bool whole) {
   if (whole) return reinterpret_cast<const uint32_t*>(cpp)[1];
+  if (P.nchunk == 1) return redc(*cpp, p, pinv);
   const int ch0 = k / P.kchunk;
   uint64_t q[8];
 #pragma unroll
@@ -2245,6 +2246,181 @@ __device__ inline void stage_crt(const DevProblem& P, const DevTables& T, const 
         crt_one<NS>(P, kbase + local, mis, L, wb, ures + local * np, pconst);
       else
         crt_one<NS>(P, kbase + local, P.Mi, L, wb, ures + local * np, pconst);
+    }
+  }
+}
+
+// ---------------------------------------------------- CRT on the matrix cores
+// The direct form Y = sum_i t_i M_i - q M of the per-lane-slot path (up to
+// kSlotCrtPrimes primes), with the limb sums as matrix products: coefficients x
+// primes times primes x limbs.  t_i < p_i splits into four balanced base-256
+// digits, and so does each 32-bit limb of M_i once the number is written with
+// signed limbs: adding 0x80808080 to every limb (with carries) and flipping the
+// top bit of each byte gives digits in -128..127 whose value is M_i exactly
+// (CrtConst::dig, in operand order).  The seven anti-diagonal sums stay below
+// 4 * 512 * 2^14 = 2^25, so
+//   V_l = A_l + 2^32 B_l,  A_l = D_0 + .. + 2^24 D_3,  B_l = D_4 + .. + 2^16 D_6
+// are 64-bit signed numbers, and one lane per coefficient walks the limbs with
+// a signed carry: limb l is the low word of A_l + B_{l-1} + NH_l + q negM_l +
+// carry.  Against one wave per coefficient with two multiply-adds per (prime,
+// limb) and ballots for the carries (725 instructions per coefficient on the
+// batch workload): 191 -> 63 us on 256 pairs, 137 -> 48 on 64 requests of
+// degrees 8..48, 259 -> 44 on 10 pairs of degree 9 with 2^512 coefficients.
+//
+// An item is 16 coefficients of a problem.  One wave takes it whole, 16 limbs per
+// step; with NW = 4 (few items) four waves share the primes of the t digits and
+// take 64 limbs per step, and the first walks their carries.
+//
+// Quotient: q is floor(sum f / 2^32) or one more (the f_i undershoot); a wave
+// with an undecided coefficient first walks the limbs of Y0 - M with no output,
+// whose final carry is its sign.
+constexpr int kCrtMmRows = 16;
+// Fewer items than four per SIMD: four waves each (10 pairs of degree 9 with
+// 2^512 coefficients, 60 items of 310 primes: 43.5 against 112 us; the
+// degree-24 pair 8.9 against 16.2; 60 pairs of the batch workload, about 1300
+// items: 25.9 against 38).  At 2900 items they tie (47.5, 49.4); from 5600 on
+// one wave each is faster (62.8 against 68.0 on 256 pairs).
+constexpr int kCrtMmSplitItems = 4096;
+constexpr int kCrtMmSums = 16 * 17;  // [limb][row], odd row count of 8-byte words
+__host__ __device__ inline int crt_mm_lds_words(int np, int nw) {
+  return (np + 63) / 64 * 64 * kCrtMmRows + 4 * kCrtMmSums * nw;
+}
+
+// Word of digit d, row r and the 4 primes 4 w .. 4 w + 3 of a 64-prime chunk:
+// 64-byte rows of four 16-byte units, the units of a row permuted so that
+// neither the word stores down the rows nor the 16-byte operand reads collide
+// in a bank.
+__device__ __forceinline__ int crt_mm_word(int d, int r, int w) {
+  return (d * kCrtMmRows + r) * 16 + (((w >> 2) ^ ((r >> 2) & 3)) << 2) + (w & 3);
+}
+
+template <int NW>
+__device__ inline void stage_crt_mm(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds,
+                                    bool whole) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane & 15, q4 = lane >> 4;
+  const int np = P.np, L = P.L_out, nkc = (np + 63) / 64;
+  auto sync = [] {
+    if constexpr (NW > 1) __syncthreads();
+    else WaveSync()();
+  };
+  uint32_t* tdig = lds;
+  int64_t* sumA = reinterpret_cast<int64_t*>(tdig + nkc * 64 * kCrtMmRows);  // [limb of the step][row]
+  int64_t* sumB = sumA + kCrtMmSums * NW;
+  const int kbase = w.blk * kCrtMmRows;
+  const size_t cstride = static_cast<size_t>(np) * (P.D + 1);
+
+  // t_i and the fixed-point parts: lane = (coefficient row, every fourth quad of primes)
+  const int k = (kbase + row <= P.D) ? kbase + row : P.D;
+  uint64_t f = 0;
+  for (int quad = q4 + 4 * wave; quad < nkc * 16; quad += 4 * NW) {
+    int32_t t[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = 4 * quad + e;
+      t[e] = 0;
+      if (i < np) {
+        const PrimeConst pc = T.pc[P.pidx[i]];
+        const uint64_t* cpp = P.cpart + static_cast<size_t>(i) * (P.D + 1) + k;
+        const uint32_t u = maddm(coeff_of(P, cpp, cstride, k, pc.p, pc.pinv, whole), P.Hm[i], pc.p);
+        const uint32_t tv = mmul(u, P.wdir[i], pc.p, pc.pinv);
+        f += static_cast<uint64_t>(tv) * P.rinv[2 * i + 1] + __umulhi(tv, P.rinv[2 * i]);
+        t[e] = static_cast<int32_t>(tv);
+      }
+    }
+    uint32_t o[kEvDigits];
+    digits4(t[0], t[1], t[2], t[3], o);
+#pragma unroll
+    for (int d = 0; d < kEvDigits; ++d) tdig[(quad >> 4) * 64 * kCrtMmRows + crt_mm_word(d, row, quad & 15)] = o[d];
+  }
+  f += static_cast<uint64_t>(__shfl_xor(static_cast<long long>(f), 16, 64));
+  f += static_cast<uint64_t>(__shfl_xor(static_cast<long long>(f), 32, 64));
+  if constexpr (NW > 1) {  // the waves' parts
+    uint64_t* fp = reinterpret_cast<uint64_t*>(sumA);
+    if (lane < kCrtMmRows) fp[16 * wave + lane] = f;
+    __syncthreads();
+    f = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) f += fp[16 * v + row];
+  }
+  uint32_t q = static_cast<uint32_t>(f >> 32);  // of coefficient row `row`, in its four lanes of every wave
+  const bool undecided = static_cast<uint32_t>(f) >= 0xFFFFFFFFu - 2u * static_cast<uint32_t>(np);
+  sync();
+
+  const ev_v4i* md = reinterpret_cast<const ev_v4i*>(P.Mdig) + lane;
+  auto load_b = [&](int u, ev_v4i (&B)[kEvDigits]) {  // u = limb tile * nkc + chunk
+#pragma unroll
+    for (int d = 0; d < kEvDigits; ++d) B[d] = md[(u * kEvDigits + d) * 64];
+  };
+  const int ntile = (L + 15) / 16;
+  for (int pass = __ballot(undecided) ? 0 : 1; pass < 2; ++pass) {  // block-uniform
+    int64_t carry = 0, lastB = 0;
+    int32_t qr[4];  // multiplier of M for the lane's four output rows
+#pragma unroll
+    for (int r = 0; r < 4; ++r) qr[r] = __shfl(static_cast<int>(q), 4 * q4 + r, 64) + (pass == 0 ? 1 : 0);
+    ev_v4i nx[kEvDigits];
+    if (wave < ntile) load_b(wave * nkc, nx);
+    for (int t0 = 0; t0 < ntile; t0 += NW) {
+      const int tile = t0 + wave;
+      const int l = 16 * tile + row;  // the lane's limb (output column)
+      const int64_t nm = l < L ? static_cast<int64_t>(P.negM[l]) : 0;
+      const int64_t nh = l < L && pass ? static_cast<int64_t>(P.NH[l]) : 0;
+      ev_v4i S[2 * kEvDigits - 1];
+#pragma unroll
+      for (int s = 0; s < 2 * kEvDigits - 1; ++s) S[s] = ev_v4i{0, 0, 0, 0};
+      if (tile < ntile)
+        for (int kc = 0; kc < nkc; ++kc) {
+          ev_v4i A[kEvDigits], B[kEvDigits];
+#pragma unroll
+          for (int d = 0; d < kEvDigits; ++d) B[d] = nx[d];
+          const int u = kc + 1 < nkc ? tile * nkc + kc + 1 : (tile + NW) * nkc;
+          if (u < ntile * nkc) load_b(u, nx);
+#pragma unroll
+          for (int d = 0; d < kEvDigits; ++d)
+            A[d] = *reinterpret_cast<const ev_v4i*>(tdig + kc * 64 * kCrtMmRows + crt_mm_word(d, row, 4 * q4));
+          digit_products(A, B, S);
+        }
+      sync();  // the previous step's sums are consumed
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int at = (16 * wave + row) * 17 + 4 * q4 + r;
+        sumA[at] = smad(S[3][r], 1 << 24, smad(S[2][r], 1 << 16, smad(S[1][r], 1 << 8, S[0][r]))) + nh + qr[r] * nm;
+        sumB[at] = smad(S[6][r], 1 << 16, smad(S[5][r], 1 << 8, S[4][r]));
+      }
+      sync();
+      if (threadIdx.x < kCrtMmRows) {
+        uint32_t* dst = P.out + static_cast<size_t>(kbase + lane) * L + 16 * t0;
+        const bool put = pass == 1 && kbase + lane <= P.D;
+        for (int v = 0; v < NW && t0 + v < ntile; ++v) {
+          const int n = L - 16 * (t0 + v) < 16 ? L - 16 * (t0 + v) : 16;
+          int64_t a[16], b[16];
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            a[j] = sumA[(16 * v + j) * 17 + lane];
+            b[j] = sumB[(16 * v + j) * 17 + lane];
+          }
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            if (j < n) {
+              const int64_t s = a[j] + lastB + carry;
+              lastB = b[j];
+              carry = s >> 32;
+              if (put) dst[16 * v + j] = static_cast<uint32_t>(s);
+            }
+          }
+        }
+      }
+    }
+    // Y0 - M = sum_l (..) 2^(32 l) - (q + 1) 2^(32 L): its sign is that of the carry out less q + 1
+    if (pass == 0) {
+      if (carry + lastB >= static_cast<int64_t>(q) + 1) q += 1u;  // lanes 0..15 of the first wave
+      if constexpr (NW > 1) {
+        __syncthreads();
+        if (threadIdx.x < kCrtMmRows) sumA[lane] = q;
+        __syncthreads();
+        q = static_cast<uint32_t>(sumA[row]);
+      } else {
+        q = static_cast<uint32_t>(__shfl(static_cast<int>(q), row, 64));
+      }
     }
   }
 }

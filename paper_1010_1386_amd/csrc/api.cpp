@@ -317,7 +317,10 @@ static int run_chunked(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g
   };
   while (static_cast<int>(ctx->chunk_jobs.size()) < S) ctx->chunk_jobs.push_back(std::make_shared<Job>());
   std::vector<Job*> jobs(S);
-  for (int c = 0; c < S; ++c) jobs[c] = ctx->chunk_jobs[c].get();
+  for (int c = 0; c < S; ++c) {
+    jobs[c] = ctx->chunk_jobs[c].get();
+    jobs[c]->lean = false;
+  }
   std::vector<std::string> errs(S);
   std::vector<int> brc(S, RSL_OK);
   std::vector<char> ready(S, 0);
@@ -410,6 +413,11 @@ static int run_chunked(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g
     Job& J = *jobs[c];
     if (brc[c]) { rc = brc[c]; break; }
     if (J.live.empty()) { ++launched; continue; }
+    if (J.total > ctx->ws_bytes) {  // the layout with the least memory
+      const int lo = ranges[c].first;
+      J.lean = true;
+      if ((rc = job_build(ctx, J.n, f + lo, g + lo, var + lo, opts, &J, &errs[c], tc, true, true))) break;
+    }
     if (J.total > ctx->ws_bytes) {
       rc = fail(ctx, RSL_ENOMEM, "workspace of " + std::to_string(ctx->ws_bytes) + " bytes < footprint " +
                                      std::to_string(J.total) + " of a chunk");
@@ -436,7 +444,7 @@ static int run_chunked(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g
     if ((rc = job_upload_copy(ctx, &J, ctx->s_up)) ||
         (rc = hip_check(ctx, hipEventRecord(cs.e3, ctx->s_up), "event")) ||
         (rc = hip_check(ctx, hipStreamWaitEvent(sc, cs.e3, 0), "hipStreamWaitEvent")) ||
-        (rc = job_upload_clear(ctx, &J, sc)) || (rc = hip_check(ctx, hipEventRecord(cs.e0, sc), "event")) ||
+        (rc = job_upload_digits(ctx, &J, sc)) || (rc = hip_check(ctx, hipEventRecord(cs.e0, sc), "event")) ||
         (rc = job_launch(ctx, &J, mode, sc, false)) || (rc = hip_check(ctx, hipEventRecord(cs.e1, sc), "event")) ||
         (rc = hip_check(ctx, hipStreamWaitEvent(ctx->s_down, cs.e1, 0), "hipStreamWaitEvent")) ||
         (rc = job_download(ctx, &J, cs.down, ctx->s_down)) ||
@@ -498,8 +506,13 @@ static int run_in_workspace(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_po
   }
   if (ctx->chunk_jobs.empty()) ctx->chunk_jobs.push_back(std::make_shared<Job>());
   Job& J = *ctx->chunk_jobs[0];
+  J.lean = false;
   job_plan(n, f, g, var, opts, &J, &err);
   int rc = job_build(ctx, n, f, g, var, opts, &J, &err, tc, true);
+  if (!rc && J.total > ctx->ws_bytes) {  // the layout with the least memory
+    J.lean = true;
+    rc = job_build(ctx, n, f, g, var, opts, &J, &err, tc, true);
+  }
   if (rc) {  // no layout (tables, options or LDS): nothing ran
     if (status)
       for (int k = 0; k < n; ++k) status[k] = J.pstatus[k] ? J.pstatus[k] : rc;
@@ -642,6 +655,7 @@ int rsl_query(const rsl_poly* f, const rsl_poly* g, int var, rsl_info* info) {
   info->bad_primes = P.bad_primes;
   info->origin = P.origin;
   Job J;
+  J.lean = true;  // what a call needs at least
   std::string e2;
   if (job_build(nullptr, 1, f, g, &var, nullptr, &J, &e2) == RSL_OK) {
     info->footprint_bytes = J.total;

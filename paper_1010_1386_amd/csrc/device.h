@@ -63,8 +63,6 @@ struct DevProblem {
   // slots < pshared also writes its residue tiles (transposed positions)
   int pshared, pmyp, pnyp, pgoff, pCS;
   uint32_t* presid;
-  int pdRTf, pdkh, pdfr;  // the partner's digit tile shape (0 when it has none)
-  uint64_t* pdig;
   int Lw;            // limbs of the rows of Mi and of negM: L_out, or L_out + 1 for the wide path
   // inputs (uploaded)
   const uint32_t* coeff;  // ncoef * L_in two's complement limbs
@@ -106,13 +104,6 @@ struct DevProblem {
 };
 
 // A unit of work of a stage kernel: one block processes one item.
-// A device range the kernels expect zeroed before a run (cleared by one
-// launch over the job's table of them).
-struct ClearRange {
-  uint32_t* dst;
-  uint64_t words;
-};
-
 struct WorkItem {
   int prob;  // index into the problem array
   int slot;  // prime slot (or -1)

@@ -166,13 +166,6 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       if (std::max(P.my, P.ny) <= nmax) return nmax;
     return 0;
   };
-  // the streamed form (one lane per pair, sums on the matrix cores): the lower
-  // degree in registers, the higher one's values in LDS
-  auto stream_ok = [&](const Plan& P) {
-    return regs_ok && !(ctx && ctx->eval_horner) && std::min(P.my, P.ny) >= 1 &&
-           std::min(P.my, P.ny) <= kStreamDegMax && std::max(P.my, P.ny) <= kStreamLongMax &&
-           P.rowf <= kMfmaXPowers && P.rowg <= kMfmaXPowers;
-  };
   const bool evk_auto = evk <= 0;
   if (evk_auto) {
     // the register form needs no cross-lane work: keep one lane per pair for it
@@ -200,6 +193,37 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     if (whole_req) Kc = dmax;
     Kc = (Kc + kCkpt - 1) / kCkpt * kCkpt;  // chunks start at checkpoint rows
   }
+  // the streamed form (one lane per pair, sums on the matrix cores): the lower
+  // degree in registers, the higher one's values in LDS
+  auto stream_ok = [&](const Plan& P) {
+    return regs_ok && !(ctx && ctx->eval_horner) && std::min(P.my, P.ny) >= 1 &&
+           std::min(P.my, P.ny) <= kStreamDegMax && std::max(P.my, P.ny) <= kStreamLongMax &&
+           P.rowf <= kMfmaXPowers && P.rowg <= kMfmaXPowers;
+  };
+  // Digit tiles share their memory with the buffers of the persistent schedule
+  // (residue tiles, convolution sums), which the staged and plain schedules do
+  // not touch.  A lean layout takes them only within that (and within the tiles
+  // of five digits that x-degrees up to 32 had of their own): no shape then needs
+  // more memory than its column layout.
+  auto lanes_asked = [&](const Plan& P) {
+    int e = 1;
+    while (e < evk && std::min(P.my, P.ny) >= 4 * e * 2) e *= 2;
+    return e;
+  };
+  auto five_digit_tiles = [&](const Plan& P) {
+    const int evk_p = lanes_asked(P);
+    return evk_p <= 2 && P.rowf <= 33 && P.rowg <= 33 && regn_of(P, evk_p == 1) > 0 && !(ctx && ctx->eval_horner);
+  };
+  auto tiles_fit = [&](const Plan& P, const DevProblem& d) {
+    if (!J->lean) return true;
+    const size_t np = P.np, rt = dig_rt(P.my + 1) + dig_rt(P.ny + 1);
+    const size_t kh = (P.rowf <= 32 && P.rowg <= 32) ? 1 : 2;
+    const int cchunk = (J->tune.conv_whole || whole_req) ? P.D + 1 : Kc;
+    const size_t shared = np * d.CS * 4 + static_cast<size_t>(blocks_of(P.D + 1, cchunk)) * np * (P.D + 1) * 8;
+    const size_t hseg = np * align_up(static_cast<size_t>(P.D + 1), kCkpt) * 4;
+    return np * rt * kh * kEvDigits * 512 + P.crt->dig.size() <=
+           shared + hseg + (five_digit_tiles(P) ? np * rt * 5 * 512 : 0);
+  };
   J->crt_ns = 1;
   J->max_np = 0;
   J->slot_np = 0;
@@ -228,8 +252,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     d.L_out = P.L_out;
     d.kchunk = Kc;
     d.nchunk = (P.D + 1 + d.kchunk - 1) / d.kchunk;
-    d.evk = 1;
-    const bool stream = stream_ok(P);
+    const bool stream = stream_ok(P) && tiles_fit(P, d);
     // with no lane count asked for, the streamed form takes every problem it
     // fits, whatever the job's size: against two lanes per pair on the
     // degree-24 pair (its smallest use) 30.2 -> 21.9 us, against the LDS columns
@@ -237,8 +260,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     // 668 -> 67 us, on 64 requests of degrees 8..48 8.35 -> 0.99 ms.  The bounds
     // are the registers (lower degree 48), the LDS rows and the K slices; the
     // shapes within them were all accepted by the column layouts it replaces.
-    if (!(evk_auto && stream))
-      while (d.evk < evk && std::min(P.my, P.ny) >= 4 * d.evk * 2) d.evk *= 2;
+    d.evk = (evk_auto && stream) ? 1 : lanes_asked(P);
     d.evpb = 64 / d.evk;
     d.regn = (d.evk <= 2) ? regn_of(P, d.evk == 1) : 0;
     d.schur = (schur_req && P.my >= 1 && P.ny >= 1 && P.my + P.ny <= kSchurMaxR) ? 1 : 0;
@@ -254,7 +276,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     // holds x-powers 0..31, two hold 0..63
     d.evmf = (d.schur || (ctx && ctx->eval_horner)) ? 0
              : d.evk == 1 ? (stream ? 1 : 0)
-                          : (d.evk == 2 && d.regn > 0 && P.rowf <= 33 && P.rowg <= 33 ? 1 : 0);
+                          : (d.evk == 2 && d.regn > 0 && P.rowf <= 33 && P.rowg <= 33 && tiles_fit(P, d) ? 1 : 0);
     if (d.evmf && d.evk == 1) d.regn = (std::min(P.my, P.ny) + 7) / 8 * 8;
     d.dkh = !d.evmf ? 0 : (P.rowf <= 32 && P.rowg <= 32) ? 1 : 2;
     d.dRTf = d.evmf ? dig_rt(P.my + 1) : 0;
@@ -295,18 +317,23 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
 
   J->crt_mm = !(ctx && ctx->crt_garner);
   if (J->crt_ns == 5 || J->crt_ns == 7) ++J->crt_ns;  // CRT kernels exist for 1-4, 6 and 8 slots per lane
+  // a pair shares its reduction where both evaluate from residue tiles; digit
+  // tiles are written whole by their own problem
   for (int li = 0; li < nl; ++li)
     if (J->partner[li] >= 0) {
-      const DevProblem& b = J->dev[J->partner[li]];
+      const int lb = J->partner[li];
+      const DevProblem& b = J->dev[lb];
       DevProblem& a = J->dev[li];
+      if (a.evmf || b.evmf) {
+        J->partner[li] = -1;
+        J->pshared[li] = J->skip_reduce[lb] = 0;
+        continue;
+      }
       a.pshared = J->pshared[li];
       a.pmyp = b.myp;
       a.pnyp = b.nyp;
       a.pgoff = b.goff;
       a.pCS = b.CS;
-      a.pdRTf = b.dRTf;
-      a.pdkh = b.dkh;
-      a.pdfr = b.dfr;
     }
 
   // work items, problem by problem (so that each problem's items are
@@ -326,10 +353,10 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
         // in y); item slot 0 of block 0 also clears the statuses, so a problem
         // whose slots are all shared keeps one such item
         const int s0 = J->skip_reduce[li];
-        if (d.evmf && d.L_in <= 2 && J->partner[li] < 0 && s0 == 0) {  // digit planes a word at a time
-          const int nb = blocks_of(reduce_words(d.my, d.ny, d.rowf, d.rowg), 256);
-          for (int sl = 0; sl < P.np; ++sl)
-            for (int b = 0; b < nb; ++b) put(sl, b, 2);
+        if (d.evmf) {
+          const int spw = d.L_in <= 2 ? kReduceSlotsShort : kReduceSlotsLong;
+          for (int sl = 0; sl < P.np; sl += 4 * spw)
+            for (int b = 0; b < reduce_tile_blocks(d); ++b) put(sl, b, spw);
         } else if (d.L_in > 2) {  // long limb chains: staged limbs, eight primes per thread
           const int first = (s0 / kReduceMlSlots) * kReduceMlSlots;
           for (int sl = first; sl < P.np; sl += kReduceMlSlots)
@@ -373,8 +400,8 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     });
     std::vector<int>& off = J->tmp_b;
     off.assign(cnt.size(), 0);
-    // the evaluation items grouped by layout variant (problem order within a
-    // variant): each variant is one launch of the staged schedule
+    // the evaluation items grouped by layout variant and the reduce items by kind
+    // (problem order within one): each is one launch of the staged schedule
     std::vector<int>& var_of = J->tmp_c;
     var_of.resize(nl);
     int nv = 1;
@@ -382,18 +409,22 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       var_of[li] = eval_variant(J->dev[li]);
       nv = std::max(nv, var_of[li] + 1);
     }
+    auto kind_of = [&](int li) { return !J->dev[li].evmf ? 0 : J->dev[li].L_in <= 2 ? 1 : 2; };
     J->eval_vstart.assign(static_cast<size_t>(nv) + 1, 0);
     for (int s = 0; s < kLists; ++s) {
       int o = 0;
-      for (int v = 0; v < (s == kStageEval ? nv : 1); ++v) {
+      for (int v = 0; v < (s == kStageEval ? nv : s == kStageReduce ? 3 : 1); ++v) {
         if (s == kStageEval) J->eval_vstart[v] = o;
+        if (s == kStageReduce) J->reduce_start[v] = o;
         for (int li = 0; li < nl; ++li) {
           if (s == kStageEval && var_of[li] != v) continue;
+          if (s == kStageReduce && kind_of(li) != v) continue;
           off[static_cast<size_t>(li) * kLists + s] = o;
           o += cnt[static_cast<size_t>(li) * kLists + s];
         }
       }
       if (s == kStageEval) J->eval_vstart[nv] = o;
+      if (s == kStageReduce) J->reduce_start[3] = o;
       J->items[s].clear();
       J->items[s].resize(o);
     }
@@ -545,11 +576,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
   }
   J->wdig_off = o;
   o = align_up(o + sizeof(WorkItem) * J->wdig_items.size(), A);
-  J->nclr = 0;
-  for (int li = 0; li < nl; ++li)
-    J->nclr += (J->dev[li].wide ? 1 : 0) + (J->dev[li].evmf ? 1 : 0) + (J->skip_reduce[li] > 0 ? 1 : 0);
-  J->clr_off = o;
-  o = align_up(o + sizeof(ClearRange) * J->nclr, A);
+  size_t digit_bytes = 0;
   for (int li = 0; li < nl; ++li) {
     const Plan& P = J->plans[J->live[li]];
     const DevProblem& d = J->dev[li];
@@ -568,6 +595,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     L.NH = o;    o = align_up(o + static_cast<size_t>(P.L_out) * 4, 16);
     L.Mi = o;    o = align_up(o + static_cast<size_t>(P.np) * P.Lw * 4, 16);
     L.Mdig = o;  o = align_up(o + P.crt->dig.size(), 16);
+    digit_bytes += P.crt->dig.size();
     L.wdir = o;  o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
     L.rinv = o;  o = align_up(o + static_cast<size_t>(P.np) * 8, 16);
     L.negM = o;  o = align_up(o + static_cast<size_t>(P.Lw) * 4, 16);
@@ -635,13 +663,13 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     const DevProblem& d = J->dev[li];
     ProbLayout& L = J->lay[li];
     const size_t np = P.np;
-    L.resid = o; o = align_up(o + np * d.CS * 4, A);
-    L.dig = o;   o = align_up(o + np * d.dfr * 512, A);
+    if (!d.evmf) {
+      L.resid = o;
+      o = align_up(o + np * d.CS * 4, A);
+    }
     L.zval = o;  o = align_up(o + np * (P.E + 1) * 4, A);
     L.zbad = o;  o = align_up(o + np * (P.E + 1), A);
-    L.aconv = o; o = align_up(o + static_cast<size_t>(d.ncchunk) * np * (P.D + 1) * 8, A);
     L.cpart = o; o = align_up(o + static_cast<size_t>(d.nchunk) * np * (P.D + 1) * 8, A);
-    L.hseg = o;  o = align_up(o + np * align_up(static_cast<size_t>(P.D + 1), kCkpt) * 4, A);
     L.wT = L.wq = L.wS = L.wMd = 0;
     if (P.wide) {
       if (!L.crt_own) {
@@ -654,8 +682,41 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       L.wS = o; o = align_up(o + static_cast<size_t>(P.D + 1) * 2 * P.Lw * 8, A);
     }
   }
-  J->queue_off = o;
-  o = align_up(o + J->queue_bytes, A);
+  // one region for buffers that are never live together: the digit tiles of the
+  // staged and plain schedules (read by the evaluation), their segment
+  // polynomials (interpolation only), and the persistent schedule's residue tiles
+  // (of problems with digit tiles), convolution sums and live queue.  Each is
+  // written before it is read, in every run.  The region is as large as those
+  // buffers side by side with five-digit tiles for x-degrees up to 32: admission
+  // against a budget counts a request as it always did.
+  {
+    size_t tiles = o, segs = o, own = o, apart = o;
+    for (int li = 0; li < nl; ++li) {
+      const Plan& P = J->plans[J->live[li]];
+      const DevProblem& d = J->dev[li];
+      ProbLayout& L = J->lay[li];
+      const size_t np = P.np;
+      L.dig = 0;
+      if (d.evmf) {
+        L.dig = tiles;
+        tiles = align_up(tiles + np * d.dfr * 512, A);
+        L.resid = own;
+        own = align_up(own + np * d.CS * 4, A);
+      }
+      L.hseg = segs;
+      segs = align_up(segs + np * align_up(static_cast<size_t>(P.D + 1), kCkpt) * 4, A);
+      L.aconv = own;
+      own = align_up(own + static_cast<size_t>(d.ncchunk) * np * (P.D + 1) * 8, A);
+      apart += align_up(np * align_up(static_cast<size_t>(P.D + 1), kCkpt) * 4, A) +
+               (five_digit_tiles(P) ? np * (dig_rt(P.my + 1) + dig_rt(P.ny + 1)) * 5 * 512 : 0);
+    }
+    J->queue_off = own;
+    own = align_up(own + J->queue_bytes, A);
+    // (less the limb digits, which the upload image holds in place of the item
+    // lists it had)
+    const size_t counted = own + (apart - o);
+    o = std::max({tiles, segs, own, counted > digit_bytes ? counted - digit_bytes : 0});
+  }
   J->total = o;
 
   // LDS per stage launch (max over problems)
@@ -669,7 +730,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     if (J->lay[li].item_end[kStageNewton] > J->lay[li].item_begin[kStageNewton]) up(kStageNewton, newton_lds_words(d, 1024));
     if (!d.wide)
       up(kStageCrt, J->crt_mm ? crt_mm_lds_words(d.np, 4) : crt_lds_words(d, J->crt_ns, crt_block_waves(J->crt_ns)));
-    if (d.L_in > 2) up(kStageReduce, reduce_ml_lds_words());
+    if (d.L_in > 2 && !d.evmf) up(kStageReduce, reduce_ml_lds_words());
   }
   for (int pass = 0; pass < 3; ++pass) J->wide_lds[pass] = 0;
   for (int li = 0; li < nl; ++li) {
@@ -800,21 +861,6 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
   for (int li = 0; li < nl; ++li) {
     const int pa = J->partner[li];
     J->dev[li].presid = (pa >= 0) ? reinterpret_cast<uint32_t*>(base + J->lay[pa].resid) : nullptr;
-    J->dev[li].pdig = (pa >= 0 && J->dev[pa].evmf) ? reinterpret_cast<uint64_t*>(base + J->lay[pa].dig) : nullptr;
-  }
-  // the clear table: the t rows of the wide CRT (their padding stays zero),
-  // the digit tiles (only the coefficient positions are written) and the
-  // residue tiles a partner fills (its padding)
-  {
-    ClearRange* cr = reinterpret_cast<ClearRange*>(blob + J->clr_off);
-    int c = 0;
-    for (int li = 0; li < nl; ++li) {
-      const DevProblem& d = J->dev[li];
-      if (d.wide) cr[c++] = ClearRange{d.wT, static_cast<uint64_t>(d.wdpad) * d.wnpad};
-      if (d.evmf) cr[c++] = ClearRange{reinterpret_cast<uint32_t*>(d.dig), static_cast<uint64_t>(d.np) * d.dfr * 128};
-      if (J->skip_reduce[li] > 0)
-        cr[c++] = ClearRange{d.resid, static_cast<uint64_t>(J->skip_reduce[li]) * d.CS};
-    }
   }
   // initial queue image: one REDUCE task per (problem, prime slot), largest problems first
   // (none when a problem has more primes than the persistent schedule takes)
@@ -901,20 +947,15 @@ int job_upload_copy(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned) {
 
 int job_upload(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned) {
   int rc = job_upload_copy(ctx, J, st, pinned);
-  if (!rc) rc = job_upload_clear(ctx, J, st);
+  if (!rc) rc = job_upload_digits(ctx, J, st);
   return rc;
 }
 
-int job_upload_clear(rsl_ctx* ctx, Job* J, hipStream_t st) {
-  // one launch over the clear table the upload brought (ordered after it)
-  int rc = hip_check(ctx, launch_clear_ranges(reinterpret_cast<const ClearRange*>(J->base + J->clr_off), J->nclr, st),
-                     "clear ranges");
-  if (!rc)
-    rc = hip_check(ctx, launch_wide_digits(reinterpret_cast<const DevProblem*>(J->base + J->probs_off),
+int job_upload_digits(rsl_ctx* ctx, Job* J, hipStream_t st) {
+  return hip_check(ctx, launch_wide_digits(reinterpret_cast<const DevProblem*>(J->base + J->probs_off),
                                            reinterpret_cast<const WorkItem*>(J->base + J->wdig_off),
                                            static_cast<int>(J->wdig_items.size()), st),
                    "wide digits");
-  return rc;
 }
 
 int job_reset(rsl_ctx* ctx, Job* J, hipStream_t st) {
@@ -939,7 +980,10 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
       for (int s = 0; s < kNumStages; ++s) {
         const int cnt = L.item_end[s] - L.item_begin[s];
         const hipError_t e =
-            s == kStageEval ? launch_eval(eval_variant(J->dev[li]), probs, items(s) + L.item_begin[s], cnt,
+            s == kStageReduce && J->dev[li].evmf
+                ? launch_reduce_tiles(J->dev[li].L_in <= 2 ? kReduceSlotsShort : kReduceSlotsLong, probs,
+                                      items(s) + L.item_begin[s], cnt, T, st)
+            : s == kStageEval ? launch_eval(eval_variant(J->dev[li]), probs, items(s) + L.item_begin[s], cnt,
                                           static_cast<size_t>(eval_stage_lds_words(J->dev[li])) * 4, T, st)
             : s == kStageConv || s == kStageStir
                 ? launch_interp(s - kStageConv, probs, items(s) + L.item_begin[s], cnt, J->dev[li].D, T, st)
@@ -1000,6 +1044,17 @@ int job_launch(rsl_ctx* ctx, Job* J, int mode, hipStream_t st, bool stage_events
   }
   for (int s = 0; s < kNumStages; ++s) {
     if (stage_events && (rc = hip_check(ctx, hipEventRecord(ctx->ev[s], st), "event"))) return rc;
+    if (s == kStageReduce) {
+      const int* rs = J->reduce_start;
+      if ((rc = hip_check(ctx, launch_stage(s, probs, items(s), rs[1], J->stage_lds[s], J->crt_ns, T, st, 1, true),
+                          "launch")) ||
+          (rc = hip_check(ctx, launch_reduce_tiles(kReduceSlotsShort, probs, items(s) + rs[1], rs[2] - rs[1], T, st),
+                          "launch")) ||
+          (rc = hip_check(ctx, launch_reduce_tiles(kReduceSlotsLong, probs, items(s) + rs[2], rs[3] - rs[2], T, st),
+                          "launch")))
+        return rc;
+      continue;
+    }
     if (s == kStageEval) {
       const WorkItem* evs = reinterpret_cast<const WorkItem*>(J->base + J->evs_off);
       for (const Job::EvalRange& r : J->eval_ranges)

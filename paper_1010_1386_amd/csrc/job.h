@@ -49,10 +49,8 @@ struct Job {
   std::vector<int> eval_vstart;        // first evaluation item of each layout variant (and the end)
   std::vector<WorkItem> eval_staged;   // evaluation items dealt across XCDs
   size_t evs_off = 0;
-  // the ranges the kernels expect zeroed (a table in the upload image, cleared
-  // by one launch after the upload)
-  size_t clr_off = 0;
-  int nclr = 0;
+  // reduce items by kind: residue tiles, digit tiles of short and of long inputs
+  int reduce_start[4] = {};
   // wide CRT (problems with more primes than the per-lane slots cover): items of
   // its three passes
   std::vector<WorkItem> wide_items[3];
@@ -96,6 +94,10 @@ struct Job {
   int64_t mfma_macs = 0;           // int8 multiply-adds issued on the matrix cores for those sums
   int64_t interp_mm = 0;           // interpolation products: N_p (D+1)(D+2) over problems
   TuneConfig tune;                 // schedule parameters the job was laid out with
+  // set before job_build: digit tiles only for problems whose layout stays within
+  // the memory it takes without them (callers with a fixed amount of memory lay
+  // a job that does not fit out again with this)
+  bool lean = false;
   // scratch of job_build, kept with the job so that a job object reused for
   // the next batch reuses its host memory (no fresh pages per call)
   std::vector<WorkItem> tmp_items;
@@ -135,12 +137,11 @@ inline size_t upload_bytes(const Job& J) { return J.with_queue ? J.up_bytes : J.
 // copy is done) or to the context's staging buffer when pinned is null, unless
 // it already is pinned memory bound with job_bind (then it is sent directly).
 int job_upload(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned = nullptr);
-// The two halves of job_upload: the copy of the image, and the launches that
-// clear the intermediate buffers the kernels expect zeroed and build the wide
-// CRT's digit planes (ordered after the copy; they may run on another stream
-// that waits for it).
+// The two halves of job_upload: the copy of the image, and the launch that builds
+// the wide CRT's digit planes from it, if any (ordered after the copy; it may
+// run on another stream that waits for it).
 int job_upload_copy(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned = nullptr);
-int job_upload_clear(rsl_ctx* ctx, Job* J, hipStream_t st);
+int job_upload_digits(rsl_ctx* ctx, Job* J, hipStream_t st);
 // Zero the status words before a persistent run (the staged and plain launches
 // clear them in their reduce stage).
 int job_reset(rsl_ctx* ctx, Job* J, hipStream_t st);

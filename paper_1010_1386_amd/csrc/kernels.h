@@ -19,6 +19,11 @@ hipError_t launch_stage(int stage, const DevProblem* probs, const WorkItem* item
 hipError_t launch_crt_mm(const DevProblem* probs, const WorkItem* items, int nitems, int max_np, const DevTables& T,
                          hipStream_t st, bool whole);
 
+// The reduction of problems with digit tiles: items whose sub is spw
+// (kReduceSlotsShort for inputs of at most two limbs, kReduceSlotsLong beyond).
+hipError_t launch_reduce_tiles(int spw, const DevProblem* probs, const WorkItem* items, int nitems, const DevTables& T,
+                               hipStream_t st);
+
 // Evaluation + univariate resultants of items that all have layout `variant`.
 hipError_t launch_eval(int variant, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
                        const DevTables& T, hipStream_t st);
@@ -48,7 +53,5 @@ hipError_t launch_stirling_build(uint32_t* stir, int64_t sstride, const PrimeCon
 
 // dst[t] = src[t] (or 0 when src is null) for t < n words.
 hipError_t launch_copy_words(uint32_t* dst, const uint32_t* src, size_t n, hipStream_t st);
-// Zero every range of a device table of n ClearRanges in one launch.
-hipError_t launch_clear_ranges(const ClearRange* ranges, int n, hipStream_t st);
 
 }  // namespace rsl

@@ -33,12 +33,29 @@ static_assert(kCrtWaves == kCrtBlockCoeffs, "one coefficient per wave of a CRT b
 __global__ __launch_bounds__(256) void k_reduce(const DevProblem* probs, const WorkItem* items, DevTables T) {
   extern __shared__ uint32_t lds[];
   const WorkItem w = items[blockIdx.x];
-  if (w.sub == 2)
-    stage_reduce_words(probs[w.prob], T, w);
-  else if (w.sub)
-    stage_reduce_ml(probs[w.prob], T, w, lds, true);
+  if (w.sub)
+    stage_reduce_ml(probs[w.prob], T, w, lds);
   else
-    stage_reduce(probs[w.prob], T, w, true, true);
+    stage_reduce(probs[w.prob], T, w, true);
+}
+
+// Digit tiles (items ordered by their sub, the prime slots per wave)
+template <int SPW>
+__global__ __launch_bounds__(256) void k_reduce_tiles(const DevProblem* probs, const WorkItem* items, DevTables T) {
+  extern __shared__ uint32_t lds[];
+  const WorkItem w = items[blockIdx.x];
+  stage_reduce_tiles<SPW>(probs[w.prob], T, w, lds);
+}
+
+hipError_t launch_reduce_tiles(int spw, const DevProblem* probs, const WorkItem* items, int nitems, const DevTables& T,
+                               hipStream_t st) {
+  if (nitems <= 0) return hipSuccess;
+  const dim3 g(nitems), b(256);
+  if (spw == kReduceSlotsShort) hipLaunchKernelGGL(k_reduce_tiles<kReduceSlotsShort>, g, b, 0, st, probs, items, T);
+  else if (spw == kReduceSlotsLong)
+    hipLaunchKernelGGL(k_reduce_tiles<kReduceSlotsLong>, g, b, reduce_tiles_lds_words() * 4, st, probs, items, T);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_eval(int variant, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
@@ -277,21 +294,6 @@ hipError_t launch_copy_words(uint32_t* dst, const uint32_t* src, size_t n, hipSt
   if (n == 0) return hipSuccess;
   const size_t blocks = std::min<size_t>((n + 255) / 256, 1024);
   hipLaunchKernelGGL(k_copy_words, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, dst, src, n);
-  return hipGetLastError();
-}
-
-// Workgroup b clears part (b mod kClearSplit) of range b / kClearSplit.
-constexpr int kClearSplit = 16;
-__global__ __launch_bounds__(256) void k_clear_ranges(const ClearRange* ranges) {
-  const ClearRange r = ranges[blockIdx.x / kClearSplit];
-  const size_t stride = static_cast<size_t>(kClearSplit) * 256;
-  for (size_t t = static_cast<size_t>(blockIdx.x % kClearSplit) * 256 + threadIdx.x; t < r.words; t += stride)
-    r.dst[t] = 0u;
-}
-
-hipError_t launch_clear_ranges(const ClearRange* ranges, int n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_clear_ranges, dim3(static_cast<unsigned>(n) * kClearSplit), dim3(256), 0, st, ranges);
   return hipGetLastError();
 }
 

@@ -62,6 +62,10 @@ extern "C" int rsl_res_static(rsl_ctx* ctx, const rsl_poly* f, const rsl_poly* g
   job_plan(1, f, g, &var, opts, &J, &err);
   // host layout only: the constant tables are not grown here (that would allocate)
   rc = job_build(ctx, 1, f, g, &var, opts, &J, &err, nullptr, true, true);
+  if (!rc && J.total > kStaticScratchBytes) {  // the layout with the least memory
+    J.lean = true;
+    rc = job_build(ctx, 1, f, g, &var, opts, &J, &err, nullptr, true, true);
+  }
   if (rc) return fail(ctx, rc, err);
   if (!J.live.empty()) {
     if (J.total > kStaticScratchBytes)

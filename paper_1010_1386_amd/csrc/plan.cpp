@@ -241,17 +241,16 @@ namespace {
 // M_j + 0x80808080 in every limb, the top bit of each byte flipped: the bytes are
 // then digits in -128..127 of M_j itself.
 void crt_digits(CrtConst* C) {
-  const int np = C->np, L = C->L_out, nkc = (np + 63) / 64, nlt = (L + 15) / 16;
-  C->dig.assign(static_cast<size_t>(nlt) * nkc * 4096, 0);
+  const int np = C->np, L = C->L_out, nq = (np + 15) / 16, nlt = (L + 15) / 16;
+  C->dig.assign(static_cast<size_t>(nlt) * nq * 1024, 0);
   for (int i = 0; i < np; ++i) {
     uint64_t carry = 0;
     for (int l = 0; l < L; ++l) {
       const uint64_t s = static_cast<uint64_t>(C->Mi[static_cast<size_t>(i) * L + l]) + 0x80808080u + carry;
       carry = s >> 32;  // zero out of the top limb: M_j < 2^(32 L - 30)
       const uint32_t v = static_cast<uint32_t>(s) ^ 0x80808080u;
-      uint8_t* at = C->dig.data() + (static_cast<size_t>(l >> 4) * nkc + (i >> 6)) * 4096 +
-                    ((l & 15) + 16 * ((i & 63) >> 4)) * 16 + (i & 15);
-      for (int d = 0; d < 4; ++d) at[d * 1024] = static_cast<uint8_t>(v >> (8 * d));
+      uint8_t* at = C->dig.data() + (static_cast<size_t>(l >> 4) * nq + (i >> 4)) * 1024 + (l & 15) * 16 + (i & 15);
+      for (int d = 0; d < 4; ++d) at[d * 256] = static_cast<uint8_t>(v >> (8 * d));
     }
   }
 }

@@ -54,9 +54,9 @@ struct CrtConst {
   // direct CRT tables: limbs of M / p_j ([np][Lw]), (M / p_i)^{-1} R mod p_i,
   // floor(2^64 / p_i) as (low, high) words, 2^(32 Lw) - M
   std::vector<uint32_t> Mi, wdir, rinv, negM;
-  // slot path: balanced base-256 digits of the M / p_j limbs as the right operands of
-  // v_mfma_i32_16x16x64_i8: [16 limbs][64 primes][digit][lane][16 bytes], lane =
-  // limb mod 16 + 16 (prime mod 64 / 16), byte = prime mod 16; zero padded
+  // slot path: balanced base-256 digits of the M / p_j limbs, 16-byte runs of the right
+  // operands of v_mfma_i32_16x16x64_i8: [16 limbs][16 primes][digit][limb mod 16][prime
+  // mod 16], zero padded
   std::vector<uint8_t> dig;
   // wide path: M in Lw limbs, -(M-1)/2 - M mod 2^(32 L_out)
   std::vector<uint32_t> Mw, NHM;

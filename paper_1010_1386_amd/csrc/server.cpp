@@ -218,8 +218,17 @@ int launch(rsl_server* S, Lane& ln, std::vector<std::shared_ptr<Request>>& grp) 
   }
   if (rc) return rc == RSL_ENOMEM ? kTablesFull : rc;  // waiting frees no table room
   size_t off = 0;
-  const size_t bytes = std::max<size_t>(J.total, 256);
-  if (!S->arena.alloc(bytes, &off)) return RSL_ENOMEM;
+  size_t bytes = std::max<size_t>(J.total, 256);
+  if (!S->arena.alloc(bytes, &off)) {  // the layout with the least memory, as admission counted it
+    J.lean = true;
+    {
+      std::lock_guard<std::recursive_mutex> lk(ctx->mu);
+      rc = job_build(ctx, n, f.data(), g.data(), var.data(), nullptr, &J, &err, &kServeLayout, /*planned=*/true);
+    }
+    if (rc) return rc == RSL_ENOMEM ? kTablesFull : rc;
+    bytes = std::max<size_t>(J.total, 256);
+    if (!S->arena.alloc(bytes, &off)) return RSL_ENOMEM;
+  }
   ln.job = std::move(J);
   ln.off = off;
   ln.bytes = bytes;
@@ -372,6 +381,7 @@ static int plan_request(rsl_server* S, const rsl_poly* f, const rsl_poly* g, int
   r->var = var;
   // the one plan of this request, and its footprint from the layout of it alone
   Job J;
+  J.lean = true;  // the least it can run in
   std::string err;
   int rc = job_build(nullptr, 1, &r->f, &r->g, &r->var, nullptr, &J, &err, &kServeLayout);
   if (rc) return rc;

@@ -148,20 +148,16 @@ __device__ inline int partner_pos(const DevProblem& P, int t) {
   return P.pgoff + j * P.pnyp + i;
 }
 
-// Tile position t -> polynomial gp (0: f, 1: g), x-power i and row j; returns
-// the input coefficient's index, -1 for a padding position.
-__device__ inline int tile_coord(const DevProblem& P, int t, int* gp, int* i, int* j) {
+// Tile position t -> the input coefficient's index, -1 for a padding position.
+__device__ inline int tile_input(const DevProblem& P, int t) {
+  if (t >= P.CS) return -1;
   if (t < P.goff) {
-    *gp = 0;
-    *i = t / P.myp;
-    *j = t - *i * P.myp;
-    return (*j <= P.my) ? *j * P.rowf + *i : -1;
+    const int i = t / P.myp, j = t - i * P.myp;
+    return (j <= P.my) ? j * P.rowf + i : -1;
   }
   const int u = t - P.goff;
-  *gp = 1;
-  *i = u / P.nyp;
-  *j = u - *i * P.nyp;
-  return (*i < P.rowg && *j <= P.ny) ? (P.my + 1) * P.rowf + *j * P.rowg + *i : -1;
+  const int i = u / P.nyp, j = u - i * P.nyp;
+  return (i < P.rowg && j <= P.ny) ? (P.my + 1) * P.rowf + j * P.rowg + i : -1;
 }
 
 // Digit tiles (evaluation on the matrix cores).  The residue c mod p of the
@@ -175,7 +171,6 @@ __device__ inline int tile_coord(const DevProblem& P, int t, int* gp, int* i, in
 //   KH = 1: digits 3, 2, 1, 0 of x-powers 8 (l / 16) .. + 7, eight bytes each
 //   KH = 2: digits 0, 1, 2, 3, sixteen bytes each: x-powers 8 (l / 16) .. + 7,
 //           then 32 + 8 (l / 16) .. + 7
-// Padding positions are never written (the tiles are cleared at upload).
 __host__ __device__ inline int dig_rt(int rows) { return (rows + 15) / 16; }
 constexpr int kEvDigits = 4;
 // balanced base-256 digits of v (|v| <= 0x7F7F7F7F) as the bytes of a word
@@ -189,89 +184,181 @@ __device__ __forceinline__ void byte_transpose4(uint32_t w0, uint32_t w1, uint32
   out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
   out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
 }
-// byte offset of digit 0, and the step between digits, of the K run of 8 x-powers
-// k8 = i / 8 of row j in a slot's tiles (rt0: tiles before the polynomial's first)
-__host__ __device__ inline size_t dig_offset(int kh, int rt0, int k8, int j, int* step) {
-  const size_t unit = (static_cast<size_t>(rt0 + (j >> 4)) * 64 + (j & 15) + 16 * (k8 & 3)) * (32 * kh);
-  *step = kh == 1 ? -8 : 16;
-  return kh == 1 ? unit + 24 : unit + 8 * (k8 >> 2);
-}
-__device__ inline void write_digits(uint64_t* dig, int fr, int kh, int rtf, int slot, int gp, int i, int j,
-                                    uint32_t r) {
-  int step;
-  uint8_t* at = reinterpret_cast<uint8_t*>(dig + static_cast<size_t>(slot) * fr * 64) +
-                dig_offset(kh, gp ? rtf : 0, i >> 3, j, &step) + (i & 7);
-  const uint32_t w = balanced_digits(r);
-#pragma unroll
-  for (int b = 0; b < kEvDigits; ++b) at[b * step] = static_cast<uint8_t>(w >> (8 * b));
-}
-
-// staged = true (the reduction launched as its own kernel): the residue tiles
-// are written only for problems whose staged evaluation reads them (Horner
-// forms); the persistent schedule evaluates by Horner and writes them all.
 __device__ inline void stage_reduce(const DevProblem& P, const DevTables& T, const WorkItem& w,
-                                    bool zero_status = false, bool staged = false) {
+                                    bool zero_status = false) {
   if (zero_status && w.slot == 0 && w.blk == 0)
     for (int i = threadIdx.x; i < 2 * P.np + 2; i += blockDim.x) P.status[i] = 0;
   const int t = w.blk * blockDim.x + threadIdx.x;
   if (t >= P.CS) return;
   const PrimeConst pc = T.pc[P.pidx[w.slot]];
-  int gp, ci, cj;
-  const int in = tile_coord(P, t, &gp, &ci, &cj);
-  const bool own_tile = !(staged && P.evmf), partner_tile = !(staged && P.pdig);
+  const int in = tile_input(P, t);
   uint32_t v = 0;
   if (in >= 0) {
-    const uint32_t p = pc.p;
     const uint32_t r = limbs_mod_p(P.coeff + static_cast<size_t>(in) * P.L_in, P.L_in, pc);
-    v = mmul(r, pc.r3, p, pc.pinv);
-    if (w.slot < P.pshared && partner_tile)
-      P.presid[static_cast<size_t>(w.slot) * P.pCS + partner_pos(P, t)] = v;
-    if (P.dig) write_digits(P.dig, P.dfr, P.dkh, P.dRTf, w.slot, gp, ci, cj, r);
-    if (P.pdig && w.slot < P.pshared) write_digits(P.pdig, P.pdfr, P.pdkh, P.pdRTf, w.slot, gp, cj, ci, r);
+    v = mmul(r, pc.r3, pc.p, pc.pinv);
+    if (w.slot < P.pshared) P.presid[static_cast<size_t>(w.slot) * P.pCS + partner_pos(P, t)] = v;
   }
-  if (own_tile) P.resid[static_cast<size_t>(w.slot) * P.CS + t] = v;
+  P.resid[static_cast<size_t>(w.slot) * P.CS + t] = v;
 }
 
-// Problems whose evaluation takes its sums from the matrix cores and that
-// share no reduction with a partner (inputs of at most two limbs): one thread
-// per (row, 8 consecutive x-powers) of a prime slot, which writes the four
-// digits of that run as 8-byte words (eight separate byte stores per digit
-// otherwise).  Consecutive threads take consecutive rows.  Item (slot, block of
-// 256 words, sub = 2).
-__host__ __device__ inline int reduce_words(int my, int ny, int rowf, int rowg) {
-  return (my + 1) * ((rowf + 7) / 8) + (ny + 1) * ((rowg + 7) / 8);
+// Problems whose evaluation takes its sums from the matrix cores: whole digit
+// tiles, written every run (padding included, so nothing is cleared before).  A
+// lane owns one K run of 8 x-powers of one row -- 8 coefficients, their four
+// digits 32 bytes of the tile -- and each of the block's four waves SPW prime
+// slots.  In signed residues a limb w = w_s + 2^32 b (w_s its signed value) takes
+//   r <- sredc((r + b) R^2 + w_s R) = r 2^32 + w mod p,
+// five instructions per limb, coefficient and prime (|r| <= 0.9 p with the two
+// constants centred).  Inputs of more than two limbs pass through LDS 16 limbs
+// at a time, read once per block for its 4 SPW primes.  Item (first slot, block
+// of 64 lanes, sub = SPW).
+//
+// Short inputs: the lanes walk the tiles in order, padding runs as zeros (a
+// separate pass over the padding cost more than the idle lanes: 41 -> 48 us on 256
+// pairs of the batch workload).  Long ones: the runs with coefficients first, the
+// padding in blocks of its own, which skip the limb loop (258 -> 193 us on 10
+// pairs of degree 15 with 2^2048 coefficients, of whose tile runs a quarter hold
+// coefficients).  Against byte or 8-byte stores of canonical residues with 14
+// instructions per limb, and a clearing launch per upload: 256 pairs 80 -> 41 us,
+// 64 requests of degrees 8..48 75 -> 38, the 2^2048 set 368 -> 193; the launch
+// saved 3-9 us per call.
+constexpr int kReduceChunk = 16;  // limbs per LDS chunk
+// Prime slots per wave for inputs of up to two limbs (2, 3, 4: 7.4, 8.1, 8.5 us on
+// the degree-24 pair, 41, 37, 38 us on 256 pairs) and of more (4, 5, 6, 8: 258,
+// 253, 264, 272 us on the 2^2048 set before its padding was split off, 29.5, 32.5,
+// 32.5, 30.3 us on 10 pairs of degree 9 with 2^512).
+constexpr int kReduceSlotsShort = 2, kReduceSlotsLong = 4;
+// runs with coefficients, and all runs of a slot's tiles
+__host__ __device__ inline int reduce_runs(const DevProblem& P) {
+  return (P.my + 1) * ((P.rowf + 7) / 8) + (P.ny + 1) * ((P.rowg + 7) / 8);
 }
-__device__ inline void stage_reduce_words(const DevProblem& P, const DevTables& T, const WorkItem& w) {
+__host__ __device__ inline int reduce_tile_runs(const DevProblem& P) { return (P.dRTf + P.dRTg) * 64 * P.dkh; }
+__host__ __device__ inline int reduce_tile_blocks(const DevProblem& P) {
+  return (P.L_in > 2 ? (reduce_runs(P) + 63) / 64 : 0) + reduce_tile_runs(P) / 64;
+}
+__host__ __device__ inline int reduce_tiles_lds_words() { return kReduceChunk * 8 * 64; }
+template <int SPW>
+__device__ inline void stage_reduce_tiles(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
   if (w.slot == 0 && w.blk == 0)
     for (int i = threadIdx.x; i < 2 * P.np + 2; i += blockDim.x) P.status[i] = 0;
-  const int t = w.blk * blockDim.x + threadIdx.x;
-  const int nwf = (P.my + 1) * ((P.rowf + 7) / 8);
-  if (t >= reduce_words(P.my, P.ny, P.rowf, P.rowg)) return;
-  const int gp = t >= nwf ? 1 : 0;
-  const int u = gp ? t - nwf : t;
-  const int rows = gp ? P.ny + 1 : P.my + 1;
-  const int k = u / rows, j = u - k * rows;
-  const int len = gp ? P.rowg : P.rowf;
-  const uint32_t* src =
-      P.coeff + (static_cast<size_t>(gp ? (P.my + 1) * P.rowf : 0) + static_cast<size_t>(j) * len) * P.L_in;
-  const PrimeConst pc = T.pc[P.pidx[w.slot]];
-  uint32_t r[8];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kh = P.dkh, s0 = w.slot + wave * SPW;
+  // run of 8 x-powers k8 of row j of polynomial gp -> its place in the slot's tiles
+  auto place = [&](int gp, int j, int k8) {
+    return reinterpret_cast<uint8_t*>(P.dig + static_cast<size_t>(s0) * P.dfr * 64) +
+           (static_cast<size_t>((gp ? P.dRTf : 0) + (j >> 4)) * 64 + (j & 15) + 16 * (k8 & 3)) * (32 * kh) +
+           8 * (k8 >> 2);
+  };
+  auto store = [&](uint8_t* at, const uint32_t (&lo)[kEvDigits], const uint32_t (&hi)[kEvDigits]) {
+    if (kh == 1) {
+      reinterpret_cast<uint4*>(at)[0] = make_uint4(lo[3], hi[3], lo[2], hi[2]);
+      reinterpret_cast<uint4*>(at)[1] = make_uint4(lo[1], hi[1], lo[0], hi[0]);
+    } else {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int i = 8 * k + e;
-    r[e] = (i < len) ? limbs_mod_p(src + static_cast<size_t>(i) * P.L_in, P.L_in, pc) : 0u;
+      for (int b = 0; b < kEvDigits; ++b)
+        *reinterpret_cast<uint64_t*>(at + 16 * b) = (static_cast<uint64_t>(hi[b]) << 32) | lo[b];
+    }
+  };
+  const size_t slot_bytes = static_cast<size_t>(P.dfr) * 512;
+  int gp, j, k8, nv;
+  auto tile_run = [&](int t) {  // run t of the tiles in order
+    const int unit = t >> (kh - 1), tile = unit >> 6, ln = unit & 63;
+    gp = tile >= P.dRTf ? 1 : 0;
+    j = 16 * (tile - (gp ? P.dRTf : 0)) + (ln & 15);
+    k8 = (ln >> 4) + 4 * (t & (kh - 1));
+    nv = j <= (gp ? P.ny : P.my) ? (gp ? P.rowg : P.rowf) - 8 * k8 : 0;
+  };
+  bool mine = true;
+  if constexpr (SPW == kReduceSlotsLong) {
+    const int nruns = reduce_runs(P), nb = (nruns + 63) / 64;
+    if (w.blk >= nb) {  // runs without coefficients: zero
+      tile_run((w.blk - nb) * 64 + lane);
+      if (nv > 0) return;
+      const uint32_t zero[kEvDigits] = {0u, 0u, 0u, 0u};
+      uint8_t* at = place(gp, j, k8);
+      for (int s = 0; s < SPW && s0 + s < P.np; ++s) store(at + s * slot_bytes, zero, zero);
+      return;
+    }
+    // runs with coefficients, consecutive lanes taking consecutive rows
+    const int t = w.blk * 64 + lane, nf = (P.my + 1) * ((P.rowf + 7) / 8);
+    gp = t >= nf ? 1 : 0;
+    const int u = gp ? t - nf : t, rows = gp ? P.ny + 1 : P.my + 1;
+    k8 = u / rows;
+    j = u - k8 * rows;
+    mine = t < nruns;
+    nv = mine ? (gp ? P.rowg : P.rowf) - 8 * k8 : 0;
+  } else {
+    tile_run(w.blk * 64 + lane);
   }
-  uint32_t lo[kEvDigits], hi[kEvDigits];
+  nv = nv < 0 ? 0 : nv > 8 ? 8 : nv;  // coefficients of the run
+  const int i0 = 8 * k8, len = gp ? P.rowg : P.rowf;
+  const int L = P.L_in;
+  const uint32_t* src =
+      P.coeff + (static_cast<size_t>(gp ? (P.my + 1) * P.rowf : 0) + static_cast<size_t>(j) * len + i0) * L;
+  SignedMod M[SPW];
+  int32_t r1[SPW], r2[SPW], acc[SPW][8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = balanced_digits(r[e]);
-  byte_transpose4(r[0], r[1], r[2], r[3], lo);
-  byte_transpose4(r[4], r[5], r[6], r[7], hi);
-  int step;
-  uint8_t* at = reinterpret_cast<uint8_t*>(P.dig + static_cast<size_t>(w.slot) * P.dfr * 64) +
-                dig_offset(P.dkh, gp ? P.dRTf : 0, k, j, &step);
+  for (int s = 0; s < SPW; ++s) {
+    const PrimeConst pc = T.pc[P.pidx[s0 + s < P.np ? s0 + s : P.np - 1]];
+    M[s] = signed_mod(pc);
+    r1[s] = scenter(static_cast<int32_t>(pc.r1), M[s]);
+    r2[s] = scenter(static_cast<int32_t>(pc.r2), M[s]);
+  }
+  auto top = [&](const uint32_t (&v)[8]) {
 #pragma unroll
-  for (int b = 0; b < kEvDigits; ++b)
-    *reinterpret_cast<uint64_t*>(at + b * step) = (static_cast<uint64_t>(hi[b]) << 32) | lo[b];
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int s = 0; s < SPW; ++s) acc[s][e] = smul(static_cast<int32_t>(v[e]), r1[s], M[s]);
+  };
+  auto next = [&](const uint32_t (&v)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int32_t b = static_cast<int32_t>(v[e] >> 31);
+#pragma unroll
+      for (int s = 0; s < SPW; ++s)
+        acc[s][e] = sredc(smad(acc[s][e] + b, r2[s], smad(static_cast<int32_t>(v[e]), r1[s], 0)), M[s]);
+    }
+  };
+  uint32_t v[8];
+  if (L <= 2) {
+    uint32_t lo[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      v[e] = e < nv ? src[e * L + L - 1] : 0u;
+      lo[e] = (L == 2 && e < nv) ? src[2 * e] : 0u;
+    }
+    top(v);
+    if (L == 2) next(lo);
+  } else {
+    for (int l1 = L; l1 > 0; l1 -= kReduceChunk) {  // limbs [l0, l1), top chunk first
+      const int l0 = l1 > kReduceChunk ? l1 - kReduceChunk : 0;
+      __syncthreads();
+      // wave q brings limbs l0 + 4 q .. + 3 of every lane's coefficients
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int u = 0; u < kReduceChunk / 4; ++u) {
+          const int l = 4 * wave + u;
+          lds[(l * 8 + e) * 64 + lane] = (e < nv && l0 + l < l1) ? src[static_cast<size_t>(e) * L + l0 + l] : 0u;
+        }
+      __syncthreads();
+      for (int l = l1 - l0 - 1; l >= 0; --l) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = lds[(l * 8 + e) * 64 + lane];
+        if (l0 + l == L - 1) top(v);
+        else next(v);
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < SPW; ++s) {
+    if (s0 + s >= P.np || !mine) break;
+    uint32_t lo[kEvDigits], hi[kEvDigits], d[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) d[e] = balanced_digits(static_cast<uint32_t>(acc[s][e]));
+    byte_transpose4(d[0], d[1], d[2], d[3], lo);
+    byte_transpose4(d[4], d[5], d[6], d[7], hi);
+    store(place(gp, j, k8) + s * slot_bytes, lo, hi);
+  }
 }
 
 // Multi-limb inputs: a block takes 64 transposed positions and 32 prime slots
@@ -285,24 +372,13 @@ constexpr int kReduceMlSlots = 32;
 constexpr int kReduceMlLimbs = 64;
 __host__ __device__ inline int reduce_ml_lds_words() { return kReduceMlLimbs * (kReduceMlCoeffs + 1); }
 
-__device__ inline void stage_reduce_ml(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds,
-                                       bool staged = false) {
+__device__ inline void stage_reduce_ml(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds) {
   if (w.slot == 0 && w.blk == 0)
     for (int i = threadIdx.x; i < 2 * P.np + 2; i += blockDim.x) P.status[i] = 0;
   constexpr int kPer = kReduceMlSlots / 4;
   const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int t = w.blk * kReduceMlCoeffs + c;
-  auto input_of = [&](int tt) {
-    if (tt >= P.CS) return -1;
-    if (tt < P.goff) {
-      const int i = tt / P.myp, j = tt - i * P.myp;
-      return (j <= P.my) ? j * P.rowf + i : -1;
-    }
-    const int u = tt - P.goff;
-    const int i = u / P.nyp, j = u - i * P.nyp;
-    return (i < P.rowg && j <= P.ny) ? (P.my + 1) * P.rowf + j * P.rowg + i : -1;
-  };
-  const int in = input_of(t);
+  const int in = tile_input(P, t);
   uint32_t p[kPer], pinv[kPer], r2[kPer], r3[kPer], acc[kPer];
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
@@ -320,7 +396,7 @@ __device__ inline void stage_reduce_ml(const DevProblem& P, const DevTables& T, 
     __syncthreads();
     for (int e = threadIdx.x; e < kReduceMlCoeffs * nl; e += blockDim.x) {
       const int cc = e / nl, l = e - cc * nl;
-      const int ci = input_of(w.blk * kReduceMlCoeffs + cc);
+      const int ci = tile_input(P, w.blk * kReduceMlCoeffs + cc);
       lds[l * (kReduceMlCoeffs + 1) + cc] = (ci >= 0) ? P.coeff[static_cast<size_t>(ci) * L + l0 + l] : 0u;
     }
     __syncthreads();
@@ -348,18 +424,13 @@ __device__ inline void stage_reduce_ml(const DevProblem& P, const DevTables& T, 
   }
   if (t >= P.CS) return;
   const int tp = (in >= 0 && w.slot < P.pshared) ? partner_pos(P, t) : 0;
-  int gp, ci, cj;
-  tile_coord(P, t, &gp, &ci, &cj);
-  const bool own_tile = !(staged && P.evmf), partner_tile = !(staged && P.pdig);
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
     const int sl = w.slot + q + 4 * r;
     if (sl < P.np) {
       const uint32_t v = (in >= 0) ? mmul(acc[r], r3[r], p[r], pinv[r]) : 0u;
-      if (own_tile) P.resid[static_cast<size_t>(sl) * P.CS + t] = v;
-      if (in >= 0 && sl < P.pshared && partner_tile) P.presid[static_cast<size_t>(sl) * P.pCS + tp] = v;
-      if (in >= 0 && P.dig) write_digits(P.dig, P.dfr, P.dkh, P.dRTf, sl, gp, ci, cj, acc[r]);
-      if (in >= 0 && P.pdig && sl < P.pshared) write_digits(P.pdig, P.pdfr, P.pdkh, P.pdRTf, sl, gp, cj, ci, acc[r]);
+      P.resid[static_cast<size_t>(sl) * P.CS + t] = v;
+      if (in >= 0 && sl < P.pshared) P.presid[static_cast<size_t>(sl) * P.pCS + tp] = v;
     }
   }
 }
@@ -2346,10 +2417,13 @@ __device__ inline void stage_crt_mm(const DevProblem& P, const DevTables& T, con
   const bool undecided = static_cast<uint32_t>(f) >= 0xFFFFFFFFu - 2u * static_cast<uint32_t>(np);
   sync();
 
-  const ev_v4i* md = reinterpret_cast<const ev_v4i*>(P.Mdig) + lane;
+  const ev_v4i* md = reinterpret_cast<const ev_v4i*>(P.Mdig) + row;
+  const int nq = (np + 15) / 16;  // groups of 16 primes
   auto load_b = [&](int u, ev_v4i (&B)[kEvDigits]) {  // u = limb tile * nkc + chunk
+    const int lt = u / nkc, qu = 4 * (u - lt * nkc) + q4;
+    const int at = lt * nq + (qu < nq ? qu : nq - 1);  // beyond the last prime: any digits, the t digits are zero
 #pragma unroll
-    for (int d = 0; d < kEvDigits; ++d) B[d] = md[(u * kEvDigits + d) * 64];
+    for (int d = 0; d < kEvDigits; ++d) B[d] = md[(at * kEvDigits + d) * 16];
   };
   const int ntile = (L + 15) / 16;
   for (int pass = __ballot(undecided) ? 0 : 1; pass < 2; ++pass) {  // block-uniform

@@ -102,16 +102,24 @@ static int bind_and_upload(rsl_ctx* ctx, rsl_job* j) {
   return RSL_OK;
 }
 
-// Lay the job out with `tc` and, when memory is bound, upload the inputs.
-static int materialize(rsl_ctx* ctx, rsl_job* j, const TuneConfig& tc) {
+static int lay_out(rsl_ctx* ctx, rsl_job* j, const TuneConfig& tc, bool lean) {
   release_mem(j);
   j->J = Job();
+  j->J.lean = lean;
   j->tc = tc;
   std::string err;
   const int n = static_cast<int>(j->f.size());
   int rc = job_build(ctx, n, j->f.data(), j->g.data(), j->var.data(), j->has_opts ? &j->opts : nullptr, &j->J,
                      &err, &tc);
   if (!err.empty()) ctx->err = err;
+  return rc;
+}
+
+// Lay the job out with `tc` and, when memory is bound, upload the inputs (the
+// layout with the least memory when the other does not fit the bound memory).
+static int materialize(rsl_ctx* ctx, rsl_job* j, const TuneConfig& tc) {
+  int rc = lay_out(ctx, j, tc, false);
+  if (!rc && j->dmem && j->J.total > j->dmem_bytes) rc = lay_out(ctx, j, tc, true);
   if (rc) return rc;
   return j->dmem ? bind_and_upload(ctx, j) : RSL_OK;
 }
@@ -271,7 +279,8 @@ int rsl_job_bind(rsl_ctx* ctx, rsl_job* j, void* d_mem, size_t bytes) {
   if (rc) return rc;
   j->dmem = static_cast<uint8_t*>(d_mem);
   j->dmem_bytes = bytes;
-  if ((rc = bind_and_upload(ctx, j))) {
+  if (j->J.total > bytes && !j->J.lean) rc = lay_out(ctx, j, TuneConfig(j->tc), true);
+  if (rc || (rc = bind_and_upload(ctx, j))) {
     j->dmem = nullptr;
     j->dmem_bytes = 0;
   }

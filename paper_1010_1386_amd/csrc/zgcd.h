@@ -3,7 +3,7 @@
 // R by Yun's algorithm, i.e. gcds of R and its derivatives; the outlook of
 // Sec. 6 proposes the modular route for it).  Device stages, per prime slot:
 //   zreduce  u, v mod p (two's complement limbs, division-free)
-//   zgcd     Euclid's algorithm over Z_p in LDS, one wave per prime,
+//   zgcd     Euclid's algorithm over Z_p in LDS, one block per prime,
 //            division-free steps; the gcd made monic and scaled by
 //            ell = gcd(lc u, lc v) mod p
 //   zpack    the kept slots' scaled gcds in the CRT input layout
@@ -45,7 +45,7 @@ struct ZgcdDesc {
   int* rem;             // [0] set when a division leaves a remainder
 };
 
-constexpr int kZThreads = 256;  // reduce and pack; Euclid and the divisions run one wave per slot
+constexpr int kZThreads = 256;  // threads of a block of every pass
 
 // residues of u (sub 0) or v (sub 1): item slot, block of 256 coefficients
 __device__ inline void stage_zreduce(const ZgcdDesc& Z, const DevTables& T, const WorkItem& w) {
@@ -72,42 +72,65 @@ __device__ inline int zdeg_below(const uint32_t* a, int d) {
   return -1;
 }
 
-// One wave per prime slot.  Pseudo-remainder steps without divisions,
-//   A <- lc(B) A - lc(A) x^(deg A - deg B) B,
-// keep A a nonzero multiple of the remainder sequence's members, so the last
-// nonzero one is a multiple of the gcd; one inversion at the end makes it monic.
+// One block per prime slot.  Pseudo-remainder steps without divisions keep A a
+// nonzero multiple of the remainder sequence's members, so the last nonzero one
+// is a multiple of the gcd; one inversion at the end makes it monic.  In the
+// generic pattern (deg A = deg B + 1) one pass takes the two eliminations at
+// once, as in the evaluation,
+//   A[j] <- L^2 A[j] - L lc(A) B[j-1] - (L A[b] - lc(A) B[b-1]) B[j],  L = lc(B),
+// with one barrier: a step's scalars and every B[j] come from entries it does
+// not write.  Bound by the latency of a step (LDS reads, the scalars' products,
+// the barrier), 0.32 us each: 115 us for a polynomial of degree 360 and its
+// derivative on all primes; one wave per prime with one elimination per pass
+// took 326 us, as six coefficients a lane went through every step in turn.
 __device__ inline void stage_zgcd(const ZgcdDesc& Z, const DevTables& T, int slot, uint32_t* lds) {
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x;
   const PrimeConst pc = T.pc[Z.pidx[slot]];
   const uint32_t p = pc.p, pinv = pc.pinv, one = pc.r1;
   uint32_t* X = lds;                 // nu + 1 words
   uint32_t* Y = lds + (Z.nu + 1);    // nv + 1 words
-  for (int k = lane; k <= Z.nu; k += 64) X[k] = mmul(Z.up[static_cast<size_t>(slot) * (Z.nu + 1) + k], pc.r2, p, pinv);
-  for (int k = lane; k <= Z.nv; k += 64) Y[k] = mmul(Z.vp[static_cast<size_t>(slot) * (Z.nv + 1) + k], pc.r2, p, pinv);
-  WaveSync()();
+  for (int k = tid; k <= Z.nu; k += nt) X[k] = mmul(Z.up[static_cast<size_t>(slot) * (Z.nu + 1) + k], pc.r2, p, pinv);
+  for (int k = tid; k <= Z.nv; k += nt) Y[k] = mmul(Z.vp[static_cast<size_t>(slot) * (Z.nv + 1) + k], pc.r2, p, pinv);
+  __syncthreads();
   uint32_t* A = X;
   uint32_t* B = Y;
+  // degrees, the same in every wave: read from LDS between barriers
   int da = zdeg_below(X, Z.nu + 1), db = (Z.nv >= 0) ? zdeg_below(Y, Z.nv + 1) : -1;
   if (da < db) {
     uint32_t* t = A; A = B; B = t;
     const int d = da; da = db; db = d;
   }
-  while (db >= 0) {
-    while (da >= db) {
-      const uint32_t la = A[da], lb = B[db];
-      const int s = da - db;
-      for (int j = lane; j < da; j += 64)
-        A[j] = (j >= s) ? mmulsub(lb, A[j], la, B[j - s], p, pinv) : mmul(lb, A[j], p, pinv);
-      WaveSync()();
-      da = zdeg_below(A, da);
+  while (db > 0) {
+    const uint32_t L = B[db];
+    int dr;
+    if (da == db + 1) {
+      const uint32_t lcA = A[da], lcAt = mmulsub(L, A[db], lcA, B[db - 1], p, pinv);
+      const uint32_t al = mmul(L, L, p, pinv), be = p - mmul(L, lcA, p, pinv), ga = p - lcAt;
+      for (int j = tid; j < db; j += nt) A[j] = mmad3(al, A[j], be, j > 0 ? B[j - 1] : 0u, ga, B[j], p, pinv);
+      __syncthreads();
+      dr = A[db - 1] != 0u ? db - 1 : zdeg_below(A, db - 1);
+    } else {
+      for (int d = da; d >= db; --d) {
+        const uint32_t la = A[d];
+        const int s = d - db;
+        for (int j = tid; j < d; j += nt)
+          A[j] = (j >= s) ? mmulsub(L, A[j], la, B[j - s], p, pinv) : mmul(L, A[j], p, pinv);
+        __syncthreads();
+      }
+      dr = zdeg_below(A, db);
     }
     uint32_t* t = A; A = B; B = t;
-    const int d = da; da = db; db = d;
+    da = db;
+    db = dr;
+  }
+  if (db == 0) {  // a nonzero constant: the gcd
+    A = B;
+    da = 0;
   }
   const uint32_t inv = (da >= 0) ? minv(A[da], one, p, pinv) : 0u;
-  for (int k = lane; k <= da; k += 64)
+  for (int k = tid; k <= da; k += nt)
     Z.gt[static_cast<size_t>(slot) * Z.gs + k] = mmul(mmul(A[k], inv, p, pinv), Z.ell[slot], p, pinv);
-  if (lane == 0) Z.gdeg[slot] = da;
+  if (tid == 0) Z.gdeg[slot] = da;
 }
 
 // kept slot i: the scaled gcd in the CRT input layout (Montgomery form: the
@@ -127,43 +150,45 @@ __host__ __device__ inline int zcof_lds_words(const ZgcdDesc& Z) {
 
 // Long division of W (degree n, Montgomery) by G (degree dg, Montgomery,
 // inverse leading coefficient ginv): quotient coefficients to q[0..n-dg]
-// (Montgomery form, the CRT input layout), remainder check.
+// (Montgomery form, the CRT input layout), remainder check.  One barrier per
+// quotient coefficient.
 __device__ inline void zdivide(uint32_t* W, int n, const uint32_t* G, int dg, uint32_t ginv, uint64_t* q,
                                int* rem, const PrimeConst& pc) {
   const uint32_t p = pc.p, pinv = pc.pinv;
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x;
   for (int k = n - dg; k >= 0; --k) {
     const uint32_t qk = mmul(W[k + dg], ginv, p, pinv);
-    if (lane == 0) q[k] = qk;
-    for (int j = lane; j < dg; j += 64) W[k + j] = msubm(W[k + j], mmul(qk, G[j], p, pinv), p);
-    WaveSync()();
+    if (tid == 0) q[k] = qk;
+    for (int j = tid; j < dg; j += nt) W[k + j] = msubm(W[k + j], mmul(qk, G[j], p, pinv), p);
+    __syncthreads();
   }
-  if (zdeg_below(W, dg) >= 0 && lane == 0) rem[0] = 1;
+  if (zdeg_below(W, dg) >= 0 && tid == 0) rem[0] = 1;
 }
 
-// kept slot i: G mod p, then u / G and v / G
-__device__ inline void stage_zcof(const ZgcdDesc& Z, const DevTables& T, int i, uint32_t* lds) {
-  const int tid = threadIdx.x;
+// Kept slot i: G mod p, then u / G (part 0) or v / G (part 1), a block each:
+// bound by the latency of a quotient coefficient like the steps above.  Degree
+// 360: 53 us (114 us with one wave per prime and the divisions in turn).
+__device__ inline void stage_zcof(const ZgcdDesc& Z, const DevTables& T, int i, int part, uint32_t* lds) {
+  const int tid = threadIdx.x, nt = blockDim.x;
   const int slot = Z.kept[i];
   const PrimeConst pc = T.pc[Z.pidx[slot]];
   const uint32_t p = pc.p, pinv = pc.pinv, one = pc.r1;
-  const int n = Z.nu > Z.nv ? Z.nu : Z.nv;
+  const int n = part ? Z.nv : Z.nu;
+  if (n < Z.dg) return;  // v = 0 (no cofactor)
   uint32_t* W = lds;              // n + 1 words
   uint32_t* G = lds + (n + 1);    // dg + 1 words
   const uint32_t sM = mmul(Z.sinv[i], pc.r2, p, pinv);
-  for (int k = tid; k <= Z.dg; k += 64) {
+  for (int k = tid; k <= Z.dg; k += nt) {
     const uint32_t g = mmul(mmul(Z.gt[static_cast<size_t>(slot) * Z.gs + k], pc.r2, p, pinv), sM, p, pinv);
     G[k] = g;
-    Z.cg[static_cast<size_t>(i) * (Z.dg + 1) + k] = g;
+    if (part == 0) Z.cg[static_cast<size_t>(i) * (Z.dg + 1) + k] = g;
   }
-  for (int k = tid; k <= Z.nu; k += 64) W[k] = mmul(Z.up[static_cast<size_t>(slot) * (Z.nu + 1) + k], pc.r2, p, pinv);
-  WaveSync()();
+  const uint32_t* src = (part ? Z.vp : Z.up) + static_cast<size_t>(slot) * (n + 1);
+  for (int k = tid; k <= n; k += nt) W[k] = mmul(src[k], pc.r2, p, pinv);
+  __syncthreads();
   const uint32_t ginv = minv(G[Z.dg], one, p, pinv);
-  zdivide(W, Z.nu, G, Z.dg, ginv, Z.ca + static_cast<size_t>(i) * (Z.nu - Z.dg + 1), Z.rem, pc);
-  if (Z.nv < Z.dg) return;  // v = 0 (no cofactor)
-  for (int k = tid; k <= Z.nv; k += 64) W[k] = mmul(Z.vp[static_cast<size_t>(slot) * (Z.nv + 1) + k], pc.r2, p, pinv);
-  WaveSync()();
-  zdivide(W, Z.nv, G, Z.dg, ginv, Z.cb + static_cast<size_t>(i) * (Z.nv - Z.dg + 1), Z.rem, pc);
+  uint64_t* q = (part ? Z.cb : Z.ca) + static_cast<size_t>(i) * (n - Z.dg + 1);
+  zdivide(W, n, G, Z.dg, ginv, q, Z.rem, pc);
 }
 
 }  // namespace rsl

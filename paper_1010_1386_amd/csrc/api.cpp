@@ -219,33 +219,62 @@ static int signed_limbs(const uint32_t* c, int L) {
   return n;
 }
 
-int decode_result(const Plan& P, const uint32_t* limbs, rsl_result* out) {
-  if (!out) return RSL_EINVAL;
-  int deg = -1, need = 1;
-  if (!P.zero) {
-    const int L = P.L_out;
-    for (int k = 0; k <= P.D; ++k) {
-      const uint32_t* c = limbs + static_cast<size_t>(k) * L;
-      bool nz = false;
-      for (int l = 0; l < L; ++l) nz |= (c[l] != 0u);
-      if (nz) {
-        deg = k;
-        need = std::max(need, signed_limbs(c, L));
-      }
+// Degree of a result of D + 1 coefficients of L limbs: the highest nonzero one.
+int result_degree(const uint32_t* limbs, int D, int L) {
+  for (int k = D; k >= 0; --k) {
+    const uint32_t* c = limbs + static_cast<size_t>(k) * L;
+    uint32_t any = 0;
+    for (int l = 0; l < L; ++l) any |= c[l];
+    if (any) return k;
+  }
+  return -1;
+}
+
+// Coefficients lo..hi-1 of a result: the limbs the widest of them needs, and
+// with `copy` (out's rows hold at least L limbs) the coefficients themselves,
+// in one pass over the limbs.
+int take_rows(const uint32_t* limbs, int L, int lo, int hi, rsl_result* out, bool copy) {
+  int need = 1;
+  for (int k = lo; k < hi; ++k) {
+    const uint32_t* c = limbs + static_cast<size_t>(k) * L;
+    const uint32_t ext = (c[L - 1] >> 31) ? 0xFFFFFFFFu : 0u;
+    // the limbs above the widest so far are sign extension, as is its sign bit?
+    uint32_t diff = (c[need - 1] ^ ext) >> 31;
+    for (int l = need; l < L; ++l) diff |= c[l] ^ ext;
+    if (diff) need = signed_limbs(c, L);
+    if (copy) {
+      uint32_t* dst = out->coeff + static_cast<size_t>(k) * out->limbs;
+      std::memcpy(dst, c, static_cast<size_t>(L) * 4);
+      for (int l = L; l < out->limbs; ++l) dst[l] = ext;
     }
   }
+  return need;
+}
+
+bool result_roomy(const rsl_result* out, int L, int deg) {
+  return out->coeff && out->limbs >= L && out->cap_deg >= deg;
+}
+
+int finish_result(const uint32_t* limbs, int L, int deg, int need, bool copied, rsl_result* out) {
   out->deg = deg;
   out->needed_limbs = need;
-  if (deg < 0) return RSL_OK;
+  if (deg < 0 || copied) return RSL_OK;
   if (out->limbs < need || out->cap_deg < deg || !out->coeff) return RSL_ERANGE;
-  const int L = P.L_out;
+  const int w = std::min(L, out->limbs);
   for (int k = 0; k <= deg; ++k) {
     const uint32_t* c = limbs + static_cast<size_t>(k) * L;
     const uint32_t ext = (c[L - 1] >> 31) ? 0xFFFFFFFFu : 0u;
     uint32_t* dst = out->coeff + static_cast<size_t>(k) * out->limbs;
-    for (int l = 0; l < out->limbs; ++l) dst[l] = (l < L) ? c[l] : ext;
+    for (int l = 0; l < out->limbs; ++l) dst[l] = (l < w) ? c[l] : ext;
   }
   return RSL_OK;
+}
+
+int decode_result(const Plan& P, const uint32_t* limbs, rsl_result* out) {
+  if (!out) return RSL_EINVAL;
+  const int L = P.L_out, deg = P.zero ? -1 : result_degree(limbs, P.D, L);
+  const bool copy = result_roomy(out, L, deg);
+  return finish_result(limbs, L, deg, deg < 0 ? 1 : take_rows(limbs, L, 0, deg + 1, out, copy), copy, out);
 }
 
 static int grow_pinned(rsl_ctx* ctx, uint8_t** buf, size_t* have, size_t need) {
@@ -467,21 +496,30 @@ static int run_chunked(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g
   return rc;
 }
 
+// batches of at least this many nonzero problems run as a pipeline of chunks
+constexpr int kChunkedLive = 96;
+
 // Run a job laid out in the context workspace, synchronously.
 static int run_in_workspace(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const int* var,
                             const rsl_opts* opts, rsl_result* out, int* status, int mode, rsl_counters* cnt) {
   if (ctx->server) return workspace_taken(ctx);
   const double t0 = now_ms();
   std::string err;
-  // shapes from the inputs alone: the schedule lookup and the chunking need no plans
-  std::vector<ShapeEst> est(n);
-  parallel_for(n, 32, [&](int k) { est[k] = estimate_shape(&f[k], &g[k], var[k]); });
+  // shapes from the inputs alone: the schedule lookup and the chunking need no
+  // plans; a call too small for chunks, with no tuned schedule to look up, needs
+  // neither (64 requests of degrees 8..48: 1.5 ms of host time)
+  const char* chunks_env = std::getenv("RSL_BATCH_CHUNKS");
+  std::vector<ShapeEst> est;
+  if ((mode == RSL_AUTO && !ctx->tune_cache.empty()) || (mode != RSL_BATCHED && (n >= kChunkedLive || chunks_env))) {
+    est.resize(n);
+    parallel_for(n, host_grain(3000.0), [&](int k) { est[k] = estimate_shape(&f[k], &g[k], var[k]); });
+  }
   // RSL_AUTO: the schedule the autotuner chose for this shape bucket, else the
   // staged default; the job is laid out once, with the chosen parameters
   const TuneConfig* tc = nullptr;
   if (mode == RSL_AUTO) {
     mode = RSL_STAGED;
-    auto it = ctx->tune_cache.find(tune_key_of(est));
+    auto it = ctx->tune_cache.empty() ? ctx->tune_cache.end() : ctx->tune_cache.find(tune_key_of(est));
     if (it != ctx->tune_cache.end()) {
       mode = it->second.cfg.mode;
       tc = &it->second.cfg;
@@ -489,11 +527,11 @@ static int run_in_workspace(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_po
   }
   // large batches on the staged or plain schedule: a pipeline of chunks, so
   // that host work overlaps the device
-  if (mode != RSL_BATCHED) {
+  if (mode != RSL_BATCHED && !est.empty()) {
     int live = 0;
     for (const ShapeEst& e : est) live += (!e.zero && !e.bad) ? 1 : 0;
-    int S = live >= 384 ? 5 : live >= 192 ? 4 : live >= 96 ? 2 : 1;
-    if (const char* env = std::getenv("RSL_BATCH_CHUNKS")) S = std::max(1, std::min(16, std::atoi(env)));
+    int S = live >= 384 ? 5 : live >= 192 ? 4 : live >= kChunkedLive ? 2 : 1;
+    if (chunks_env) S = std::max(1, std::min(16, std::atoi(chunks_env)));
     if (S > 1) {
       std::vector<std::pair<int, int>> ranges = chunk_ranges(est, var, S);
       if (ranges.size() > 1) {

@@ -135,6 +135,11 @@ int ensure_staging(rsl_ctx* ctx, size_t up, size_t down);
 
 // Decode the CRT limbs of a problem into the caller's result.
 int decode_result(const Plan& P, const uint32_t* limbs, rsl_result* out);
+// its parts, for decoding in blocks of coefficients on several threads
+int result_degree(const uint32_t* limbs, int D, int L);
+bool result_roomy(const rsl_result* out, int L, int deg);
+int take_rows(const uint32_t* limbs, int L, int lo, int hi, rsl_result* out, bool copy);
+int finish_result(const uint32_t* limbs, int L, int deg, int need, bool copied, rsl_result* out);
 
 double now_ms();
 

@@ -34,7 +34,11 @@ int job_plan(int n, const rsl_poly* f, const rsl_poly* g, const int* var, const 
   J->live.clear();
   // planning is independent per problem: spread it over host threads
   std::vector<std::string> perr(n);
-  parallel_for(n, 4, [&](int k) {
+  double words = 0.0;  // of the inputs, while their sizes make sense
+  for (int k = 0; k < n; ++k)
+    for (const rsl_poly* q : {&f[k], &g[k]})
+      if (q->dx >= 0 && q->dy >= 0 && q->limbs > 0) words += (q->dx + 1.0) * (q->dy + 1.0) * q->limbs;
+  parallel_for(n, host_grain(2000.0 + 8.0 * words / std::max(n, 1)), [&](int k) {
     std::string& e = perr[k];
     int rc = make_plan(&f[k], &g[k], var[k], opts, &J->plans[k], &e);
     if (!rc && !J->plans[k].zero) {
@@ -343,9 +347,13 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     const Plan& P = J->plans[J->live[li]];
     const DevProblem& d = J->dev[li];
     int c = 0;
-    auto put = [&](int slot, int blk, int sub) {
-      if (out) out[c] = WorkItem{li, slot, blk, sub};
-      ++c;
+    // blocks 0..nb-1 of every step-th slot of s0..np-1
+    auto put = [&](int s0, int np, int step, int nb, int sub) {
+      if (out)
+        for (int sl = s0; sl < np; sl += step)
+          for (int b = 0; b < nb; ++b) out[c++] = WorkItem{li, sl, b, sub};
+      else if (s0 < np)
+        c += (np - s0 + step - 1) / step * nb;
     };
     switch (s) {
       case kStageReduce: {
@@ -355,38 +363,31 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
         const int s0 = J->skip_reduce[li];
         if (d.evmf) {
           const int spw = d.L_in <= 2 ? kReduceSlotsShort : kReduceSlotsLong;
-          for (int sl = 0; sl < P.np; sl += 4 * spw)
-            for (int b = 0; b < reduce_tile_blocks(d); ++b) put(sl, b, spw);
+          put(0, P.np, 4 * spw, reduce_tile_blocks(d), spw);
         } else if (d.L_in > 2) {  // long limb chains: staged limbs, eight primes per thread
           const int first = (s0 / kReduceMlSlots) * kReduceMlSlots;
-          for (int sl = first; sl < P.np; sl += kReduceMlSlots)
-            for (int b = 0; b < blocks_of(d.CS, kReduceMlCoeffs); ++b) put(sl, b, 1);
-          if (first > 0) put(0, 0, 1);
+          put(first, P.np, kReduceMlSlots, blocks_of(d.CS, kReduceMlCoeffs), 1);
+          if (first > 0) put(0, 1, 1, 1, 1);
         } else {
-          for (int sl = s0; sl < P.np; ++sl)
-            for (int b = 0; b < blocks_of(d.CS, 256); ++b) put(sl, b, 0);
-          if (s0 > 0) put(0, 0, 0);
+          put(s0, P.np, 1, blocks_of(d.CS, 256), 0);
+          if (s0 > 0) put(0, 1, 1, 1, 0);
         }
         break;
       }
       case kStageEval:
-        for (int sl = 0; sl < P.np; ++sl)
-          for (int b = 0; b < blocks_of(P.E + 1, d.evpb); ++b) put(sl, b, 0);
+        put(0, P.np, 1, blocks_of(P.E + 1, d.evpb), 0);
         break;
       case kStageConv:  // Newton coefficients and segment polynomials, then the basis change:
       case kStageStir:  // tiles of 256 coefficients
-        for (int sl = 0; sl < P.np; ++sl)
-          for (int b = 0; b < blocks_of(P.D + 1, kTile); ++b) put(sl, b, 0);
+        put(0, P.np, 1, blocks_of(P.D + 1, kTile), 0);
         break;
       case kStageNewton:
         // gapped interpolation is possible only with a non-constant leading
         // coefficient (bad points) or a shifted origin
-        if (P.origin != 0 || (!P.formal && P.s > 0) || d.newton_all)
-          for (int sl = 0; sl < P.np; ++sl) put(sl, 0, 0);
+        if (P.origin != 0 || (!P.formal && P.s > 0) || d.newton_all) put(0, P.np, 1, 1, 0);
         break;
       case kStageCrt:
-        if (!P.wide)
-          for (int b = 0; b < blocks_of(P.D + 1, J->crt_mm ? kCrtMmRows : kCrtWaves); ++b) put(-1, b, 0);
+        if (!P.wide) put(-1, 0, 1, blocks_of(P.D + 1, J->crt_mm ? kCrtMmRows : kCrtWaves), 0);
         break;
     }
     return c;
@@ -395,9 +396,8 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     constexpr int kLists = kNumStages;
     std::vector<int>& cnt = J->tmp_a;
     cnt.assign(static_cast<size_t>(nl) * kLists, 0);
-    parallel_for(nl, 16, [&](int li) {
+    for (int li = 0; li < nl; ++li)
       for (int s = 0; s < kLists; ++s) cnt[static_cast<size_t>(li) * kLists + s] = emit(li, s, nullptr);
-    });
     std::vector<int>& off = J->tmp_b;
     off.assign(cnt.size(), 0);
     // the evaluation items grouped by layout variant and the reduce items by kind
@@ -428,7 +428,9 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       J->items[s].clear();
       J->items[s].resize(o);
     }
-    parallel_for(nl, 16, [&](int li) {
+    double total = 0.0;
+    for (int s = 0; s < kLists; ++s) total += J->items[s].size();
+    parallel_for(nl, host_grain(50.0 + 3.0 * total / std::max(nl, 1)), [&](int li) {
       ProbLayout& L = J->lay[li];
       for (int s = 0; s < kLists; ++s) {
         const size_t at = static_cast<size_t>(li) * kLists + s;
@@ -501,43 +503,59 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     // instead of eight.  Per variant range: the g-th (problem, prime) of the
     // range goes to bin g mod 8, and launch position t takes the next item of
     // bin t mod 8 (of the bin with the most items left once that one is empty).
-    // The ranges are independent: one host thread each.
+    // Each bin is a cursor over the range's problems, so an item costs a few
+    // instructions and no memory but its own; the ranges are independent.
     constexpr int kXcds = 8;
     J->eval_staged.resize(ev.size());
-    std::vector<int>& bin = J->tmp_a;
-    std::vector<int>& order = J->tmp_b;  // items of the range by bin, stable
-    bin.resize(ev.size());
-    order.resize(ev.size());
-    parallel_for(static_cast<int>(J->eval_ranges.size()), 1, [&](int ri) {
-      const size_t b0 = static_cast<size_t>(J->eval_ranges[ri].begin), b1 = static_cast<size_t>(J->eval_ranges[ri].end);
-      size_t bsize[kXcds] = {}, bstart[kXcds + 1] = {}, pos[kXcds] = {};
-      int pairs_seen = -1, last_prob = -1, last_slot = -1;
-      for (size_t t = b0; t < b1; ++t) {
-        if (ev[t].prob != last_prob || ev[t].slot != last_slot) {
-          ++pairs_seen;
-          last_prob = ev[t].prob;
-          last_slot = ev[t].slot;
+    parallel_for(static_cast<int>(J->eval_ranges.size()), host_grain(4.0 * ev.size() / std::max<size_t>(1, J->eval_ranges.size())),
+                 [&](int ri) {
+      const auto& R = J->eval_ranges[ri];
+      struct Bin {
+        int li, slot, blk, nb, np;  // the next item; blocks and primes of its problem
+        int64_t left;               // items of the bin
+      } bin[kXcds] = {};
+      auto settle = [&](Bin& B) {  // slots past a problem's end are the next problem's
+        while (B.li < nl && (J->tmp_c[B.li] != R.variant || B.slot >= J->dev[B.li].np)) {
+          if (J->tmp_c[B.li] == R.variant) B.slot -= J->dev[B.li].np;
+          ++B.li;
         }
-        bin[t] = pairs_seen % kXcds;
-        ++bsize[bin[t]];
+        if (B.li < nl) {
+          B.np = J->dev[B.li].np;
+          B.nb = blocks_of(J->dev[B.li].E + 1, J->dev[B.li].evpb);
+        }
+      };
+      int g = 0;  // (problem, prime) groups before this problem, mod 8
+      for (int li = 0; li < nl; ++li) {
+        if (J->tmp_c[li] != R.variant) continue;
+        const int np = J->dev[li].np, nb = blocks_of(J->dev[li].E + 1, J->dev[li].evpb);
+        for (int x = 0; x < kXcds; ++x)
+          bin[x].left += static_cast<int64_t>((np + 7 - (x - g + kXcds) % kXcds) / kXcds) * nb;
+        g = (g + np) % kXcds;
       }
-      for (int x = 0; x < kXcds; ++x) bstart[x + 1] = bstart[x] + bsize[x];
-      {
-        size_t fill[kXcds];
-        for (int x = 0; x < kXcds; ++x) fill[x] = bstart[x];
-        for (size_t t = b0; t < b1; ++t) order[b0 + fill[bin[t]]++] = static_cast<int>(t);
+      for (int x = 0; x < kXcds; ++x) {
+        bin[x].slot = x;
+        settle(bin[x]);
       }
-      for (size_t t = b0; t < b1; ++t) {
-        int x = static_cast<int>((t - b0) % kXcds);
-        if (pos[x] >= bsize[x]) {  // bin x is empty: take from the fullest
-          size_t best = 0;
+      WorkItem* out = J->eval_staged.data() + R.begin;
+      const int total = R.end - R.begin;
+      for (int t = 0; t < total; ++t) {
+        int x = t % kXcds;
+        if (bin[x].left == 0) {  // bin x is empty: take from the fullest
+          int64_t best = 0;
           for (int y = 0; y < kXcds; ++y)
-            if (bsize[y] - pos[y] > best) {
-              best = bsize[y] - pos[y];
+            if (bin[y].left > best) {
+              best = bin[y].left;
               x = y;
             }
         }
-        J->eval_staged[t] = ev[order[b0 + bstart[x] + pos[x]++]];
+        Bin& B = bin[x];
+        --B.left;
+        out[t] = WorkItem{B.li, B.slot, B.blk, 0};
+        if (++B.blk == B.nb) {
+          B.blk = 0;
+          B.slot += kXcds;
+          if (B.slot >= B.np) settle(B);
+        }
       }
     });
   }
@@ -776,7 +794,9 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
   J->image = image;
   uint8_t* blob = image;
   // each problem writes its own regions (a shared CRT block only by its owner)
-  parallel_for(nl, 8, [&](int li) {
+  double words = 0.0;
+  for (int li = 0; li < nl; ++li) words += static_cast<double>(J->dev[li].ncoef) * J->lay[li].L_in;
+  parallel_for(nl, host_grain(300.0 + 2.0 * words / std::max(nl, 1)), [&](int li) {
     const Plan& P = J->plans[J->live[li]];
     const ProbLayout& L = J->lay[li];
     DevProblem& d = J->dev[li];
@@ -1099,25 +1119,47 @@ int job_download(rsl_ctx* ctx, Job* J, uint8_t* host, hipStream_t st) {
 int job_decode(rsl_ctx* ctx, const Job& J, const uint8_t* host, rsl_result* out, int* status, rsl_counters* cnt) {
   std::vector<int> li_of(J.n, -1);
   for (size_t li = 0; li < J.live.size(); ++li) li_of[J.live[li]] = static_cast<int>(li);
-  // results are independent per problem: decode them on host threads, then
-  // gather counters and the first error in problem order
+  // statuses and degrees first; then the coefficients in blocks of about 64 KiB
+  // over host threads, each read once (limbs needed and copy); then counters and
+  // the first error in problem order
   std::vector<int> rcs(J.n, RSL_OK);
-  parallel_for(J.n, 16, [&](int k) {
-    int rc = J.pstatus[k];
+  struct Rows { int k, lo, hi, need; };
+  std::vector<Rows> rows;
+  std::vector<int> deg(J.n, -1);
+  constexpr int kRowWords = 1 << 14;
+  double words = 0.0;
+  auto limbs_of = [&](int k) {
+    return reinterpret_cast<const uint32_t*>(host + (J.lay[li_of[k]].out - J.down_off));
+  };
+  for (int k = 0; k < J.n; ++k) {
     const Plan& P = J.plans[k];
-    if (!rc) {
-      if (P.zero) {
-        rc = decode_result(P, nullptr, &out[k]);
-      } else {
-        const ProbLayout& L = J.lay[li_of[k]];
-        const int* st = reinterpret_cast<const int*>(host + (L.status - J.down_off));
-        if (st[0] & kErrQueueStall) rc = RSL_EDEVICE;
-        else if (st[0] & kErrTooFewGoodPoints) rc = RSL_EPRIMES;
-        else rc = decode_result(P, reinterpret_cast<const uint32_t*>(host + (L.out - J.down_off)), &out[k]);
-      }
+    rcs[k] = J.pstatus[k];
+    if (rcs[k] || P.zero) {
+      if (!rcs[k]) rcs[k] = decode_result(P, nullptr, &out[k]);
+      continue;
     }
-    rcs[k] = rc;
-  });
+    const int* st = reinterpret_cast<const int*>(host + (J.lay[li_of[k]].status - J.down_off));
+    if (st[0] & kErrQueueStall) { rcs[k] = RSL_EDEVICE; continue; }
+    if (st[0] & kErrTooFewGoodPoints) { rcs[k] = RSL_EPRIMES; continue; }
+    deg[k] = result_degree(limbs_of(k), P.D, P.L_out);
+    const int step = std::max(1, kRowWords / P.L_out);
+    for (int lo = 0; lo <= deg[k]; lo += step) rows.push_back({k, lo, std::min(deg[k] + 1, lo + step), 1});
+    if (deg[k] < 0) rows.push_back({k, 0, 0, 1});
+    words += (deg[k] + 1.0) * P.L_out;
+  }
+  parallel_for(static_cast<int>(rows.size()),
+               std::max(1, static_cast<int>(rows.size() * static_cast<double>(kRowWords) / std::max(words, 1.0))),
+               [&](int i) {
+                 Rows& r = rows[i];
+                 const int L = J.plans[r.k].L_out;
+                 r.need = take_rows(limbs_of(r.k), L, r.lo, r.hi, &out[r.k], result_roomy(&out[r.k], L, deg[r.k]));
+               });
+  for (size_t i = 0; i < rows.size();) {
+    const int k = rows[i].k, L = J.plans[k].L_out;
+    int need = 1;
+    for (; i < rows.size() && rows[i].k == k; ++i) need = std::max(need, rows[i].need);
+    rcs[k] = finish_result(limbs_of(k), L, deg[k], need, result_roomy(&out[k], L, deg[k]), &out[k]);
+  }
   int first = RSL_OK;
   for (int k = 0; k < J.n; ++k) {
     const int rc = rcs[k];

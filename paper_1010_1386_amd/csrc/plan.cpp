@@ -132,7 +132,14 @@ int make_view(const rsl_poly* f, int var, View* v, std::string* err) {
   v->rdeg = rdeg;
   const int row = v->dx + 1;
   v->c.assign(static_cast<size_t>(v->dy + 1) * row * L, 0u);
-  v->row_l1.assign(v->dy + 1, BigU());
+  // rows of at most 60 bits (the usual case) are squared and summed in 128 bits
+  unsigned __int128 sq = 0;
+  auto big128 = [](unsigned __int128 x) {
+    BigU t;
+    for (; x; x >>= 32) t.d.push_back(static_cast<uint32_t>(x));
+    return t;
+  };
+  v->sq = BigU();
   for (int j = 0; j <= v->dy; ++j) {
     if (v->rdeg[j] < 0) continue;
     if (var == RSL_Y) {
@@ -156,19 +163,24 @@ int make_view(const rsl_poly* f, int var, View* v, std::string* err) {
           acc += (u >> 63) ? (~u + 1) : u;  // |INT64_MIN| = 2^63 as unsigned
         }
       }
-      BigU t;
-      for (int q = 0; q < 4 && acc; ++q) {
-        t.d.push_back(static_cast<uint32_t>(acc));
-        acc >>= 32;
+      if (acc >> 60) {
+        const BigU t = big128(acc);
+        v->sq = BigU::add(v->sq, BigU::mul(t, t));
+      } else {
+        sq += acc * acc;
+        if (sq >> 127) {
+          v->sq = BigU::add(v->sq, big128(sq));
+          sq = 0;
+        }
       }
-      v->row_l1[j] = t;
     } else {
       BigU t;
       for (int i = 0; i <= v->rdeg[j]; ++i)
         t = BigU::add(t, abs_limbs(&v->c[(static_cast<size_t>(j) * row + i) * L], L, nullptr));
-      v->row_l1[j] = t;
+      v->sq = BigU::add(v->sq, BigU::mul(t, t));
     }
   }
+  if (sq) v->sq = BigU::add(v->sq, big128(sq));
   v->lc_abs.assign(v->rdeg[v->dy] + 1, BigU());
   v->lc_neg.assign(v->rdeg[v->dy] + 1, 0);
   for (int i = 0; i <= v->rdeg[v->dy]; ++i) {
@@ -441,13 +453,20 @@ class HostPool {
       std::lock_guard<std::mutex> lk(mu_);
       q_.push_back(t);
     }
-    cv_.notify_all();
+    // the caller wakes two workers, and each of those two more while blocks are
+    // left: nobody pays for a wake-up that finds no work
+    wake(*t);
     work(*t);
     std::unique_lock<std::mutex> lk(t->m);
     t->done.wait(lk, [&] { return t->left.load() == 0; });
   }
 
  private:
+  void wake(const Task& t) {
+    const int blocks = (t.n - t.next.load() + t.grain - 1) / t.grain;
+    if (blocks > 0) cv_.notify_one();
+    if (blocks > 1) cv_.notify_one();
+  }
   void work(Task& t) {
     for (;;) {
       const int b = t.next.fetch_add(t.grain);
@@ -472,6 +491,7 @@ class HostPool {
           continue;
         }
       }
+      wake(*t);
       work(*t);
     }
   }
@@ -508,6 +528,34 @@ void parallel_for(int n, int grain, const std::function<void(int)>& fn, int thre
   static HostPool* pool = new HostPool(host_threads() - 1);
   pool->run(fn, n, grain);
 }
+
+int host_grain(double ns) { return std::max(1, static_cast<int>(20000.0 / std::max(ns, 1.0))); }
+
+namespace {
+
+// Which of the primes p[0..n-1] (n <= 8) may divide a: Montgomery reduction of a
+// from its lowest limb, without divisions, the primes side by side.
+uint32_t maybe_divides(const BigU& a, const uint32_t* p, int n) {
+  uint64_t t[8] = {}, m[8] = {};
+  uint32_t ninv[8] = {};
+  for (int q = 0; q < n; ++q) {
+    uint32_t x = p[q];  // p^-1 mod 2^3, then 6, 12, 24, 48 bits
+    for (int it = 0; it < 4; ++it) x *= 2u - p[q] * x;
+    m[q] = p[q];
+    ninv[q] = 0u - x;
+  }
+  for (const uint32_t w : a.d)
+    for (int q = 0; q < 8; ++q) {
+      const uint64_t s = t[q] + w;  // t < 2^32
+      t[q] = (s + static_cast<uint64_t>(static_cast<uint32_t>(s) * ninv[q]) * m[q]) >> 32;
+    }
+  uint32_t flags = 0;
+  for (int q = 0; q < n; ++q)
+    if (t[q] % p[q] == 0) flags |= 1u << q;
+  return flags;
+}
+
+}  // namespace
 
 int make_plan(const rsl_poly* f, const rsl_poly* g, int var, const rsl_opts* opts, Plan* P,
               std::string* err) {
@@ -567,12 +615,7 @@ int make_plan(const rsl_poly* f, const rsl_poly* g, int var, const rsl_opts* opt
   // on log2 values in double precision (relative error far below 1e-12) and
   // falls back to exact big integers only when the two sides are within a
   // safety margin of each other, so the prime count is the exact minimum.
-  auto row_sq_sum = [](const View& V) {
-    BigU S;
-    for (int j = 0; j <= V.dy; ++j) S = BigU::add(S, BigU::mul(V.row_l1[j], V.row_l1[j]));
-    return S;
-  };
-  const BigU Sf = row_sq_sum(F), Sg = row_sq_sum(G);
+  const BigU &Sf = F.sq, &Sg = G.sq;
   auto log2_of = [](const BigU& a) {
     if (a.is_zero()) return 0.0;
     const int nb = a.bitlen();
@@ -601,6 +644,17 @@ int make_plan(const rsl_poly* f, const rsl_poly* g, int var, const rsl_opts* opt
       if (a.mod_small(p) != 0) return false;
     return true;
   };
+  // a prime is bad only if it divides the shortest nonzero coefficient, and the
+  // primes exceed 2^30: eight primes at a time are tested against that one
+  auto shortest = [](const View& V) -> const BigU* {
+    const BigU* s = nullptr;
+    for (const BigU& a : V.lc_abs)
+      if (!a.is_zero() && (!s || a.d.size() < s->d.size())) s = &a;
+    return (s && s->bitlen() > 30) ? s : nullptr;
+  };
+  const BigU *sf = shortest(F), *sg = shortest(G);
+  size_t tested = 0;  // primes below this index have their flag
+  uint32_t maybe_bad = 0;
   const size_t limit = o.prime_limit ? static_cast<size_t>(o.prime_limit) : kPrimeTableMax;
   double lm = 0.0;  // log2(M)
   P->pidx.clear();
@@ -619,7 +673,15 @@ int make_plan(const rsl_poly* f, const rsl_poly* g, int var, const rsl_opts* opt
       return RSL_EPRIMES;
     }
     uint32_t p = tab[k];
-    if (lc_vanishes(F, p) || lc_vanishes(G, p)) {
+    if ((sf || sg) && k >= tested) {
+      tab = prime_table(k + 8, &have);
+      const int nt = static_cast<int>(std::min<size_t>(8, have - k));
+      maybe_bad = (sf ? maybe_divides(*sf, tab + k, nt) : 0u) | (sg ? maybe_divides(*sg, tab + k, nt) : 0u);
+      tested = k + nt;
+    } else {
+      maybe_bad >>= 1;
+    }
+    if ((maybe_bad & 1u) && (lc_vanishes(F, p) || lc_vanishes(G, p))) {
       ++P->bad_primes;
       continue;
     }

@@ -33,7 +33,7 @@ struct View {
   int L = 1;                // limbs per coefficient
   std::vector<int> rdeg;    // per-row x-degree, -1 for a zero row
   std::vector<uint32_t> c;  // rows 0..dy, cols 0..dx, L limbs each (two's complement)
-  std::vector<BigU> row_l1; // per row j: ||f_j||_1, the sum of |coefficient| (planning only)
+  BigU sq;                  // sum_j ||f_j||_1^2 over the rows, ||f_j||_1 the sum of |coefficient| (planning only)
   std::vector<BigU> lc_abs; // |coefficient| of the leading row (bad-prime screen)
   std::vector<uint8_t> lc_neg;  // its signs
 };
@@ -112,8 +112,14 @@ struct ShapeEst {
 ShapeEst estimate_shape(const rsl_poly* f, const rsl_poly* g, int var);
 
 // Run fn(i) for i in [0, n) on up to `threads` host threads (0: the default,
-// at most 16); blocks of `grain` consecutive indices per task.
+// at most 16); blocks of `grain` consecutive indices per task, on the calling
+// thread alone when there is only one.
 void parallel_for(int n, int grain, const std::function<void(int)>& fn, int threads = 0);
+// The grain for items of `ns` nanoseconds each: waking a worker takes 5 to 10 us,
+// so a block holds about 20 us of work (61 small systems planned, laid out and
+// decoded: 360 us of host time in blocks of 4 to 32 with every worker woken each
+// time, 182 us so).
+int host_grain(double ns);
 
 // CRT tables for an ordered prime list (Garner constants and prefix products).
 //   Tg[j*np + i] = (prod_{l<j} p_l mod p_i) R mod p_i          (j < i)

@@ -94,17 +94,6 @@ int norm2_bits(const UPoly& u) {
   return (s.bitlen() + 2) / 2;
 }
 
-uint64_t powmod(uint64_t a, uint64_t e, uint64_t m) {
-  uint64_t r = 1 % m;
-  a %= m;
-  while (e) {
-    if (e & 1) r = r * a % m;
-    a = a * a % m;
-    e >>= 1;
-  }
-  return r;
-}
-
 int bitlen_i(int64_t v) {
   int b = 0;
   while (v > 0) {
@@ -123,6 +112,7 @@ struct Dev {
   bool bad = false;
   std::vector<uint8_t> host;  // staged bytes of [lo, hi)
   size_t lo = 0, hi = 0;
+  size_t staged = 0;          // pinned bytes that copies of this call may still read
   template <class T>
   T* take(size_t count) {
     const size_t at = align_up(used, 256), bytes = sizeof(T) * std::max<size_t>(count, 1);
@@ -153,12 +143,19 @@ int flush(rsl_ctx* ctx, Dev* D) {
   if (D->bad) return fail(ctx, RSL_ENOMEM, "workspace smaller than the gcd footprint");
   if (D->hi == D->lo) return RSL_OK;
   const size_t n = D->hi - D->lo;
-  // the pinned buffer may still feed an earlier copy of this call
-  int rc = hip_check(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-  if (!rc) rc = ensure_staging(ctx, n, 0);
-  if (rc) return rc;
-  std::memcpy(ctx->h_up, D->host.data(), n);
-  rc = hip_check(ctx, hipMemcpyAsync(D->base + D->lo, ctx->h_up, n, hipMemcpyHostToDevice, ctx->stream), "upload");
+  // each copy has its own part of the pinned buffer, so the stream is waited for
+  // only by the call's first one and when the buffer is used up
+  int rc = RSL_OK;
+  if (D->staged == 0 || D->staged + n > ctx->h_up_bytes) {
+    rc = hip_check(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+    if (!rc) rc = ensure_staging(ctx, n, 0);
+    if (rc) return rc;
+    D->staged = 0;
+  }
+  std::memcpy(ctx->h_up + D->staged, D->host.data(), n);
+  rc = hip_check(ctx, hipMemcpyAsync(D->base + D->lo, ctx->h_up + D->staged, n, hipMemcpyHostToDevice, ctx->stream),
+                 "upload");
+  D->staged += align_up(n, 256);
   D->host.clear();
   D->lo = D->hi = 0;
   return rc;
@@ -298,17 +295,19 @@ int run_crt(rsl_ctx* ctx, Dev* D, const std::vector<DevProblem>& probs) {
 }
 
 int download(rsl_ctx* ctx, void* dst, const void* src, size_t bytes) {
-  int rc = hip_check(ctx, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, ctx->stream), "download");
-  if (rc) return rc;
-  return hip_check(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+  int rc = ensure_staging(ctx, 0, bytes);  // no copy is in flight to it: every download waits
+  if (!rc) rc = hip_check(ctx, hipMemcpyAsync(ctx->h_down, src, bytes, hipMemcpyDeviceToHost, ctx->stream), "download");
+  if (!rc) rc = hip_check(ctx, hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
+  if (!rc) std::memcpy(dst, ctx->h_down, bytes);
+  return rc;
 }
 
 // bit length of the largest |coefficient| of a CRT output ((D+1) x L limbs)
-int max_bits(const std::vector<uint32_t>& limbs, int D, int L) {
+int max_bits(const uint32_t* limbs, int D, int L) {
   int b = 0;
   for (int k = 0; k <= D; ++k) {
     bool n;
-    b = std::max(b, abs_limbs(limbs.data() + static_cast<size_t>(k) * L, L, &n).bitlen());
+    b = std::max(b, abs_limbs(limbs + static_cast<size_t>(k) * L, L, &n).bitlen());
   }
   return b;
 }
@@ -321,7 +320,7 @@ void put_zero(rsl_result* r) {
 }
 
 // CRT output limbs ((D + 1) x L) as a trimmed polynomial
-UPoly as_upoly(const std::vector<uint32_t>& limbs, int D, int L) {
+UPoly as_upoly(const uint32_t* limbs, int D, int L) {
   UPoly r;
   r.L = L;
   r.deg = D;
@@ -331,7 +330,7 @@ UPoly as_upoly(const std::vector<uint32_t>& limbs, int D, int L) {
     return false;
   };
   while (r.deg >= 0 && !nonzero(r.deg)) --r.deg;
-  r.c.assign(limbs.begin(), limbs.begin() + static_cast<size_t>(r.deg + 1) * L);
+  r.c.assign(limbs, limbs + static_cast<size_t>(r.deg + 1) * L);
   return r;
 }
 
@@ -367,8 +366,8 @@ UPoly sub_upoly(const UPoly& x, const UPoly& y) {
     }
   }
   r.deg = n;
-  std::vector<uint32_t> tmp = r.c;
-  return as_upoly(tmp, n, r.L);
+  const std::vector<uint32_t> tmp = r.c;
+  return as_upoly(tmp.data(), n, r.L);
 }
 
 // G = gcd(pp(u), pp(v)), A = u / G, B = v / G (see the file comment)
@@ -546,42 +545,42 @@ int gcd_core(rsl_ctx* ctx, const UPoly& u, const UPoly& v, UPoly* gout, UPoly* u
     bool lneg;
     (void)abs_limbs(gt.data() + static_cast<size_t>(dg) * L, L, &lneg);
     if (s.is_zero()) return fail(ctx, RSL_EDEVICE, "modular gcd: zero scaled gcd");
-    std::vector<uint32_t> sinv(nk);
+    std::vector<uint32_t> smod(nk);  // signed content mod p, inverted on the device
     for (int i = 0; i < nk; ++i) {
       const uint32_t p = tab[kpidx[i]];
       uint64_t sm = s.mod_small(p);
       if (lneg) sm = (p - sm) % p;
       if (sm == 0) return fail(ctx, RSL_EDEVICE, "modular gcd: content divisible by a kept prime");
-      sinv[i] = static_cast<uint32_t>(powmod(sm, p - 2, p));
+      smod[i] = static_cast<uint32_t>(sm);
     }
-    uint32_t* dsinv = nullptr;
-    if ((rc = upload_vec(ctx, &D, sinv, &dsinv))) return rc;
-    Z.sinv = dsinv;
+    uint32_t* dsmod = nullptr;
+    if ((rc = upload_vec(ctx, &D, smod, &dsmod))) return rc;
+    Z.smod = dsmod;
+    // the results side by side, the remainder flag first (uploaded with the
+    // contents): one copy back
+    const int na = nu - dg, nb = nv - dg;
+    const size_t wg = static_cast<size_t>(dg + 1) * L, wa = static_cast<size_t>(na + 1) * L,
+                 wb = static_cast<size_t>(std::max(nb, 0) + 1) * L;
+    constexpr size_t kFlagWords = 64;
+    uint32_t* res = D.take<uint32_t>(kFlagWords + wg + wa + wb);
+    if (!res) return fail(ctx, RSL_ENOMEM, "workspace smaller than the gcd footprint");
+    Z.rem = reinterpret_cast<int*>(res);
+    uint32_t *outg = res + kFlagWords, *outa = outg + wg, *outb = outa + wa;
+    const int zero = 0;
+    D.put(Z.rem, &zero, 4);
     Z.cg = D.take<uint64_t>(static_cast<size_t>(nk) * (dg + 1));
     Z.ca = D.take<uint64_t>(static_cast<size_t>(nk) * (nu - dg + 1));
     Z.cb = D.take<uint64_t>(static_cast<size_t>(nk) * std::max(nv - dg + 1, 1));
-    Z.rem = D.take<int>(1);
-    const int na = nu - dg, nb = nv - dg;
-    uint32_t* outg = D.take<uint32_t>(static_cast<size_t>(dg + 1) * L);
-    uint32_t* outa = D.take<uint32_t>(static_cast<size_t>(na + 1) * L);
-    uint32_t* outb = D.take<uint32_t>(static_cast<size_t>(std::max(nb, 0) + 1) * L);
     std::vector<DevProblem> p1{crt_problem(ctx, &D, C, dg, Z.cg, outg), crt_problem(ctx, &D, C, na, Z.ca, outa)};
     if (nv >= 0) p1.push_back(crt_problem(ctx, &D, C, nb, Z.cb, outb));
     if (D.bad) return fail(ctx, RSL_ENOMEM, "workspace smaller than the gcd footprint");
-    const int zero = 0;
-    D.put(Z.rem, &zero, 4);
     if ((rc = flush(ctx, &D)) || (rc = hip_check(ctx, launch_zgcd_pass(3, Z, nullptr, 0, T, ctx->stream), "zcof")) ||
         (rc = run_crt(ctx, &D, p1)))
       return rc;
-    std::vector<uint32_t> g(static_cast<size_t>(dg + 1) * L), a(static_cast<size_t>(na + 1) * L), b;
-    int remv = 0;
-    if ((rc = download(ctx, g.data(), outg, g.size() * 4)) || (rc = download(ctx, a.data(), outa, a.size() * 4)) ||
-        (rc = download(ctx, &remv, Z.rem, 4)))
-      return rc;
-    if (nv >= 0) {
-      b.resize(static_cast<size_t>(nb + 1) * L);
-      if ((rc = download(ctx, b.data(), outb, b.size() * 4))) return rc;
-    }
+    std::vector<uint32_t> all(kFlagWords + wg + wa + (nv >= 0 ? wb : 0));
+    if ((rc = download(ctx, all.data(), res, all.size() * 4))) return rc;
+    const int remv = static_cast<int>(all[0]);
+    const uint32_t *g = all.data() + kFlagWords, *a = g + wg, *b = a + wa;
     // certificate
     if (remv || max_bits(g, dg, L) > bG || max_bits(a, na, L) > bA || (nv >= 0 && max_bits(b, nb, L) > bB))
       continue;  // all kept primes unlucky (vanishingly rare): more primes

@@ -37,7 +37,7 @@ struct ZgcdDesc {
   // kept slots (least gcd degree)
   int nk, dg;           // kept slots, degree of G
   const int* kept;      // nk slot indices
-  const uint32_t* sinv; // nk: (signed content of the scaled gcd)^{-1} mod p, normal form
+  const uint32_t* smod; // nk: signed content of the scaled gcd mod p, normal form
   uint64_t* c0;         // nk * (dg + 1): scaled gcd, CRT input layout (Montgomery form)
   uint64_t* cg;         // nk * (dg + 1): G mod p
   uint64_t* ca;         // nk * (nu - dg + 1): u / G mod p
@@ -79,10 +79,13 @@ __device__ inline int zdeg_below(const uint32_t* a, int d) {
 // once, as in the evaluation,
 //   A[j] <- L^2 A[j] - L lc(A) B[j-1] - (L A[b] - lc(A) B[b-1]) B[j],  L = lc(B),
 // with one barrier: a step's scalars and every B[j] come from entries it does
-// not write.  Bound by the latency of a step (LDS reads, the scalars' products,
-// the barrier), 0.32 us each: 115 us for a polynomial of degree 360 and its
-// derivative on all primes; one wave per prime with one elimination per pass
-// took 326 us, as six coefficients a lane went through every step in turn.
+// not write.  Bound by the latency of a step, so a step is one LDS round trip
+// (a thread's first kZHold entries are read together with the scalars' operands)
+// and one product for all three scalars, a lane each.  A polynomial of degree 360
+// and its derivative: 92 us, 0.25 us a step (115 us with the scalars as three
+// products and the entries read after them; 326 us with one wave per prime and
+// one elimination per pass, six coefficients a lane going through every step).
+constexpr int kZHold = 2;
 __device__ inline void stage_zgcd(const ZgcdDesc& Z, const DevTables& T, int slot, uint32_t* lds) {
   const int tid = threadIdx.x, nt = blockDim.x;
   const PrimeConst pc = T.pc[Z.pidx[slot]];
@@ -101,15 +104,37 @@ __device__ inline void stage_zgcd(const ZgcdDesc& Z, const DevTables& T, int slo
     const int d = da; da = db; db = d;
   }
   while (db > 0) {
-    const uint32_t L = B[db];
-    int dr;
     if (da == db + 1) {
-      const uint32_t lcA = A[da], lcAt = mmulsub(L, A[db], lcA, B[db - 1], p, pinv);
-      const uint32_t al = mmul(L, L, p, pinv), be = p - mmul(L, lcA, p, pinv), ga = p - lcAt;
-      for (int j = tid; j < db; j += nt) A[j] = mmad3(al, A[j], be, j > 0 ? B[j - 1] : 0u, ga, B[j], p, pinv);
+      uint32_t av[kZHold], bv[kZHold], bl[kZHold];
+#pragma unroll
+      for (int r = 0; r < kZHold; ++r) {
+        const int j = tid + r * nt, jj = j < db ? j : 0;
+        av[r] = A[jj];
+        bv[r] = B[jj];
+        bl[r] = B[jj > 0 ? jj - 1 : 0];
+      }
+      const uint32_t L = B[db], lcA = A[da], Ab = A[db], Bb = B[db - 1];
+      if (L == 0u) {  // the last remainder dropped by more than one degree
+        db = zdeg_below(B, db);
+        continue;
+      }
+      // lane 0: L L, lane 1: -L lc(A), lane 2: lc(A) B[b-1] - L A[b], as x y - u w
+      const int ln = tid & 3;
+      const uint32_t v = mmulsub(ln == 0 ? L : ln == 1 ? 0u : lcA, ln == 0 ? L : Bb, ln == 0 ? 0u : L, ln == 1 ? lcA : Ab,
+                                 p, pinv);
+      const uint32_t al = __builtin_amdgcn_readlane(v, 0), be = __builtin_amdgcn_readlane(v, 1),
+                     ga = __builtin_amdgcn_readlane(v, 2);
+#pragma unroll
+      for (int r = 0; r < kZHold; ++r) {
+        const int j = tid + r * nt;
+        if (j < db) A[j] = mmad3(al, av[r], be, j > 0 ? bl[r] : 0u, ga, bv[r], p, pinv);
+      }
+      for (int j = tid + kZHold * nt; j < db; j += nt) A[j] = mmad3(al, A[j], be, B[j - 1], ga, B[j], p, pinv);
       __syncthreads();
-      dr = A[db - 1] != 0u ? db - 1 : zdeg_below(A, db - 1);
+      da = db;
+      db -= 1;  // at most: the next step sees a zero leading coefficient
     } else {
+      const uint32_t L = B[db];
       for (int d = da; d >= db; --d) {
         const uint32_t la = A[d];
         const int s = d - db;
@@ -117,13 +142,12 @@ __device__ inline void stage_zgcd(const ZgcdDesc& Z, const DevTables& T, int slo
           A[j] = (j >= s) ? mmulsub(L, A[j], la, B[j - s], p, pinv) : mmul(L, A[j], p, pinv);
         __syncthreads();
       }
-      dr = zdeg_below(A, db);
+      da = db;
+      db = zdeg_below(A, db);
     }
     uint32_t* t = A; A = B; B = t;
-    da = db;
-    db = dr;
   }
-  if (db == 0) {  // a nonzero constant: the gcd
+  if (db == 0 && B[0] != 0u) {  // a nonzero constant: the gcd
     A = B;
     da = 0;
   }
@@ -151,23 +175,39 @@ __host__ __device__ inline int zcof_lds_words(const ZgcdDesc& Z) {
 // Long division of W (degree n, Montgomery) by G (degree dg, Montgomery,
 // inverse leading coefficient ginv): quotient coefficients to q[0..n-dg]
 // (Montgomery form, the CRT input layout), remainder check.  One barrier per
-// quotient coefficient.
-__device__ inline void zdivide(uint32_t* W, int n, const uint32_t* G, int dg, uint32_t ginv, uint64_t* q,
+// quotient coefficient; the row taken off is W[k+dg] (G / lc G), one product
+// behind the barrier, and a thread's first kZHold entries of G / lc G stay in
+// registers.
+__device__ inline void zdivide(uint32_t* W, int n, uint32_t* G, int dg, uint32_t ginv, uint64_t* q,
                                int* rem, const PrimeConst& pc) {
   const uint32_t p = pc.p, pinv = pc.pinv;
   const int tid = threadIdx.x, nt = blockDim.x;
+  __syncthreads();  // every thread has read lc G
+  for (int j = tid; j < dg; j += nt) G[j] = mmul(G[j], ginv, p, pinv);
+  uint32_t gv[kZHold];
+#pragma unroll
+  for (int r = 0; r < kZHold; ++r) gv[r] = tid + r * nt < dg ? G[tid + r * nt] : 0u;
   for (int k = n - dg; k >= 0; --k) {
-    const uint32_t qk = mmul(W[k + dg], ginv, p, pinv);
-    if (tid == 0) q[k] = qk;
-    for (int j = tid; j < dg; j += nt) W[k + j] = msubm(W[k + j], mmul(qk, G[j], p, pinv), p);
+    uint32_t wv[kZHold];
+#pragma unroll
+    for (int r = 0; r < kZHold; ++r) wv[r] = tid + r * nt < dg ? W[k + tid + r * nt] : 0u;
+    const uint32_t top = W[k + dg];
+#pragma unroll
+    for (int r = 0; r < kZHold; ++r)
+      if (tid + r * nt < dg) W[k + tid + r * nt] = msubm(wv[r], mmul(top, gv[r], p, pinv), p);
+    for (int j = tid + kZHold * nt; j < dg; j += nt) W[k + j] = msubm(W[k + j], mmul(top, G[j], p, pinv), p);
     __syncthreads();
   }
+  // the tops stayed where they were; stores inside the loop would each be waited
+  // for at its barrier
+  for (int k = tid; k <= n - dg; k += nt) q[k] = mmul(W[k + dg], ginv, p, pinv);
   if (zdeg_below(W, dg) >= 0 && tid == 0) rem[0] = 1;
 }
 
 // Kept slot i: G mod p, then u / G (part 0) or v / G (part 1), a block each:
 // bound by the latency of a quotient coefficient like the steps above.  Degree
-// 360: 53 us (114 us with one wave per prime and the divisions in turn).
+// 360: 43 us (53 us with two products behind each barrier and the quotient stored
+// as it came; 114 us with one wave per prime and the divisions in turn).
 __device__ inline void stage_zcof(const ZgcdDesc& Z, const DevTables& T, int i, int part, uint32_t* lds) {
   const int tid = threadIdx.x, nt = blockDim.x;
   const int slot = Z.kept[i];
@@ -177,7 +217,7 @@ __device__ inline void stage_zcof(const ZgcdDesc& Z, const DevTables& T, int i, 
   if (n < Z.dg) return;  // v = 0 (no cofactor)
   uint32_t* W = lds;              // n + 1 words
   uint32_t* G = lds + (n + 1);    // dg + 1 words
-  const uint32_t sM = mmul(Z.sinv[i], pc.r2, p, pinv);
+  const uint32_t sM = minv(mmul(Z.smod[i], pc.r2, p, pinv), one, p, pinv);
   for (int k = tid; k <= Z.dg; k += nt) {
     const uint32_t g = mmul(mmul(Z.gt[static_cast<size_t>(slot) * Z.gs + k], pc.r2, p, pinv), sM, p, pinv);
     G[k] = g;

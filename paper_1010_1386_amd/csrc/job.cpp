@@ -445,6 +445,7 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
   for (int pass = 0; pass < 3; ++pass) J->wide_items[pass].clear();
   J->wide_mfma = false;
   J->wdig_items.clear();
+  J->wdig_lds = 0;
   for (int li = 0; li < nl; ++li) {
     const Plan& P = J->plans[J->live[li]];
     const DevProblem& d = J->dev[li];
@@ -587,14 +588,16 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
       const auto own = crt_owner.emplace(P.crt.get(), li);
       L.crt_own = own.second;
       L.crt_from = own.first->second;
-      if (L.crt_own && d.wide_mfma)
+      if (L.crt_own && d.wide_mfma) {
+        J->wdig_lds = std::max(J->wdig_lds, static_cast<size_t>(wide_digits_lds_words(d)) * 4);
         for (int b = 0; b < d.wnpad / kWideMfmaK; ++b)
           for (int t = 0; t < blocks_of(d.wlpad, kWideDigitLimbs); ++t) J->wdig_items.push_back({li, -1, b, t});
+      }
     }
   }
   J->wdig_off = o;
   o = align_up(o + sizeof(WorkItem) * J->wdig_items.size(), A);
-  size_t digit_bytes = 0;
+  size_t digit_bytes = 0, spared_bytes = 0;
   for (int li = 0; li < nl; ++li) {
     const Plan& P = J->plans[J->live[li]];
     const DevProblem& d = J->dev[li];
@@ -611,7 +614,9 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     }
     L.Hm = o;    o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
     L.NH = o;    o = align_up(o + static_cast<size_t>(P.L_out) * 4, 16);
-    L.Mi = o;    o = align_up(o + static_cast<size_t>(P.np) * P.Lw * 4, 16);
+    // (the wide path's matrix products take the M_i from M itself)
+    L.Mi = o;
+    (d.wide_mfma ? spared_bytes : o) += align_up(static_cast<size_t>(P.np) * P.Lw * 4, 16);
     L.Mdig = o;  o = align_up(o + P.crt->dig.size(), 16);
     digit_bytes += P.crt->dig.size();
     L.wdir = o;  o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
@@ -731,8 +736,8 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     J->queue_off = own;
     own = align_up(own + J->queue_bytes, A);
     // (less the limb digits, which the upload image holds in place of the item
-    // lists it had)
-    const size_t counted = own + (apart - o);
+    // lists it had, and with the M_i that are no longer stored)
+    const size_t counted = own + (apart - o) + spared_bytes;
     o = std::max({tiles, segs, own, counted > digit_bytes ? counted - digit_bytes : 0});
   }
   J->total = o;
@@ -835,7 +840,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     if (L.crt_own) {
     std::memcpy(blob + L.Hm, P.crt->Hm.data(), P.np * 4);
     std::memcpy(blob + L.NH, P.crt->NH.data(), P.L_out * 4);
-    std::memcpy(blob + L.Mi, P.crt->Mi.data(), P.crt->Mi.size() * 4);
+    if (!d.wide_mfma) std::memcpy(blob + L.Mi, P.crt->Mi.data(), P.crt->Mi.size() * 4);
     if (!P.crt->dig.empty()) std::memcpy(blob + L.Mdig, P.crt->dig.data(), P.crt->dig.size());
     std::memcpy(blob + L.wdir, P.crt->wdir.data(), P.crt->wdir.size() * 4);
     std::memcpy(blob + L.rinv, P.crt->rinv.data(), P.crt->rinv.size() * 4);
@@ -856,7 +861,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     d.pidx = reinterpret_cast<const int*>(base + L.pidx);
     d.Hm = reinterpret_cast<const uint32_t*>(base + L.Hm);
     d.NH = reinterpret_cast<const uint32_t*>(base + L.NH);
-    d.Mi = reinterpret_cast<const uint32_t*>(base + L.Mi);
+    d.Mi = d.wide_mfma ? nullptr : reinterpret_cast<const uint32_t*>(base + L.Mi);
     d.Mdig = base + L.Mdig;
     d.wdir = reinterpret_cast<const uint32_t*>(base + L.wdir);
     d.rinv = reinterpret_cast<const uint32_t*>(base + L.rinv);
@@ -972,9 +977,12 @@ int job_upload(rsl_ctx* ctx, Job* J, hipStream_t st, uint8_t* pinned) {
 }
 
 int job_upload_digits(rsl_ctx* ctx, Job* J, hipStream_t st) {
+  if (J->wdig_items.empty()) return RSL_OK;
+  const int rc = ensure_tables(ctx, J->need_g, J->need_E, J->need_D);  // the prime constants; a no-op once grown
+  if (rc) return rc;
   return hip_check(ctx, launch_wide_digits(reinterpret_cast<const DevProblem*>(J->base + J->probs_off),
                                            reinterpret_cast<const WorkItem*>(J->base + J->wdig_off),
-                                           static_cast<int>(J->wdig_items.size()), st),
+                                           static_cast<int>(J->wdig_items.size()), J->wdig_lds, tables_of(ctx), st),
                    "wide digits");
 }
 

@@ -56,6 +56,7 @@ struct Job {
   std::vector<WorkItem> wide_items[3];
   bool wide_mfma = false;          // the contraction (pass 1) runs on the matrix cores
   std::vector<WorkItem> wdig_items;  // limb digit planes, built after the upload (64 primes x 64 limbs each)
+  size_t wdig_lds = 0;                 // LDS bytes of its launch
   size_t wdig_off = 0;
   size_t wide_off[3] = {};
   size_t wide_lds[3] = {};

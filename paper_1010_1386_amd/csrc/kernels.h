@@ -33,8 +33,10 @@ hipError_t launch_eval(int variant, const DevProblem* probs, const WorkItem* ite
 hipError_t launch_crt_wide(int pass, const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
                            const DevTables& T, hipStream_t st, bool whole);
 
-// The wide CRT's digit planes of the M_i limbs (items: problem, 64 primes, 64 limbs).
-hipError_t launch_wide_digits(const DevProblem* probs, const WorkItem* items, int nitems, hipStream_t st);
+// The wide CRT's digit planes of the M_i limbs, from M (items: problem, 64 primes,
+// 64 limbs; lds: the most wide_digits_lds_words of its problems, in bytes).
+hipError_t launch_wide_digits(const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
+                              const DevTables& T, hipStream_t st);
 
 // Pass 0 (reduce u, v over `nitems` items), 1 (Euclid per prime slot), 2 (pack
 // the kept scaled gcds) or 3 (G and the cofactors per kept slot) of the modular gcd.

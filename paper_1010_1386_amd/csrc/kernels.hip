@@ -157,15 +157,16 @@ __global__ __launch_bounds__(256) void k_crt_wide_sum_mfma(const DevProblem* pro
   stage_crt_wide_sum_mfma(probs[w.prob], w, reinterpret_cast<uint32_t*>(lds4));
 }
 
-__global__ __launch_bounds__(256) void k_wide_digits(const DevProblem* probs, const WorkItem* items) {
-  __shared__ uint32_t lds[kWideDigitLdsWords];
+__global__ __launch_bounds__(256) void k_wide_digits(const DevProblem* probs, const WorkItem* items, DevTables T) {
+  extern __shared__ uint32_t lds[];
   const WorkItem w = items[blockIdx.x];
-  stage_wide_digits(probs[w.prob], w, lds);
+  stage_wide_digits(probs[w.prob], T, w, lds);
 }
 
-hipError_t launch_wide_digits(const DevProblem* probs, const WorkItem* items, int nitems, hipStream_t st) {
+hipError_t launch_wide_digits(const DevProblem* probs, const WorkItem* items, int nitems, size_t lds,
+                              const DevTables& T, hipStream_t st) {
   if (nitems <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_wide_digits, dim3(nitems), dim3(256), 0, st, probs, items);
+  hipLaunchKernelGGL(k_wide_digits, dim3(nitems), dim3(256), lds, st, probs, items, T);
   return hipGetLastError();
 }
 

@@ -2666,21 +2666,61 @@ constexpr int kWideMfmaTT = 32;  // limbs per block
 __host__ __device__ inline int wide_mfma_lds_words() { return kWideDigits * kWideMfmaTT * kWideMfmaK / 4; }
 typedef int wide_v4i __attribute__((ext_vector_type(4)));
 
-// The digit planes Md[b][t][i] from the rows M_i (limbs contiguous): item
-// (problem, blk = 64 primes, sub = 64 limbs), a transposition through LDS.
-// Each block reads 16 KB of limbs once and writes their five digits as
-// 16-byte words of 16 primes (zero beyond the last prime or limb).  Bound by
-// the launch and the stores.  On the host the same loop cost one scattered
-// byte store per digit and 20 MB more upload: 91 of the 101 ms of a call on
-// ten pairs of degree 15 with 2^2048 coefficients.
+// The digit planes Md[b][t][i] of M_i = M / p_i, from the limbs of M alone: item
+// (problem, blk = 64 primes, sub = 64 limbs).  Limb t of an exact quotient comes
+// from limb t of M and the borrow into it,
+//   q = (m_t - b) / p mod 2^32,  b' = (q p - (m_t - b)) / 2^32,
+// and the borrow into the block's first limb t0 is -(M mod 2^(32 t0)) 2^(-32 t0)
+// mod p: a reduction chain over the limbs below, a quarter of them per wave (a
+// lane per prime), joined by the power 2^(-8 t0).  So every block starts by
+// itself, and the M_i, np times as long as M, are neither uploaded nor stored.
+// Wave 0 then walks the block's 64 limbs, and the digits go out as 16-byte
+// words of 16 primes (zero beyond the last prime or limb).  Bound by the chains'
+// latency, 27 us for 2025 primes and 1925 limbs; as a transposition of uploaded
+// M_i it took 19 us, behind 0.55 ms for their 15.6 MB (image and transfer).
 constexpr int kWideDigitLimbs = 64;
-constexpr int kWideDigitLdsWords = kWideMfmaK * (kWideDigitLimbs + 1);
-__device__ inline void stage_wide_digits(const DevProblem& P, const WorkItem& w, uint32_t* lds) {
+__host__ __device__ inline int wide_digits_lds_words(const DevProblem& P) {
+  return P.wlpad + kWideDigitLimbs + kWideMfmaK * (kWideDigitLimbs + 1) + 4 * kWideMfmaK;
+}
+__device__ inline void stage_wide_digits(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* smem) {
   const int i0 = w.blk * kWideMfmaK, t0 = w.sub * kWideDigitLimbs;
-  for (int e = threadIdx.x; e < kWideMfmaK * kWideDigitLimbs; e += blockDim.x) {
-    const int ii = e / kWideDigitLimbs, tt = e % kWideDigitLimbs;
-    const int i = i0 + ii, t = t0 + tt;
-    lds[ii * (kWideDigitLimbs + 1) + tt] = (i < P.np && t < P.Lw) ? P.Mi[static_cast<size_t>(i) * P.Lw + t] : 0u;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t* lds = smem;                                             // [prime][limb]
+  uint32_t* part = lds + kWideMfmaK * (kWideDigitLimbs + 1);        // [quarter][prime]
+  uint32_t* m32 = part + 4 * kWideMfmaK;                            // limbs of M, zero above
+  for (int t = threadIdx.x; t < t0 + kWideDigitLimbs; t += blockDim.x) m32[t] = t < P.Lw ? P.Mw[t] : 0u;
+  __syncthreads();
+  const bool on = i0 + lane < P.np;
+  const PrimeConst pc = T.pc[P.pidx[on ? i0 + lane : 0]];
+  const uint32_t p = pc.p, pinv = pc.pinv;
+  const int len = t0 / 4;
+  {
+    uint32_t r = 0;  // at most p + 1 between limbs
+    const uint32_t* seg = m32 + wave * len;
+#pragma unroll 4
+    for (int t = 0; t < len; ++t) {
+      const uint64_t x = static_cast<uint64_t>(r) + seg[t];
+      r = static_cast<uint32_t>((x + static_cast<uint64_t>(static_cast<uint32_t>(x) * pinv) * p) >> 32);
+    }
+    part[wave * kWideMfmaK + lane] = r >= p ? r - p : r;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const uint32_t f = mpow(1u, static_cast<uint32_t>(len), pc.r1, p, pinv);  // 2^(-32 len), Montgomery form
+    uint32_t r = part[lane];
+#pragma unroll
+    for (int j = 1; j < 4; ++j) {
+      r = mmul(r, f, p, pinv) + part[j * kWideMfmaK + lane];
+      r = r >= p ? r - p : r;
+    }
+    uint32_t b = r ? p - r : 0u;
+    const uint32_t pi = 0u - pinv;  // 1 / p mod 2^32
+#pragma unroll 4
+    for (int t = 0; t < kWideDigitLimbs; ++t) {
+      const uint32_t m = m32[t0 + t], q = (m - b) * pi;
+      b = static_cast<uint32_t>((static_cast<uint64_t>(q) * p) >> 32) + (m < b ? 1u : 0u);
+      lds[lane * (kWideDigitLimbs + 1) + t] = on ? q : 0u;
+    }
   }
   __syncthreads();
   const size_t plane = static_cast<size_t>(P.wlpad) * P.wnpad;

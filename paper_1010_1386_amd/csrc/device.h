@@ -95,6 +95,7 @@ struct DevProblem {
   uint32_t* wT;           // wdpad * wnpad  t_{k,i} = u_{k,i} (M / p_i)^{-1} mod p_i, zero padded (wide path)
   uint32_t* wq;           // D+1         quotient estimate floor(sum_i f_{k,i} / 2^32) (wide path)
   uint64_t* wS;           // (D+1) * Lw * 2  column sum of each limb as (low, high) 64-bit words (wide path)
+  uint64_t* wsum;        // wide_mfma: sums of t over the primes, per coefficient
   int8_t* wMd;            // 5 * wlpad * wnpad  7-bit digit planes of the M_i limbs, [digit][limb][prime] (stage_wide_digits)
   int wdpad, wlpad, wnpad;// D+1, Lw and np rounded up (64, 32, 64); wT rows have wnpad entries
   int wide_mfma;          // 1: contraction on the matrix cores

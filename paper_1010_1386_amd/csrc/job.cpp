@@ -693,16 +693,22 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     L.zval = o;  o = align_up(o + np * (P.E + 1) * 4, A);
     L.zbad = o;  o = align_up(o + np * (P.E + 1), A);
     L.cpart = o; o = align_up(o + static_cast<size_t>(d.nchunk) * np * (P.D + 1) * 8, A);
-    L.wT = L.wq = L.wS = L.wMd = 0;
+    L.wT = L.wq = L.wS = L.wMd = L.wsum = 0;
     if (P.wide) {
       if (!L.crt_own) {
         L.wMd = J->lay[L.crt_from].wMd;  // the owner comes first
       } else if (d.wide_mfma) {
         L.wMd = o; o = align_up(o + static_cast<size_t>(kWideDigits) * d.wlpad * d.wnpad, A);
+        spared_bytes += static_cast<size_t>(d.wlpad) * d.wnpad;  // (five digits' planes)
       }
       L.wT = o; o = align_up(o + static_cast<size_t>(d.wdpad) * d.wnpad * 4, A);
       L.wq = o; o = align_up(o + static_cast<size_t>(P.D + 1) * 4, A);
       L.wS = o; o = align_up(o + static_cast<size_t>(P.D + 1) * 2 * P.Lw * 8, A);
+      if (d.wide_mfma) {
+        L.wsum = o;
+        o = align_up(o + static_cast<size_t>(P.D + 1) * 8, A);
+        digit_bytes += align_up(static_cast<size_t>(P.D + 1) * 8, A);
+      }
     }
   }
   // one region for buffers that are never live together: the digit tiles of the
@@ -736,7 +742,8 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     J->queue_off = own;
     own = align_up(own + J->queue_bytes, A);
     // (less the limb digits, which the upload image holds in place of the item
-    // lists it had, and with the M_i that are no longer stored)
+    // lists it had, and the sums of t; with the M_i and the fifth digits' planes
+    // that are no longer stored)
     const size_t counted = own + (apart - o) + spared_bytes;
     o = std::max({tiles, segs, own, counted > digit_bytes ? counted - digit_bytes : 0});
   }
@@ -871,6 +878,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     d.wT = P.wide ? reinterpret_cast<uint32_t*>(base + L.wT) : nullptr;
     d.wq = P.wide ? reinterpret_cast<uint32_t*>(base + L.wq) : nullptr;
     d.wS = P.wide ? reinterpret_cast<uint64_t*>(base + L.wS) : nullptr;
+    d.wsum = (P.wide && d.wide_mfma) ? reinterpret_cast<uint64_t*>(base + L.wsum) : nullptr;
     d.wMd = (P.wide && d.wide_mfma) ? reinterpret_cast<int8_t*>(base + L.wMd) : nullptr;
     d.resid = reinterpret_cast<uint32_t*>(base + L.resid);
     d.dig = d.evmf ? reinterpret_cast<uint64_t*>(base + L.dig) : nullptr;

@@ -23,7 +23,7 @@ namespace rsl {
 struct ProbLayout {
   // offsets from the job base
   size_t coeff, gdeg, pidx, Hm, NH, Tg, invM, Plimb, Mi, Mdig, wdir, rinv, negM, Mw, NHM, wMd, status;
-  size_t out, resid, dig, zval, zbad, aconv, cpart, hseg, wT, wq, wS;
+  size_t out, resid, dig, zval, zbad, aconv, cpart, hseg, wT, wq, wS, wsum;
   int L_in;
   bool crt_own;  // this problem's layout holds the CRT constant block it shares
   int crt_from;  // live index of the problem whose layout holds its CRT constant block

@@ -2516,9 +2516,10 @@ constexpr int kWideTCoeffs = 8;    // coefficients per block of pass 1 (256 thre
 constexpr int kWideKT = 16;        // coefficients per block of pass 2
 constexpr int kWideHT = 256;       // limbs per block of pass 2 (one per thread)
 constexpr int kWideChunk = 64;     // primes per LDS chunk of pass 2
-constexpr int kWideDigits = 5;     // 7-bit digits of t and of the M_i limbs (matrix-core pass 2)
+constexpr int kWideDigits = 4;     // base-256 digits of t and of the M_i limbs (matrix-core pass 2)
+constexpr uint32_t kWideOffset = 0x80808080u;  // a limb's digits in -128..127 are those of the limb less this
 
-__host__ __device__ inline int wide_t_lds_words() { return 4 * 2 * kWideTCoeffs; }
+__host__ __device__ inline int wide_t_lds_words() { return 4 * 4 * kWideTCoeffs; }
 __host__ __device__ inline int wide_sum_lds_words() { return kWideChunk * kWideKT; }
 __host__ __device__ inline int wide_fin_lds_words(const DevProblem& P) { return P.Lw; }
 
@@ -2546,6 +2547,7 @@ __device__ inline void stage_crt_wide_t(const DevProblem& P, const DevTables& T,
   const int np = P.np;
   const size_t cstride = static_cast<size_t>(np) * (P.D + 1);
   uint32_t fa = 0u, fb = 0u;  // 16-bit halves of the f parts, summed
+  uint32_t ta = 0u, tb = 0u;  // and of the t
   for (int i = threadIdx.x / kWideTCoeffs; i < np; i += blockDim.x / kWideTCoeffs) {
     const uint64_t* cpp = P.cpart + static_cast<size_t>(i) * (P.D + 1) + k;
     const PrimeConst pc = T.pc[P.pidx[i]];
@@ -2555,26 +2557,37 @@ __device__ inline void stage_crt_wide_t(const DevProblem& P, const DevTables& T,
     const uint64_t f = static_cast<uint64_t>(t) * P.rinv[2 * i + 1] + __umulhi(t, P.rinv[2 * i]);
     fa += static_cast<uint32_t>(f) & 0xFFFFu;
     fb += static_cast<uint32_t>(f >> 16);
+    ta += t & 0xFFFFu;
+    tb += t >> 16;
   }
   // lanes of one coefficient differ in lane bits 3..5
 #pragma unroll
   for (int m = kWideTCoeffs; m < 64; m <<= 1) {
     fa += static_cast<uint32_t>(__shfl_xor(static_cast<int>(fa), m, 64));
     fb += static_cast<uint32_t>(__shfl_xor(static_cast<int>(fb), m, 64));
+    ta += static_cast<uint32_t>(__shfl_xor(static_cast<int>(ta), m, 64));
+    tb += static_cast<uint32_t>(__shfl_xor(static_cast<int>(tb), m, 64));
   }
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
   if (lane < kWideTCoeffs) {
-    lds[wave * 2 * kWideTCoeffs + lane] = fa;
-    lds[wave * 2 * kWideTCoeffs + kWideTCoeffs + lane] = fb;
+    uint32_t* at = lds + wave * 4 * kWideTCoeffs + lane;
+    at[0] = fa;
+    at[kWideTCoeffs] = fb;
+    at[2 * kWideTCoeffs] = ta;
+    at[3 * kWideTCoeffs] = tb;
   }
   __syncthreads();
   if (threadIdx.x < kWideTCoeffs && valid) {
-    uint64_t sa = 0, sb = 0;
+    uint64_t sa = 0, sb = 0, ua = 0, ub = 0;
     for (int v = 0; v < nw; ++v) {
-      sa += lds[v * 2 * kWideTCoeffs + c];
-      sb += lds[v * 2 * kWideTCoeffs + kWideTCoeffs + c];
+      const uint32_t* at = lds + v * 4 * kWideTCoeffs + c;
+      sa += at[0];
+      sb += at[kWideTCoeffs];
+      ua += at[2 * kWideTCoeffs];
+      ub += at[3 * kWideTCoeffs];
     }
     P.wq[k] = static_cast<uint32_t>((sa + (sb << 16)) >> 32);
+    if (P.wide_mfma) P.wsum[k] = ua + (ub << 16);
   }
 }
 
@@ -2646,12 +2659,16 @@ __device__ inline void stage_crt_wide_sum(const DevProblem& P, const WorkItem& w
       }
 }
 
-// Pass 2 on the matrix cores.  t and the M_i limbs are split into five 7-bit
-// digits each (t = sum_a t_a 2^(7a), m = sum_b m_b 2^(7b), 35 bits >= 32), so
-// every digit is a non-negative int8; the int8 MFMA (16 x 16 outputs, 64
-// primes per step) accumulates sum_i t_a m_b in int32 per anti-diagonal
-// s = a + b: at most 5 * 127^2 * 4096 < 2^29 for 4096 primes, exact.  The
-// column sum is then sum_s D_s 2^(7s) < 2^85.  The limb digits are planes
+// Pass 2 on the matrix cores, in base-256 digits of -128..127: t < 2^31 has four
+// (t = sum_a t_a 2^(8a)), and so has a limb less kWideOffset (its bytes with the
+// top bit flipped, no carry to the next limb), whose products fall short of the
+// column sum by kWideOffset sum_i t_i, added at the end from pass 1's sum of the
+// t.  The int8 MFMA (16 x 16 outputs, 64 primes per step) accumulates
+// sum_i t_a m_b in int32 per anti-diagonal s = a + b: at most 4 * 2^14 * 4096 =
+// 2^28 for 4096 primes, exact.  Sixteen products a step; five 7-bit digits,
+// which need no offset, take 25 (ten
+// resultants of degree 225 over 2025 primes: 289 -> 215 us).  The
+// column sum is below 2^85.  The limb digits are planes
 // Md[b][t][i] built with the job (a limb's primes contiguous); the block
 // stages its 32 limbs x 64 primes x 5 digits in LDS once per step for its
 // four waves.  The t values come from wT (rows padded with zeros to wnpad)
@@ -2719,24 +2736,23 @@ __device__ inline void stage_wide_digits(const DevProblem& P, const DevTables& T
     for (int t = 0; t < kWideDigitLimbs; ++t) {
       const uint32_t m = m32[t0 + t], q = (m - b) * pi;
       b = static_cast<uint32_t>((static_cast<uint64_t>(q) * p) >> 32) + (m < b ? 1u : 0u);
-      lds[lane * (kWideDigitLimbs + 1) + t] = on ? q : 0u;
+      lds[lane * (kWideDigitLimbs + 1) + t] = on ? q ^ kWideOffset : 0u;
     }
   }
   __syncthreads();
   const size_t plane = static_cast<size_t>(P.wlpad) * P.wnpad;
   const int q = threadIdx.x & 3, tt = threadIdx.x >> 2;  // 16 primes of one limb, every digit
   if (t0 + tt >= P.wlpad) return;
-  uint32_t m[16];
+  uint32_t dg[4][kWideDigits];  // [4 primes][digit]
 #pragma unroll
-  for (int u = 0; u < 16; ++u) m[u] = lds[(16 * q + u) * (kWideDigitLimbs + 1) + tt];
+  for (int v = 0; v < 4; ++v) {
+    const uint32_t* m = lds + (16 * q + 4 * v) * (kWideDigitLimbs + 1) + tt;
+    byte_transpose4(m[0], m[kWideDigitLimbs + 1], m[2 * (kWideDigitLimbs + 1)], m[3 * (kWideDigitLimbs + 1)], dg[v]);
+  }
   int8_t* dst = P.wMd + static_cast<size_t>(t0 + tt) * P.wnpad + i0 + 16 * q;
 #pragma unroll
-  for (int d = 0; d < kWideDigits; ++d) {
-    uint32_t word[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int u = 0; u < 16; ++u) word[u >> 2] |= ((m[u] >> (7 * d)) & 127u) << (8 * (u & 3));
-    *reinterpret_cast<uint4*>(dst + d * plane) = make_uint4(word[0], word[1], word[2], word[3]);
-  }
+  for (int d = 0; d < kWideDigits; ++d)
+    *reinterpret_cast<uint4*>(dst + d * plane) = make_uint4(dg[0][d], dg[1][d], dg[2][d], dg[3][d]);
 }
 
 __device__ inline void stage_crt_wide_sum_mfma(const DevProblem& P, const WorkItem& w, uint32_t* lds) {
@@ -2771,14 +2787,13 @@ __device__ inline void stage_crt_wide_sum_mfma(const DevProblem& P, const WorkIt
     }
     wide_v4i a[kWideDigits];
 #pragma unroll
-    for (int d = 0; d < kWideDigits; ++d)
+    for (int wd = 0; wd < 4; ++wd) {
+      uint32_t o[kWideDigits];
+      digits4(static_cast<int32_t>(tv[4 * wd]), static_cast<int32_t>(tv[4 * wd + 1]),
+              static_cast<int32_t>(tv[4 * wd + 2]), static_cast<int32_t>(tv[4 * wd + 3]), o);
 #pragma unroll
-      for (int wd = 0; wd < 4; ++wd) {
-        uint32_t word = 0;
-#pragma unroll
-        for (int by = 0; by < 4; ++by) word |= ((tv[4 * wd + by] >> (7 * d)) & 127u) << (8 * by);
-        a[d][wd] = static_cast<int>(word);
-      }
+      for (int d = 0; d < kWideDigits; ++d) a[d][wd] = static_cast<int>(o[d]);
+    }
     __syncthreads();
 #pragma unroll
     for (int db = 0; db < kWideDigits; ++db) {
@@ -2798,11 +2813,10 @@ __device__ inline void stage_crt_wide_sum_mfma(const DevProblem& P, const WorkIt
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int k = k0 + 4 * kg + e;
-      unsigned __int128 v = 0;
-#pragma unroll
-      for (int d = 0; d < 2 * kWideDigits - 1; ++d)
-        v += static_cast<unsigned __int128>(static_cast<uint32_t>(acc[u][d][e])) << (7 * d);
       if (k <= P.D && t < Lw) {
+        __int128 v = static_cast<__int128>(P.wsum[k]) * kWideOffset;
+#pragma unroll
+        for (int d = 0; d < 2 * kWideDigits - 1; ++d) v += static_cast<__int128>(acc[u][d][e]) * (1ll << (8 * d));
         uint64_t* dst = P.wS + static_cast<size_t>(k) * nh + 2 * t;
         dst[0] = static_cast<uint64_t>(v);
         dst[1] = static_cast<uint64_t>(v >> 64);

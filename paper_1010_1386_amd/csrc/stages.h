@@ -209,8 +209,14 @@ __device__ inline void stage_reduce(const DevProblem& P, const DevTables& T, con
 //   r <- sredc((r + b) R^2 + w_s R) = r 2^32 + w mod p,
 // five instructions per limb, coefficient and prime (|r| <= 0.9 p with the two
 // constants centred).  Inputs of more than two limbs pass through LDS 16 limbs
-// at a time, read once per block for its 4 SPW primes.  Item (first slot, block
-// of 64 lanes, sub = SPW).
+// at a time, read once per block for its 4 SPW primes, each limb below the top
+// less 2^31 (its top bit flipped: a signed word without a carry), two limbs a
+// step,
+//   r <- sredc(r R^3 + w_1 R^2 + w_0 R) = r 2^64 + w_1 2^32 + w_0 mod p,
+// five instructions per two limbs (|r| <= 1.2 p); the same steps on zero
+// coefficients (off) give what the offsets add, taken off at the end: 10 pairs of
+// degree 15 with 2^2048 coefficients 190 -> 151 us.  Item (first slot, block of
+// 64 lanes, sub = SPW).
 //
 // Short inputs: the lanes walk the tiles in order, padding runs as zeros (a
 // separate pass over the padding cost more than the idle lanes: 41 -> 48 us on 256
@@ -219,13 +225,13 @@ __device__ inline void stage_reduce(const DevProblem& P, const DevTables& T, con
 // pairs of degree 15 with 2^2048 coefficients, of whose tile runs a quarter hold
 // coefficients).  Against byte or 8-byte stores of canonical residues with 14
 // instructions per limb, and a clearing launch per upload: 256 pairs 80 -> 41 us,
-// 64 requests of degrees 8..48 75 -> 38, the 2^2048 set 368 -> 193; the launch
-// saved 3-9 us per call.
+// 64 requests of degrees 8..48 75 -> 38, the 2^2048 set 368 -> 193 (one limb a
+// step); the launch saved 3-9 us per call.
 constexpr int kReduceChunk = 16;  // limbs per LDS chunk
 // Prime slots per wave for inputs of up to two limbs (2, 3, 4: 7.4, 8.1, 8.5 us on
-// the degree-24 pair, 41, 37, 38 us on 256 pairs) and of more (4, 5, 6, 8: 258,
-// 253, 264, 272 us on the 2^2048 set before its padding was split off, 29.5, 32.5,
-// 32.5, 30.3 us on 10 pairs of degree 9 with 2^512).
+// the degree-24 pair, 41, 37, 38 us on 256 pairs) and of more (3, 4: 162, 151 us
+// on the 2^2048 set, 23, 24.5 us on 10 pairs of degree 9 with 2^512; 5, 6 and 8
+// were no better than 4 with one limb a step).
 constexpr int kReduceSlotsShort = 2, kReduceSlotsLong = 4;
 // runs with coefficients, and all runs of a slot's tiles
 __host__ __device__ inline int reduce_runs(const DevProblem& P) {
@@ -295,13 +301,16 @@ __device__ inline void stage_reduce_tiles(const DevProblem& P, const DevTables& 
   const uint32_t* src =
       P.coeff + (static_cast<size_t>(gp ? (P.my + 1) * P.rowf : 0) + static_cast<size_t>(j) * len + i0) * L;
   SignedMod M[SPW];
-  int32_t r1[SPW], r2[SPW], acc[SPW][8];
+  int32_t r1[SPW], r2[SPW], r3[SPW], off[SPW], acc[SPW][8];
+  constexpr int32_t kMin = INT32_MIN;
 #pragma unroll
   for (int s = 0; s < SPW; ++s) {
     const PrimeConst pc = T.pc[P.pidx[s0 + s < P.np ? s0 + s : P.np - 1]];
     M[s] = signed_mod(pc);
     r1[s] = scenter(static_cast<int32_t>(pc.r1), M[s]);
     r2[s] = scenter(static_cast<int32_t>(pc.r2), M[s]);
+    r3[s] = scenter(static_cast<int32_t>(pc.r3), M[s]);
+    off[s] = 0;
   }
   auto top = [&](const uint32_t (&v)[8]) {
 #pragma unroll
@@ -338,15 +347,49 @@ __device__ inline void stage_reduce_tiles(const DevProblem& P, const DevTables& 
 #pragma unroll
         for (int u = 0; u < kReduceChunk / 4; ++u) {
           const int l = 4 * wave + u;
-          lds[(l * 8 + e) * 64 + lane] = (e < nv && l0 + l < l1) ? src[static_cast<size_t>(e) * L + l0 + l] : 0u;
+          const uint32_t x = (e < nv && l0 + l < l1) ? src[static_cast<size_t>(e) * L + l0 + l] : 0u;
+          lds[(l * 8 + e) * 64 + lane] = l0 + l < L - 1 ? x ^ 0x80000000u : x;
         }
       __syncthreads();
-      for (int l = l1 - l0 - 1; l >= 0; --l) {
+      int l = l1 - l0 - 1;
+      if (l1 == L) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = lds[(l * 8 + e) * 64 + lane];
-        if (l0 + l == L - 1) top(v);
-        else next(v);
+        top(v);
+        --l;
       }
+      if (l >= 0 && (l & 1) == 0) {  // an odd number of limbs: one by itself
+#pragma unroll
+        for (int s = 0; s < SPW; ++s) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            acc[s][e] = sredc(smad(acc[s][e], r2[s], smad(static_cast<int32_t>(lds[(l * 8 + e) * 64 + lane]), r1[s], 0)), M[s]);
+          off[s] = sredc(smad(off[s], r2[s], smad(kMin, r1[s], 0)), M[s]);
+        }
+        --l;
+      }
+      for (; l > 0; l -= 2) {
+        uint32_t lo[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          v[e] = lds[(l * 8 + e) * 64 + lane];
+          lo[e] = lds[(l * 8 - 8 + e) * 64 + lane];
+        }
+#pragma unroll
+        for (int s = 0; s < SPW; ++s) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            acc[s][e] = sredc(smad(acc[s][e], r3[s], smad(static_cast<int32_t>(v[e]), r2[s],
+                                                          smad(static_cast<int32_t>(lo[e]), r1[s], 0))), M[s]);
+          off[s] = sredc(smad(off[s], r3[s], smad(kMin, r2[s], smad(kMin, r1[s], 0))), M[s]);
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < SPW; ++s) {
+      const int32_t o = scenter(off[s], M[s]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[s][e] = scenter(scenter(acc[s][e], M[s]) - o, M[s]);
     }
   }
 #pragma unroll
@@ -2667,11 +2710,10 @@ __device__ inline void stage_crt_wide_sum(const DevProblem& P, const WorkItem& w
 // sum_i t_a m_b in int32 per anti-diagonal s = a + b: at most 4 * 2^14 * 4096 =
 // 2^28 for 4096 primes, exact.  Sixteen products a step; five 7-bit digits,
 // which need no offset, take 25 (ten
-// resultants of degree 225 over 2025 primes: 289 -> 215 us).  The
-// column sum is below 2^85.  The limb digits are planes
-// Md[b][t][i] built with the job (a limb's primes contiguous); the block
-// stages its 32 limbs x 64 primes x 5 digits in LDS once per step for its
-// four waves.  The t values come from wT (rows padded with zeros to wnpad)
+// resultants of degree 225 over 2025 primes: 289 -> 215 us).  The column sum is
+// below 2^85.  The limb digits are planes Md[b][t][i] (a limb's primes
+// contiguous); the block stages its 32 limbs x 64 primes x 4 digits in LDS once
+// per step for its four waves.  The t values come from wT (rows padded with zeros to wnpad)
 // and are split into digits in registers.  Wave w takes coefficients
 // k0 + 16 w ... (one 16-row tile) and the block's 32 limbs (two 16-column
 // tiles); a lane holds row r of A and column r of B for the 16 primes of its

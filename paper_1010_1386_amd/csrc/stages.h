@@ -2580,7 +2580,10 @@ __device__ inline uint32_t wave_carry_in(bool gen, bool prop, uint64_t* cin) {
 }
 
 // Pass 1: block item blk covers coefficients blk*8 .. blk*8+7; thread owns
-// coefficient c = tid mod 8 and primes tid/8 + 32 r.
+// coefficient c = tid mod 8 and primes tid/8 + 32 r, kWideTPrimes of them at a
+// time: a prime's constants are three dependent loads, which bound the pass (ten
+// resultants of degree 225 over 2025 primes: one prime at a time 99 us, four 59, eight 55).
+constexpr int kWideTPrimes = 8;
 __device__ inline void stage_crt_wide_t(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds,
                                         bool whole) {
   const int c = threadIdx.x & (kWideTCoeffs - 1);
@@ -2591,17 +2594,29 @@ __device__ inline void stage_crt_wide_t(const DevProblem& P, const DevTables& T,
   const size_t cstride = static_cast<size_t>(np) * (P.D + 1);
   uint32_t fa = 0u, fb = 0u;  // 16-bit halves of the f parts, summed
   uint32_t ta = 0u, tb = 0u;  // and of the t
-  for (int i = threadIdx.x / kWideTCoeffs; i < np; i += blockDim.x / kWideTCoeffs) {
-    const uint64_t* cpp = P.cpart + static_cast<size_t>(i) * (P.D + 1) + k;
-    const PrimeConst pc = T.pc[P.pidx[i]];
-    const uint32_t u = maddm(coeff_of(P, cpp, cstride, k, pc.p, pc.pinv, whole), P.Hm[i], pc.p);  // c_k + H mod p
-    const uint32_t t = mmul(u, P.wdir[i], pc.p, pc.pinv);
-    if (valid) P.wT[static_cast<size_t>(k) * P.wnpad + i] = t;
-    const uint64_t f = static_cast<uint64_t>(t) * P.rinv[2 * i + 1] + __umulhi(t, P.rinv[2 * i]);
-    fa += static_cast<uint32_t>(f) & 0xFFFFu;
-    fb += static_cast<uint32_t>(f >> 16);
-    ta += t & 0xFFFFu;
-    tb += t >> 16;
+  const int step = blockDim.x / kWideTCoeffs;
+  for (int i0 = threadIdx.x / kWideTCoeffs; i0 < np; i0 += kWideTPrimes * step) {
+    uint32_t t[kWideTPrimes];
+    uint64_t f[kWideTPrimes];
+#pragma unroll
+    for (int v = 0; v < kWideTPrimes; ++v) {
+      const int i = min(i0 + v * step, np - 1);
+      const uint64_t* cpp = P.cpart + static_cast<size_t>(i) * (P.D + 1) + k;
+      const PrimeConst pc = T.pc[P.pidx[i]];
+      const uint32_t u = maddm(coeff_of(P, cpp, cstride, k, pc.p, pc.pinv, whole), P.Hm[i], pc.p);  // c_k + H mod p
+      t[v] = mmul(u, P.wdir[i], pc.p, pc.pinv);
+      f[v] = static_cast<uint64_t>(t[v]) * P.rinv[2 * i + 1] + __umulhi(t[v], P.rinv[2 * i]);
+    }
+#pragma unroll
+    for (int v = 0; v < kWideTPrimes; ++v) {
+      const int i = i0 + v * step;
+      if (i >= np) break;
+      if (valid) P.wT[static_cast<size_t>(k) * P.wnpad + i] = t[v];
+      fa += static_cast<uint32_t>(f[v]) & 0xFFFFu;
+      fb += static_cast<uint32_t>(f[v] >> 16);
+      ta += t[v] & 0xFFFFu;
+      tb += t[v] >> 16;
+    }
   }
   // lanes of one coefficient differ in lane bits 3..5
 #pragma unroll

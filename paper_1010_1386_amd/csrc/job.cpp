@@ -35,7 +35,7 @@ int job_plan(int n, const rsl_poly* f, const rsl_poly* g, const int* var, const 
   // planning is independent per problem: spread it over host threads
   std::vector<std::string> perr(n);
   double words = 0.0;  // of the inputs, while their sizes make sense
-  for (int k = 0; k < n; ++k)
+  for (int k = 0; k < n && f && g; ++k)  // (a null polynomial is make_plan's to refuse)
     for (const rsl_poly* q : {&f[k], &g[k]})
       if (q->dx >= 0 && q->dy >= 0 && q->limbs > 0) words += (q->dx + 1.0) * (q->dy + 1.0) * q->limbs;
   parallel_for(n, host_grain(2000.0 + 8.0 * words / std::max(n, 1)), [&](int k) {

@@ -108,7 +108,9 @@ int bitlen_i(int64_t v) {
 // from pinned memory.
 struct Dev {
   uint8_t* base;
-  size_t cap, used = 0;
+  size_t cap;
+  bool digits;  // the slot CRT on the matrix cores, from the digits of the M_i
+  size_t used = 0;
   bool bad = false;
   std::vector<uint8_t> host;  // staged bytes of [lo, hi)
   size_t lo = 0, hi = 0;
@@ -185,10 +187,13 @@ int crt_setup(rsl_ctx* ctx, Dev* D, const std::vector<int>& pidx, CrtDev* C) {
   const Plan& P = C->P;
   int rc;
   if ((rc = upload_vec(ctx, D, P.pidx, &C->pidx)) || (rc = upload_vec(ctx, D, P.crt->Hm, &C->Hm)) ||
-      (rc = upload_vec(ctx, D, P.crt->NH, &C->NH)) || (rc = upload_vec(ctx, D, P.crt->Mi, &C->Mi)) ||
-      (rc = upload_vec(ctx, D, P.crt->dig, &C->Mdig)) || (rc = upload_vec(ctx, D, P.crt->wdir, &C->wdir)) || (rc = upload_vec(ctx, D, P.crt->rinv, &C->rinv)) ||
-      (rc = upload_vec(ctx, D, P.crt->negM, &C->negM)))
+      (rc = upload_vec(ctx, D, P.crt->NH, &C->NH)) || (rc = upload_vec(ctx, D, P.crt->wdir, &C->wdir)) ||
+      (rc = upload_vec(ctx, D, P.crt->rinv, &C->rinv)) || (rc = upload_vec(ctx, D, P.crt->negM, &C->negM)))
     return rc;
+  // the matrix cores read the digits only, the column sums the limbs (and, when
+  // undecided, Garner's tables)
+  if (D->digits && !P.wide) return upload_vec(ctx, D, P.crt->dig, &C->Mdig);
+  if ((rc = upload_vec(ctx, D, P.crt->Mi, &C->Mi))) return rc;
   if (P.wide && ((rc = upload_vec(ctx, D, P.crt->Mw, &C->Mw)) || (rc = upload_vec(ctx, D, P.crt->NHM, &C->NHM)))) return rc;
   if (!P.canonical && !P.wide &&
       ((rc = upload_vec(ctx, D, P.crt->Tg, &C->Tg)) || (rc = upload_vec(ctx, D, P.crt->invM, &C->invM)) ||
@@ -256,7 +261,7 @@ int run_crt(rsl_ctx* ctx, Dev* D, const std::vector<DevProblem>& probs) {
   if (!wide) {
     int ns = (np + 63) / 64;
     if (ns == 5 || ns == 7) ++ns;
-    const bool mm = !ctx->crt_garner;
+    const bool mm = probs[0].Mdig != nullptr;
     std::vector<WorkItem> items;
     size_t lds = 0;
     for (size_t q = 0; q < probs.size(); ++q) {
@@ -370,13 +375,14 @@ UPoly sub_upoly(const UPoly& x, const UPoly& y) {
   return as_upoly(tmp.data(), n, r.L);
 }
 
-// G = gcd(pp(u), pp(v)), A = u / G, B = v / G (see the file comment)
-int gcd_core(rsl_ctx* ctx, const UPoly& u, const UPoly& v, UPoly* gout, UPoly* uout, UPoly* vout) {
+// G = gcd(pp(u), pp(v)), A = u / G, B = v / G (see the file comment); digits: the
+// slot CRT on the matrix cores
+int gcd_with(rsl_ctx* ctx, const UPoly& u, const UPoly& v, bool digits, UPoly* gout, UPoly* uout, UPoly* vout) {
   if (u.deg < 0 && v.deg < 0) {
     *gout = *uout = *vout = UPoly();
     return RSL_OK;
   }
-  if (u.deg < 0) return gcd_core(ctx, v, u, gout, vout, uout);
+  if (u.deg < 0) return gcd_with(ctx, v, u, digits, gout, vout, uout);
   const int nu = u.deg, nv = v.deg;  // nv = -1: v is zero
   if (nv < 0) {
     // gcd(u, 0) = pp(u), u / G = sign(lc u) content(u): a one-limb content (the
@@ -460,7 +466,7 @@ int gcd_core(rsl_ctx* ctx, const UPoly& u, const UPoly& v, UPoly* gout, UPoly* u
     if (rc) return rc;
     const DevTables T = tables_of(ctx);
 
-    Dev D{ctx->ws, ctx->ws_bytes};
+    Dev D{ctx->ws, ctx->ws_bytes, digits};
     ZgcdDesc Z{};
     Z.nu = nu;
     Z.nv = nv;
@@ -590,6 +596,18 @@ int gcd_core(rsl_ctx* ctx, const UPoly& u, const UPoly& v, UPoly* gout, UPoly* u
     return RSL_OK;
   }
   return fail(ctx, RSL_EPRIMES, "modular gcd: no consistent set of primes found");
+}
+
+// The digits take up to 15 limbs and 15 primes of padding more than the limbs
+// they stand for, some kilobytes: in a workspace with no room for that the CRT
+// takes the column sums.
+int gcd_core(rsl_ctx* ctx, const UPoly& u, const UPoly& v, UPoly* gout, UPoly* uout, UPoly* vout) {
+  int rc = gcd_with(ctx, u, v, !ctx->crt_garner, gout, uout, vout);
+  if (rc == RSL_ENOMEM && !ctx->crt_garner) {
+    ctx->err.clear();
+    rc = gcd_with(ctx, u, v, false, gout, uout, vout);
+  }
+  return rc;
 }
 
 }  // namespace

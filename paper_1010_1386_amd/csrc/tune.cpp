@@ -279,10 +279,18 @@ int rsl_job_bind(rsl_ctx* ctx, rsl_job* j, void* d_mem, size_t bytes) {
   if (rc) return rc;
   j->dmem = static_cast<uint8_t*>(d_mem);
   j->dmem_bytes = bytes;
-  if (j->J.total > bytes && !j->J.lean) rc = lay_out(ctx, j, TuneConfig(j->tc), true);
-  if (rc || (rc = bind_and_upload(ctx, j))) {
+  // the usual layout where it fits (an earlier bind to less memory may have left
+  // the one with the least), and again after a bind that failed
+  const TuneConfig tc = j->tc;
+  if (j->J.lean) rc = lay_out(ctx, j, tc, false);
+  if (!rc && j->J.total > bytes) rc = lay_out(ctx, j, tc, true);
+  if (!rc) rc = bind_and_upload(ctx, j);
+  if (rc) {
     j->dmem = nullptr;
     j->dmem_bytes = 0;
+    const std::string err = ctx->err;
+    if (j->J.lean) (void)lay_out(ctx, j, tc, false);
+    ctx->err = err;
   }
   return rc;
 }

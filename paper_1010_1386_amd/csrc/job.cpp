@@ -6,6 +6,7 @@
 #include <cstring>
 #include <map>
 #include <numeric>
+#include <set>
 
 #include "context.h"
 #include "kernels.h"
@@ -218,15 +219,34 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     const int evk_p = lanes_asked(P);
     return evk_p <= 2 && P.rowf <= 33 && P.rowg <= 33 && regn_of(P, evk_p == 1) > 0 && !(ctx && ctx->eval_horner);
   };
+  // what the sharing leaves of a problem's column layout: its segment polynomials
+  // (and those tiles)
+  auto spare_bytes = [&](const Plan& P) {
+    const size_t np = P.np, rt = dig_rt(P.my + 1) + dig_rt(P.ny + 1);
+    return np * align_up(static_cast<size_t>(P.D + 1), kCkpt) * 4 + (five_digit_tiles(P) ? np * rt * 5 * 512 : 0);
+  };
+  // The CRT's limb digits (as many bytes as the limbs of M / p_i beside them) have
+  // to fit in the same: not where a low degree needs many primes (degrees 17 and
+  // 49, x-degrees 1 and 2, 219-bit coefficients: 490 primes, 0.9 MB of digits in a
+  // layout of 4.4 MB).  A lean layout without them takes the column sums.
+  J->crt_mm = !(ctx && ctx->crt_garner);
+  if (J->crt_mm && J->lean) {
+    size_t digits = 0, spare = 0;
+    std::set<const CrtConst*> seen;
+    for (int k : J->live) {
+      const Plan& P = J->plans[k];
+      spare += spare_bytes(P);
+      if (seen.insert(P.crt.get()).second) digits += P.crt->dig.size();
+    }
+    J->crt_mm = digits <= spare;
+  }
   auto tiles_fit = [&](const Plan& P, const DevProblem& d) {
     if (!J->lean) return true;
     const size_t np = P.np, rt = dig_rt(P.my + 1) + dig_rt(P.ny + 1);
     const size_t kh = (P.rowf <= 32 && P.rowg <= 32) ? 1 : 2;
     const int cchunk = (J->tune.conv_whole || whole_req) ? P.D + 1 : Kc;
     const size_t shared = np * d.CS * 4 + static_cast<size_t>(blocks_of(P.D + 1, cchunk)) * np * (P.D + 1) * 8;
-    const size_t hseg = np * align_up(static_cast<size_t>(P.D + 1), kCkpt) * 4;
-    return np * rt * kh * kEvDigits * 512 + P.crt->dig.size() <=
-           shared + hseg + (five_digit_tiles(P) ? np * rt * 5 * 512 : 0);
+    return np * rt * kh * kEvDigits * 512 + (J->crt_mm ? P.crt->dig.size() : 0) <= shared + spare_bytes(P);
   };
   J->crt_ns = 1;
   J->max_np = 0;
@@ -319,7 +339,6 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     }
   }
 
-  J->crt_mm = !(ctx && ctx->crt_garner);
   if (J->crt_ns == 5 || J->crt_ns == 7) ++J->crt_ns;  // CRT kernels exist for 1-4, 6 and 8 slots per lane
   // a pair shares its reduction where both evaluate from residue tiles; digit
   // tiles are written whole by their own problem
@@ -617,8 +636,11 @@ int job_build(rsl_ctx* ctx, int n, const rsl_poly* f, const rsl_poly* g, const i
     // (the wide path's matrix products take the M_i from M itself)
     L.Mi = o;
     (d.wide_mfma ? spared_bytes : o) += align_up(static_cast<size_t>(P.np) * P.Lw * 4, 16);
-    L.Mdig = o;  o = align_up(o + P.crt->dig.size(), 16);
-    digit_bytes += P.crt->dig.size();
+    L.Mdig = o;
+    if (J->crt_mm) {
+      o = align_up(o + P.crt->dig.size(), 16);
+      digit_bytes += P.crt->dig.size();
+    }
     L.wdir = o;  o = align_up(o + static_cast<size_t>(P.np) * 4, 16);
     L.rinv = o;  o = align_up(o + static_cast<size_t>(P.np) * 8, 16);
     L.negM = o;  o = align_up(o + static_cast<size_t>(P.Lw) * 4, 16);
@@ -848,7 +870,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     std::memcpy(blob + L.Hm, P.crt->Hm.data(), P.np * 4);
     std::memcpy(blob + L.NH, P.crt->NH.data(), P.L_out * 4);
     if (!d.wide_mfma) std::memcpy(blob + L.Mi, P.crt->Mi.data(), P.crt->Mi.size() * 4);
-    if (!P.crt->dig.empty()) std::memcpy(blob + L.Mdig, P.crt->dig.data(), P.crt->dig.size());
+    if (J->crt_mm && !P.crt->dig.empty()) std::memcpy(blob + L.Mdig, P.crt->dig.data(), P.crt->dig.size());
     std::memcpy(blob + L.wdir, P.crt->wdir.data(), P.crt->wdir.size() * 4);
     std::memcpy(blob + L.rinv, P.crt->rinv.data(), P.crt->rinv.size() * 4);
     std::memcpy(blob + L.negM, P.crt->negM.data(), P.crt->negM.size() * 4);
@@ -869,7 +891,7 @@ void job_bind(Job* J, uint8_t* base, uint8_t* image, bool with_queue) {
     d.Hm = reinterpret_cast<const uint32_t*>(base + L.Hm);
     d.NH = reinterpret_cast<const uint32_t*>(base + L.NH);
     d.Mi = d.wide_mfma ? nullptr : reinterpret_cast<const uint32_t*>(base + L.Mi);
-    d.Mdig = base + L.Mdig;
+    d.Mdig = J->crt_mm ? base + L.Mdig : nullptr;
     d.wdir = reinterpret_cast<const uint32_t*>(base + L.wdir);
     d.rinv = reinterpret_cast<const uint32_t*>(base + L.rinv);
     d.negM = reinterpret_cast<const uint32_t*>(base + L.negM);

@@ -62,8 +62,9 @@ struct Job {
   size_t wide_lds[3] = {};
   size_t items_off[kNumStages] = {};
   size_t stage_lds[kNumStages] = {};
-  int crt_ns = 1;                  // prime slots per lane of the column-sum CRT (persistent schedule, Garner hook)
-  bool crt_mm = true;              // the slot CRT on the matrix cores (not under the Garner hook)
+  int crt_ns = 1;                  // prime slots per lane of the column-sum CRT (persistent schedule, or !crt_mm)
+  bool crt_mm = true;              // the slot CRT on the matrix cores (not under the Garner hook, nor in a lean
+                                   // layout without room for its digits)
   int max_np = 0;                  // most primes of any live problem
   int slot_np = 0;                 // the same without the wide CRT's problems
   int need_g = 0, need_E = 0, need_D = 0;  // constant tables the job reads (primes, points, degree)
@@ -96,8 +97,8 @@ struct Job {
   int64_t interp_mm = 0;           // interpolation products: N_p (D+1)(D+2) over problems
   TuneConfig tune;                 // schedule parameters the job was laid out with
   // set before job_build: digit tiles only for problems whose layout stays within
-  // the memory it takes without them (callers with a fixed amount of memory lay
-  // a job that does not fit out again with this)
+  // the memory it takes without them, and the CRT's digits likewise (callers with a
+  // fixed amount of memory lay a job that does not fit out again with this)
   bool lean = false;
   // scratch of job_build, kept with the job so that a job object reused for
   // the next batch reuses its host memory (no fresh pages per call)

@@ -3,17 +3,11 @@ call goes through (a driver linked with the library, since the entry points need
 context).  GPU: by the entry points of one problem, which then still work."""
 
 import ctypes
-import os
-import shutil
-import subprocess
 
 import pytest
 
+from _host_driver import run_driver
 from workloads import dense_total, rng_for
-
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-PKG = os.path.join(ROOT, "paper_1010_1386_amd")
-ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 DRIVER = r"""
 #include <cstdio>
@@ -36,20 +30,9 @@ int main() {
 
 
 def test_planning_refuses_null(tmp_path):
-    hipcc = shutil.which("hipcc") or os.path.join(ROCM, "bin", "hipcc")
-    clang = os.path.join(ROCM, "llvm", "bin", "clang++")
-    if not (os.path.exists(hipcc) and os.path.exists(clang)):
-        pytest.skip("ROCm compilers not found")
-    src, obj, exe = (str(tmp_path / n) for n in ("driver.cpp", "driver.o", "driver"))
-    with open(src, "w") as fh:
-        fh.write(DRIVER)
-    subprocess.run([hipcc, "-std=c++17", "-x", "hip", "--offload-host-only", "-I" + os.path.join(PKG, "csrc"),
-                    "-I" + os.path.join(ROOT, "include"), "-c", src, "-o", obj], check=True)
-    subprocess.run([clang, obj, "-o", exe, os.path.join(PKG, "librsl.so"), f"-L{ROCM}/lib", "-lamdhip64",
-                    f"-Wl,-rpath,{PKG}:{ROCM}/lib"], check=True)
-    r = subprocess.run([exe], capture_output=True, text=True)
-    assert r.returncode == 0, r.returncode
-    assert r.stdout.split("\n")[:3] == ["0 -1 0"] * 3  # laid out, problem 0 refused, nothing to run
+    rc, out = run_driver(DRIVER, tmp_path)
+    assert rc == 0
+    assert out.split("\n")[:3] == ["0 -1 0"] * 3  # laid out, problem 0 refused, nothing to run
 
 
 @pytest.mark.gpu

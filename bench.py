@@ -418,7 +418,7 @@ def pair_bench(a):
     # counts when steps overlap), a lane pair gives the shorter single launch
     # (which the autotuner times); both sets are timed and the faster kept
     inflight_sets = [(info["eval_lanes"], all_jobs)]
-    if extra and mode == "staged" and info.get("eval_mfma", 0) > 0 and not a.eval_schur and not a.eval_lanes:
+    if extra and mode == "staged" and info["mulmods_sums_mfma"] > 0 and not a.eval_schur and not a.eval_lanes:
         alt = 1 if info["eval_lanes"] == 2 else 2
         alt_jobs = []
         for c in [ctx] + extra_ctx:
@@ -895,8 +895,8 @@ def batch_headline(a):
         "mfma": {"achieved": 2.0 * macs / t_eval / 1e12, "peak": MFMA_INT8_PEAK_TOPS, "unit": "TOP/s int8",
                  "frac": 2.0 * macs / t_eval / 1e12 / MFMA_INT8_PEAK_TOPS, "int8_macs_per_launch": macs,
                  "sums_mulmods": mfma_mm,
-                 "note": "evaluation sums on the matrix cores: 25 int8 digit products per residue product, "
-                         "padded 16x16x32 tiles"},
+                 "note": "evaluation sums on the matrix cores: 16 int8 digit products per residue product, as "
+                         "10 (x-powers 0..31) or 16 (0..63) 16x16x64 products per padded 16-point, 16-row tile"},
         "all_products_frac": info["mulmods"] / t_eval / 1e12 / PEAK_TMULMOD,
     }
     # the same launches against the measured issue rates of the units
@@ -907,9 +907,9 @@ def batch_headline(a):
         mont = rates["montgomery_mul"] / 1e12
         roofline["measured_peak"] = {
             "montgomery_tmulmod_s": mont, "fused_update_t_s": rates["fused_update_3_products"] / 1e12,
-            "mfma_int8_top_s": 2.0 * rates["mfma_i32_16x16x32_i8_macs"] / 1e12,
+            "mfma_int8_top_s": 2.0 * rates["mfma_i32_16x16x64_i8_macs"] / 1e12,
             "valu_frac_of_measured": valu_mm / t_eval / 1e12 / mont,
-            "mfma_frac_of_measured": macs / t_eval / rates["mfma_i32_16x16x32_i8_macs"],
+            "mfma_frac_of_measured": macs / t_eval / rates["mfma_i32_16x16x64_i8_macs"],
             "rates": rates, "source": "paper_1010_1386_amd/peak.py (csrc/peak.hip)"}
     except Exception as e:  # measurement is auxiliary: report, never fail the line
         roofline["measured_peak"] = {"error": str(e)}

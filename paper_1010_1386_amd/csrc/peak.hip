@@ -12,6 +12,8 @@
 //   kind 3  Montgomery product          (mmul: three multiplies, the final min)
 //   kind 4  fused three-product update  (mmad3: the remainder-sequence step)
 //   kind 5  int8 16x16x32 matrix product (v_mfma_i32_16x16x32_i8), MACs
+//   kind 6  int8 16x16x64 matrix product (v_mfma_i32_16x16x64_i8, the one the
+//           library's kernels issue), MACs
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -39,6 +41,8 @@ __global__ __launch_bounds__(256) void k_peak(uint32_t* sink, int iters, uint32_
   for (int c = 0; c < kChains; ++c) S[c] = v4i{static_cast<int>(x[c]), 0, 0, 0};
   const long a8 = static_cast<long>(static_cast<uint64_t>(x[0]) * 0x0101010101010101ull);
   const long b8 = static_cast<long>(static_cast<uint64_t>(y) * 0x0001000100010001ull);
+  const v4i a16{static_cast<int>(a8), static_cast<int>(a8 >> 32), static_cast<int>(x[1]), static_cast<int>(x[2])};
+  const v4i b16{static_cast<int>(b8), static_cast<int>(b8 >> 32), static_cast<int>(y), static_cast<int>(z)};
   for (int i = 0; i < iters; ++i) {
 #pragma unroll
     for (int c = 0; c < kChains; ++c) {
@@ -47,14 +51,15 @@ __global__ __launch_bounds__(256) void k_peak(uint32_t* sink, int iters, uint32_
       else if constexpr (KIND == 2) acc[c] = static_cast<uint64_t>(static_cast<uint32_t>(acc[c])) * y + acc[c];
       else if constexpr (KIND == 3) x[c] = mmul(x[c], y, p, pinv);
       else if constexpr (KIND == 4) x[c] = mmad3(y, x[c], z, x[c], y, x[c] ^ 1u, p, pinv);
-      else S[c] = __builtin_amdgcn_mfma_i32_16x16x32_i8(a8, b8, S[c], 0, 0, 0);
+      else if constexpr (KIND == 5) S[c] = __builtin_amdgcn_mfma_i32_16x16x32_i8(a8, b8, S[c], 0, 0, 0);
+      else S[c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a16, b16, S[c], 0, 0, 0);
     }
   }
   uint32_t r = 0;
 #pragma unroll
   for (int c = 0; c < kChains; ++c) {
     if constexpr (KIND == 2) r ^= static_cast<uint32_t>(acc[c] ^ (acc[c] >> 32));
-    else if constexpr (KIND == 5) r ^= static_cast<uint32_t>(S[c][0] ^ S[c][1] ^ S[c][2] ^ S[c][3]);
+    else if constexpr (KIND >= 5) r ^= static_cast<uint32_t>(S[c][0] ^ S[c][1] ^ S[c][2] ^ S[c][3]);
     else r ^= x[c];
   }
   if (r == 0x9E3779B9u) sink[t] = r;  // keeps the chains live; practically never taken
@@ -78,7 +83,7 @@ using namespace rsl;
 // buffer of at least cus * 4 * waves_per_simd * 64 words (written almost never).
 extern "C" int rsl_peak_rate(int device, int kind, int cus, int waves_per_simd, int iters, int reps,
                              uint32_t* sink, double* ops_per_s) {
-  if (!ops_per_s || !sink || kind < 0 || kind > 5 || cus < 1 || waves_per_simd < 1 || iters < 1 || reps < 1)
+  if (!ops_per_s || !sink || kind < 0 || kind > 6 || cus < 1 || waves_per_simd < 1 || iters < 1 || reps < 1)
     return -1;
   if (hipSetDevice(device) != hipSuccess) return -2;
   const uint32_t p = 1431655751u;  // the largest prime below 2^32 / 3, as in the library's table
@@ -93,7 +98,8 @@ extern "C" int rsl_peak_rate(int device, int kind, int cus, int waves_per_simd, 
       case 2: return launch_peak<2>(blocks, sink, iters, p, pc.pinv, nullptr);
       case 3: return launch_peak<3>(blocks, sink, iters, p, pc.pinv, nullptr);
       case 4: return launch_peak<4>(blocks, sink, iters, p, pc.pinv, nullptr);
-      default: return launch_peak<5>(blocks, sink, iters, p, pc.pinv, nullptr);
+      case 5: return launch_peak<5>(blocks, sink, iters, p, pc.pinv, nullptr);
+      default: return launch_peak<6>(blocks, sink, iters, p, pc.pinv, nullptr);
     }
   };
   int rc = 0;
@@ -110,8 +116,8 @@ extern "C" int rsl_peak_rate(int device, int kind, int cus, int waves_per_simd, 
   if (rc) return rc;
   const double lanes = static_cast<double>(blocks) * 256;
   const double steps = lanes * kChains * static_cast<double>(iters) * reps;
-  // a 16x16x32 product is 8192 multiply-adds per wave: 128 per lane
-  const double per_step = (kind == 5) ? 128.0 : 1.0;
+  // a 16x16x32 product is 8192 multiply-adds per wave, 128 per lane; 16x16x64 twice that
+  const double per_step = (kind == 6) ? 256.0 : (kind == 5) ? 128.0 : 1.0;
   *ops_per_s = steps * per_step / (ms * 1e-3);
   return 0;
 }

@@ -16,7 +16,7 @@ import os
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 KINDS = {0: "v_add_u32", 1: "v_mul_lo_u32", 2: "mad_u64_u32", 3: "montgomery_mul", 4: "fused_update_3_products",
-         5: "mfma_i32_16x16x32_i8_macs"}
+         5: "mfma_i32_16x16x32_i8_macs", 6: "mfma_i32_16x16x64_i8_macs"}
 
 
 def _lib():
@@ -45,7 +45,7 @@ def measure(device=0, waves=(4, 8), iters=4096, reps=5):
         best = 0.0
         for w in waves:
             r = ctypes.c_double()
-            it = iters if kind != 5 else max(1, iters // 8)
+            it = iters if kind < 5 else max(1, iters // 8)
             rc = lib.rsl_peak_rate(device, kind, cus, w, it, reps, ctypes.c_void_p(sink.data_ptr()), ctypes.byref(r))
             if rc:
                 raise RuntimeError(f"rsl_peak_rate({name}) failed: {rc}")

@@ -429,10 +429,9 @@ def pair_bench(a):
                 sys.exit(1)
             alt_jobs.append(j)
         inflight_sets.append((alt, alt_jobs))
-    # the autotuner times one launch at a time; when it kept a layout other than
-    # the default interpolation form (whole convolution sums, matrix-core
-    # products, other chunking), the default layout is timed in flight too, on
-    # contexts of its own (no cached choice), in each lane layout
+    # when the tuned choice (a loaded one) has partial sums other than the default
+    # layout's, the default layout is timed in flight too, on contexts of its own
+    # (no cached choice), in each lane layout
     dctx = []
     if extra and mode == "staged" and not a.eval_schur and any(
             tune.get(k, d) != d for k, d in (("conv_whole", 0), ("interp_mm", 0), ("chunk_target", 4096))):

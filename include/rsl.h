@@ -64,8 +64,7 @@ extern "C" {
 
 /* Environment read by rsl_ctx_create (test hooks): RSL_CRT_GARNER=1 makes the
  * CRT stage use Garner's mixed-radix digits for every coefficient instead of
- * the direct form (whose quotient estimate falls back to Garner only when it
- * cannot be decided); RSL_WIDE_VALU=1 runs the wide CRT's contraction on the
+ * the direct form; RSL_WIDE_VALU=1 runs the wide CRT's contraction on the
  * vector ALUs instead of the int8 matrix cores; RSL_EVAL_HORNER=1 keeps the
  * register-form evaluation on Horner's rule (vector ALUs) instead of the
  * int8 matrix-core sums.  In every case the results are identical. */
@@ -120,7 +119,8 @@ typedef struct {
   int32_t out_limbs;    /* limbs that always suffice for every coefficient */
   int32_t my, ny;       /* actual degrees in the eliminated variable */
   int32_t bad_primes;   /* primes skipped because they divide a leading coefficient */
-  size_t footprint_bytes; /* device workspace one rsl_res call needs */
+  size_t footprint_bytes; /* device workspace one rsl_res call needs: its buffers counted side
+                             by side (some share memory, so the call touches less) */
   size_t table_bytes;     /* bytes of the context's constant tables that cover this problem
                              (primes, factorials, checkpoint rows of the Stirling triangle,
                              CRT constants), rounded up as the context grows them */

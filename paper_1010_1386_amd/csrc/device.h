@@ -50,7 +50,8 @@ struct DevProblem {
   int evk, evpb;     // evaluation: lanes per (prime, point) pair (1, 2, 4), pairs per block (64 / evk)
   int regn;          // evaluation with the polynomials in registers up to this degree (8..32, the streamed
                      // form's lower degree up to 48), 0 = no
-  int crt_garner;    // 1: CRT by Garner's digits only (test hook), 0: direct form with Garner fallback
+  int crt_garner;    // column-sum CRT: 1: by Garner's digits only (test hook), 0: direct form, Garner's
+                     // digits where its quotient is undecided
   int schur;         // 1: univariate resultants by the Schur algorithm (one wave per pair)
   int newton_all;    // 1: every prime interpolates by divided differences (the Vandermonde
                      // solve of the gapped path), none by the consecutive-point products
@@ -92,11 +93,14 @@ struct DevProblem {
   uint32_t* hseg;         // np * hstride: per segment of kCkpt rows, the monomial coefficients of
                           // sum_t a_{k0+t} (x - k0)^(t) (basis change from checkpoint rows)
   int hstride;            // D+1 rounded up to kCkpt
-  uint32_t* wT;           // wdpad * wnpad  t_{k,i} = u_{k,i} (M / p_i)^{-1} mod p_i, zero padded (wide path)
+  uint32_t* wT;           // wdpad * wnpad  t_{k,i} = u_{k,i} (M / p_i)^{-1} mod p_i (wide path); the padding, rows
+                          // beyond D and primes beyond np, holds anything: the matrix-core pass reads it
+                          // against the zero digits of wMd and stores no such row, the other pass masks it
   uint32_t* wq;           // D+1         quotient estimate floor(sum_i f_{k,i} / 2^32) (wide path)
   uint64_t* wS;           // (D+1) * Lw * 2  column sum of each limb as (low, high) 64-bit words (wide path)
   uint64_t* wsum;        // wide_mfma: sums of t over the primes, per coefficient
-  int8_t* wMd;            // 5 * wlpad * wnpad  7-bit digit planes of the M_i limbs, [digit][limb][prime] (stage_wide_digits)
+  int8_t* wMd;            // 4 * wlpad * wnpad  digit planes of the M_i limbs, [digit][limb][prime]: base-256 digits of
+                          // limb - 0x80808080, zero for primes beyond np (stage_wide_digits; wide_mfma)
   int wdpad, wlpad, wnpad;// D+1, Lw and np rounded up (64, 32, 64); wT rows have wnpad entries
   int wide_mfma;          // 1: contraction on the matrix cores
   uint32_t* out;          // (D+1) * L_out two's complement limbs of R

@@ -102,7 +102,6 @@ struct Job {
   bool lean = false;
   // scratch of job_build, kept with the job so that a job object reused for
   // the next batch reuses its host memory (no fresh pages per call)
-  std::vector<WorkItem> tmp_items;
   std::vector<int> tmp_a, tmp_b, tmp_c;
 };
 

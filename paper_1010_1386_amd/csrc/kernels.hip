@@ -12,7 +12,10 @@
 //               polynomials; falling-factorial -> monomial basis
 //   interp_newton divided differences on a gapped point set (bad points replaced)
 //                                                         (Sec. 4.1, step 3)
-//   crt         direct form with Garner fallback + radix conversion to limbs (Sec. 4.1, step 3)
+//   crt_mm      direct form, limb sums on the matrix cores, an undecided quotient settled by
+//               the sign of Y - M                        (Sec. 4.1, step 3)
+//   crt         direct form by column sums with Garner fallback (gcds and jobs without room for
+//               the digits, the Garner hook); crt_wide_* beyond 512 primes
 //   crt_wide_*  the direct form in three passes for problems with many primes
 //   stirling_build  per-prime table of Stirling numbers of the first kind
 #include <hip/hip_runtime.h>

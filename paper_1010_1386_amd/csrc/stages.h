@@ -2024,9 +2024,6 @@ __device__ inline void stage_interp_newton(const DevProblem& P, const DevTables&
 
 // ----------------------------------------------------------------------- CRT
 
-// Whether the Garner table (np^2 words) and the limb table of the prefix
-// products (np L_out words) of a problem are staged in LDS by the CRT kernel,
-// and the CRT block's LDS words.
 // dst[t] = src(t) for t < n with the block's threads; every thread issues up
 // to eight loads (clamped to valid indices) before storing any, so a small
 // table costs about one memory latency.
@@ -2314,7 +2311,7 @@ __device__ __forceinline__ uint32_t coeff_of(const DevProblem& P, const uint64_t
 // item's coefficients are summed from the basis-change partial sums, with the
 // block's threads reading kCrtBlockCoeffs consecutive coefficients of one
 // prime together.
-constexpr int kCrtItemsPerBlock = 4;  // items per block of the staged launch
+constexpr int kCrtItemsPerBlock = 4;  // items per block of the staged launch, from 1024 items on
 template <int NS>
 __device__ inline void stage_crt(const DevProblem& P, const DevTables& T, const WorkItem& w, uint32_t* lds,
                                  int cpw, bool fresh, bool whole) {
@@ -2728,7 +2725,8 @@ __device__ inline void stage_crt_wide_sum(const DevProblem& P, const WorkItem& w
 // resultants of degree 225 over 2025 primes: 289 -> 215 us).  The column sum is
 // below 2^85.  The limb digits are planes Md[b][t][i] (a limb's primes
 // contiguous); the block stages its 32 limbs x 64 primes x 4 digits in LDS once
-// per step for its four waves.  The t values come from wT (rows padded with zeros to wnpad)
+// per step for its four waves.  The t values come from wT (beyond the last prime it
+// holds anything, which meets the zero digits that stage_wide_digits writes there)
 // and are split into digits in registers.  Wave w takes coefficients
 // k0 + 16 w ... (one 16-row tile) and the block's 32 limbs (two 16-column
 // tiles); a lane holds row r of A and column r of B for the 16 primes of its
@@ -2749,7 +2747,9 @@ typedef int wide_v4i __attribute__((ext_vector_type(4)));
 // lane per prime), joined by the power 2^(-8 t0).  So every block starts by
 // itself, and the M_i, np times as long as M, are neither uploaded nor stored.
 // Wave 0 then walks the block's 64 limbs, and the digits go out as 16-byte
-// words of 16 primes (zero beyond the last prime or limb).  Bound by the chains'
+// words of 16 primes: zero beyond the last prime, which the contraction relies on (it
+// reads t values there that nothing writes); those beyond the last limb are not used.
+// Bound by the chains'
 // latency, 27 us for 2025 primes and 1925 limbs; as a transposition of uploaded
 // M_i it took 19 us, behind 0.55 ms for their 15.6 MB (image and transfer).
 constexpr int kWideDigitLimbs = 64;

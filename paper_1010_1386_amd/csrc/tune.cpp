@@ -443,7 +443,7 @@ int rsl_job_tune(rsl_ctx* ctx, rsl_job* j, int reps, rsl_tune_result* best) {
                   "autotuner: candidate (mode " + std::to_string(tc.mode) + ", chunk target " +
                       std::to_string(tc.chunk_target) + ", grid x" + std::to_string(tc.grid_mult) +
                       ", lanes per pair " + std::to_string(tc.evk) + ", Schur " + std::to_string(tc.schur) +
-                      ", matrix-core interpolation " + std::to_string(tc.interp_mm) +
+                      ", whole partial sums " + std::to_string(tc.interp_mm) +
                       ") differs from the first candidate in its statuses or outputs (byte " + std::to_string(at) +
                       " of the compared image)");
     }

@@ -1041,11 +1041,13 @@ __device__ __forceinline__ const uint4* ev_tiles(const DevProblem& P, int slot, 
 // generic pattern (or whose leading coefficient vanishes) starts over: the
 // values of both polynomials are formed again, 32 points at a time, in the
 // same LDS, and the general column code runs on them in place.
-// Bound by VALU issue: 0.74 and 0.78 of the 4-cycle rate at lower degrees up to
-// 24 and 32 on 256 pairs of the batch workload (4.1 K and 4.9 K instructions per
-// 64 pairs), 0.6-0.67 with two K slices; the matrix cores are busy for about a
-// quarter of it.  That workload's evaluation went from 1394 us (both values in
-// LDS, five 7-bit digits, canonical residues, long divisions from LDS) to 0.9 ms.
+// Bound by VALU issue: 0.86 of the 4-cycle rate at lower degrees up to 24 and 32 on the
+// 512 pairs of the batch workload (4.2 K and 5.1 K instructions per 64 pairs, 469 and
+// 366 us), 0.64-0.71 with two K slices where the launch fills the chip (64 requests of
+// degrees 8..48, lower degrees up to 32, 40 and 48: 180, 387 and 161 us); the matrix
+// cores are busy for an eighth to a sixth of it.  256 pairs went from 1394 us (both
+// values in LDS, five 7-bit digits, canonical residues, long divisions from LDS) to
+// 0.9 ms.
 // LDS: 64 rows of kStreamFront zeros and the values, at an odd stride.
 __host__ __device__ inline int eval_stream_row_stride(const DevProblem& P) {
   return ((P.my > P.ny ? P.my : P.ny) + 1 + kStreamFront) | 1;
